@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <functional>
 #include <new>
 #include <string>
 #include <vector>
@@ -107,6 +108,8 @@ struct Regions {
     size_t samples, items, mode_start, idx, J, chunk_start, cx, cyz, cJ, pair_start, pidx, pJ, fields, ell_start, gidx16, gidx32, gJ, c0, quads, Jq, amp, E, E64, drift, temp_of, copy_at, beta, beta64;
     size_t acc_begin, acc, swap_acc, obs, hist, hist_I, spec, series_e, series_q, meas_cnt, counters, acc_end;
     size_t scratch, scratch_doubles, rs_part, mlp, total;
+    size_t slot_items;  // one item per copy, in the order of temperature slots
+    size_t p_samples, p_rest, p_modes, p_rank, p_tile, p_first, p_desc, p_fields, p_draws, p_order, p_after, p_prod, p_list, p_band, p_end;
 };
 
 int check_config(const rlpt_config* cfg) {
@@ -250,6 +253,39 @@ bool build_cached_tables(const rlpt_graph* g, int layout, std::vector<uint32_t>*
     return true;
 }
 
+// copies of one sample in the banded product: whole matrix-core tiles for large N
+size_t pair_copies(const rlpt_config& cfg, int N) {
+    const size_t R = (size_t)cfg.n_temps * cfg.n_reps;
+    return N > kGatherModes ? (R + kCopyTile - 1) / kCopyTile * kCopyTile : R;
+}
+
+// Samples of a context that the pair-space sweep serves: those with a narrow
+// band (complete graphs, N <= 256) from kPairModes modes on, in FP32, unless
+// the caller names a launch tile (a tile belongs to the list-streaming
+// kernels).  Below, a sweep from the lists is as fast or faster (us per sweep,
+// lists -> pairs, 64 copies of 8 samples on an MI355X: N = 64 70 -> 67, 96 158
+// -> 115, 128 261 -> 186, 200 972 -> 502).  The tables take about 5 times the
+// lists' memory (the per-pair entries), so past kPairTableBytes the context
+// keeps to the lists.
+constexpr int kPairModes = 88;
+constexpr size_t kPairTableBytes = (size_t)64 << 30;
+
+std::vector<int> pair_samples(const rlpt_config& cfg, const rlpt_graph* const* g, int S) {
+    std::vector<int> served;
+    if (cfg.precision != RLPT_FP32 || cfg.field_mode != RLPT_FIELDS_STREAM || cfg.block_threads > 0 ||
+        cfg.copies_per_block > 0)
+        return served;
+    size_t bytes = 0;
+    for (int i = 0; i < S; ++i) {
+        if (g[i]->N < kPairModes || g[i]->pair_modes.empty()) continue;
+        served.push_back(i);
+        bytes += g[i]->band_entries * 4 + g[i]->pair_modes.size() * pair_copies(cfg, g[i]->N) * 8 +
+                 kListUnit * (size_t)g[i]->pair_first.back() * sizeof(PairEntry);
+    }
+    if (bytes > kPairTableBytes) served.clear();
+    return served;
+}
+
 int check_graphs(const rlpt_graph* const* g, int n) {
     if (!g || n < 1) return fail(RLPT_E_ARG, "need at least one graph");
     for (int i = 0; i < n; ++i)
@@ -326,6 +362,35 @@ Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layo
     r.scratch_doubles = std::max<size_t>(2 * amp, 8192);
     r.scratch = L.take(r.scratch_doubles * 8);
     r.rs_part = L.take(copies * kResyncParts * 8);
+    r.slot_items = L.take(copies * sizeof(ItemDev));
+    const std::vector<int> served = pair_samples(cfg, g, S);
+    if (!served.empty()) {
+        size_t np = 0, rank = 0, tiles = 0, band = 0, list = 0, prod = 0, desc = 0;
+        for (int i : served) {
+            np += g[i]->pair_modes.size();
+            rank += g[i]->pair_rank.size();
+            desc += (size_t)g[i]->N * (g[i]->N + 1);
+            tiles += g[i]->pair_tile.size() / 2;
+            band += g[i]->band_entries;
+            prod += g[i]->pair_modes.size() * pair_copies(cfg, g[i]->N);
+            list += kListUnit * (size_t)g[i]->pair_first.back();
+        }
+        r.p_samples = L.take(S * sizeof(PairSample));
+        r.p_rest = L.take(copies * sizeof(ItemDev));
+        r.p_modes = L.take(np * 2);
+        r.p_rank = L.take(rank * 2);
+        r.p_tile = L.take(tiles * 8);
+        r.p_first = L.take(modes * 4);
+        r.p_desc = L.take(desc * 2);
+        r.p_fields = L.take(amp * 8);
+        r.p_draws = L.take(copies * (max_N / 2) * kPairDrawBytes);
+        r.p_order = L.take(copies * max_N * 2);
+        r.p_after = L.take(copies * (max_N / 2 + 1) * 2);
+        r.p_prod = L.take(prod * 8);
+        r.p_list = L.take(list * sizeof(PairEntry));
+        r.p_band = L.take(band * 4);
+        r.p_end = L.off;
+    }
     r.mlp = L.off;
     L.off = mlp_layout(cfg, g[0]->N, S, nullptr, nullptr, L.off);
     r.total = L.off;
@@ -375,6 +440,25 @@ void fill_ptrs(DevPtrs<R>& P, unsigned char* b, const Regions& r) {
     P.rs_part = reinterpret_cast<double*>(b + r.rs_part);
 }
 
+void fill_pair_ptrs(PairDev& Q, unsigned char* b, const Regions& r, int max_N) {
+    Q.samples = reinterpret_cast<const PairSample*>(b + r.p_samples);
+    Q.items = reinterpret_cast<const ItemDev*>(b + r.slot_items);
+    Q.pm = reinterpret_cast<const uint16_t*>(b + r.p_modes);
+    Q.pos = reinterpret_cast<const uint16_t*>(b + r.p_rank);
+    Q.tile = reinterpret_cast<const uint2*>(b + r.p_tile);
+    Q.first = reinterpret_cast<const uint32_t*>(b + r.p_first);
+    Q.band = reinterpret_cast<float*>(b + r.p_band);
+    Q.desc = reinterpret_cast<uint16_t*>(b + r.p_desc);
+    Q.list = reinterpret_cast<PairEntry*>(b + r.p_list);
+    Q.prod = reinterpret_cast<float2*>(b + r.p_prod);
+    Q.fields = reinterpret_cast<float2*>(b + r.p_fields);
+    Q.draws = b + r.p_draws;
+    Q.order = reinterpret_cast<uint16_t*>(b + r.p_order);
+    Q.after = reinterpret_cast<uint16_t*>(b + r.p_after);
+    Q.max_N = max_N;
+    Q.max_steps = max_N / 2;
+}
+
 template <typename T>
 hipError_t upload(unsigned char* base, size_t off, const std::vector<T>& v, hipStream_t st) {
     if (v.empty()) return hipSuccess;
@@ -418,7 +502,15 @@ int enqueue_sweeps(rlpt_ctx* c, int64_t done, int64_t n, int64_t* swaps_added) {
             }
             HIP_TRY(hipEventRecord(ev.first, c->stream), "event record");
         }
-        HIP_TRY(launch_sweep(cfg.precision, c->ptrs(), c->sh, c->launch, (int)step, c->stream), "sweep launch");
+        if (c->pair_launch.empty()) {
+            HIP_TRY(launch_sweep(cfg.precision, c->ptrs(), c->sh, c->launch, (int)step, c->stream), "sweep launch");
+        } else {
+            for (int w = 0; w < (int)step; ++w)
+                for (const PairLaunch& L : c->pair_launch)
+                    HIP_TRY(launch_sweep_pairs(c->pf, c->pairs, c->sh, L, w, c->stream), "sweep launch");
+            if (c->rest.n_items > 0)
+                HIP_TRY(launch_sweep(RLPT_FP32, &c->pf_rest, c->sh, c->rest, (int)step, c->stream), "sweep launch");
+        }
         if (ev.first) {
             HIP_TRY(hipEventRecord(ev.second, c->stream), "event record");
             c->events.push_back(ev);
@@ -457,16 +549,18 @@ int sync_and_flags(rlpt_ctx* c) {
 // Cached-field contexts name temperature slots instead, hottest first (the
 // copies with the most accepted moves, hence field updates, start first); the
 // kernel finds each slot's copy in copy_at.
-int build_items(rlpt_ctx* c, int block, const std::map<int, int>& copies) {
+int lay_items(rlpt_ctx* c, int block, const std::map<int, int>& copies, const std::vector<int>& samples,
+              std::vector<ItemDev>* out, SweepLaunch* launch) {
     if (block < 64 || block > 1024 || (block & (block - 1))) return fail(RLPT_E_ARG, "bad workgroup size");
     std::vector<ItemDev> items;
     int max_cpi = 1;
-    std::vector<int> order(c->S);
-    for (int s = 0; s < c->S; ++s) order[s] = s;
+    std::vector<int> order(samples);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b2) { return c->N[a] > c->N[b2]; });
-    // every copy group is sized for the largest N of the context: cap the copies
+    // every copy group is sized for the largest N of the launch: cap the copies
     // per workgroup so that the groups fit in 64 KiB of LDS
-    const size_t per_copy = sweep_lds_bytes(c->cfg.precision, block, 1, c->max_N, c->sh.cached, c->sh.short_lists);
+    int max_N = 0;
+    for (int i : samples) max_N = std::max(max_N, c->N[i]);
+    const size_t per_copy = sweep_lds_bytes(c->cfg.precision, block, 1, max_N, c->sh.cached, c->sh.short_lists);
     const int lds_cap = (int)std::max<size_t>(1, (64 * 1024) / per_copy);
     for (int s : order) {
         auto it_c = copies.find(c->N[s]);
@@ -509,7 +603,7 @@ int build_items(rlpt_ctx* c, int block, const std::map<int, int>& copies) {
         }
         items.swap(rr);
     }
-    const size_t lds = sweep_lds_bytes(c->cfg.precision, block, max_cpi, c->max_N, c->sh.cached, c->sh.short_lists);
+    const size_t lds = sweep_lds_bytes(c->cfg.precision, block, max_cpi, max_N, c->sh.cached, c->sh.short_lists);
     if (lds > 64 * 1024) return fail(RLPT_E_ARG, "sweep tile needs more than 64 KiB of LDS; use fewer copies per block");
     // streaming sweep over chunked lists: hold a step's chunks in registers
     // ahead when every list of the launch fits 1, 2 or 4 chunks per thread; if
@@ -535,15 +629,24 @@ int build_items(rlpt_ctx* c, int block, const std::map<int, int>& copies) {
             prefetch = pf(need);
         }
     }
-    c->items = items;
+    launch->block_threads = block;
+    launch->n_items = (int)items.size();
+    launch->max_copies_per_item = max_cpi;
+    launch->max_N = max_N;
+    launch->prefetch = prefetch;
+    launch->split = split;
+    launch->lds_bytes = lds;
+    out->swap(items);
+    return RLPT_OK;
+}
+
+// the launch over every sample
+int build_items(rlpt_ctx* c, int block, const std::map<int, int>& copies) {
+    std::vector<int> all(c->S);
+    for (int s = 0; s < c->S; ++s) all[s] = s;
+    int rc = lay_items(c, block, copies, all, &c->items, &c->launch);
+    if (rc) return rc;
     c->tile_copies = copies;
-    c->launch.block_threads = block;
-    c->launch.n_items = (int)items.size();
-    c->launch.max_copies_per_item = max_cpi;
-    c->launch.max_N = c->max_N;
-    c->launch.prefetch = prefetch;
-    c->launch.split = split;
-    c->launch.lds_bytes = lds;
     c->sh.by_slot = c->sh.cached;
     return RLPT_OK;
 }
@@ -554,6 +657,127 @@ int upload_items(rlpt_ctx* c) {
             "upload items");
     HIP_TRY(hipStreamSynchronize(c->stream), "stream synchronize");
     return RLPT_OK;
+}
+
+// tile of a launch over the samples counted by N: the tuned one, else the built-in one
+void streaming_tile(const rlpt_ctx* c, const std::map<int, int>& counts, int* block, std::map<int, int>* copies) {
+    if (tune_choose(counts, c->cfg.precision, c->cfg.shared_pairs, block, copies)) return;
+    *block = default_tile(counts.rbegin()->first).block;
+    for (const auto& nc : counts) (*copies)[nc.first] = default_tile(nc.first).copies;
+    // the one-wave-per-copy path of short lists packs copies by itself
+    if (!c->sh.short_lists) spread_tile(counts, c->Rc, 512, block, copies);
+}
+
+std::map<int, std::vector<int>, std::greater<int>> samples_by_N(const rlpt_ctx* c) {
+    std::map<int, std::vector<int>, std::greater<int>> m;
+    for (int s = 0; s < c->S; ++s) m[c->N[s]].push_back(s);
+    return m;
+}
+
+// one item per copy: largest N first; within one N the samples in turn (each
+// XCD takes every eighth workgroup, so it reads few samples' lists), and each
+// sample's temperature slots from the hottest, which accepts the most updates
+std::vector<ItemDev> slot_items(const rlpt_ctx* c) {
+    std::vector<ItemDev> items;
+    for (const auto& kv : samples_by_N(c))
+        for (int i = 0; i < c->Rc; ++i)
+            for (int s : kv.second) {
+                ItemDev it{};
+                it.first_copy = s * c->Rc + i;
+                it.n_copies = 1;
+                it.sample = s;
+                items.push_back(it);
+            }
+    return items;
+}
+
+// pair-space sweep: uploads the samples' band structure, fills the tables on
+// the device from the lists already there, and lays out the launches: one per
+// N it serves, and the list-streaming kernel's over the items of the others
+hipError_t build_pairs(rlpt_ctx* c, const rlpt_graph* const* g, const std::vector<int>& served,
+                       unsigned char* b, const Regions& r) {
+    fill_pair_ptrs(c->pairs, b, r, c->max_N);
+    std::vector<PairSample> smp(c->S);
+    std::vector<uint16_t> pm, rank;
+    std::vector<uint32_t> tile, first;
+    PairSample at{};
+    int64_t max_quads = 0;
+    for (int s = 0; s < c->S; ++s) {
+        const rlpt_graph* q = g[s];
+        if (!std::binary_search(served.begin(), served.end(), s)) {  // N = 0: the kernels pass over it
+            first.resize(first.size() + q->N + 1);
+            continue;
+        }
+        smp[s] = at;
+        smp[s].N = q->N;
+        smp[s].n_pairs = (int32_t)q->pair_modes.size();
+        smp[s].n_tiles = (int32_t)(q->pair_tile.size() / 2);
+        at.pm_base += smp[s].n_pairs;
+        at.pos_base += (int64_t)q->pair_rank.size();
+        at.tile_base += smp[s].n_tiles;
+        at.band_base += (int64_t)q->band_entries;
+        at.prod_base += (int64_t)(q->pair_modes.size() * pair_copies(c->cfg, q->N));
+        at.desc_base += (int64_t)q->N * (q->N + 1);
+        at.list_base += kListUnit * (int64_t)q->pair_first.back();
+        pm.insert(pm.end(), q->pair_modes.begin(), q->pair_modes.end());
+        rank.insert(rank.end(), q->pair_rank.begin(), q->pair_rank.end());
+        tile.insert(tile.end(), q->pair_tile.begin(), q->pair_tile.end());
+        first.insert(first.end(), q->pair_first.begin(), q->pair_first.end());
+        max_quads = std::max<int64_t>(max_quads, q->n_terms());
+    }
+    int first_item = 0;
+    for (const auto& kv : samples_by_N(c)) {
+        std::vector<int> mine;
+        for (int s : kv.second)
+            if (smp[s].N > 0) mine.push_back(s);
+        if (mine.size() == kv.second.size()) {  // a class is served as a whole or not at all
+            PairLaunch L{};
+            L.N = kv.first;
+            L.first = first_item;
+            L.samples = (int)mine.size();
+            L.n = L.samples * c->Rc;
+            const int per_block = 4 * pairs_tiles_per_wave(kv.first);
+            for (int s : mine) {
+                const std::vector<uint32_t>& t = g[s]->pair_tile;
+                const int n = (int)t.size() / 2;
+                for (int b0 = 0; b0 < n; b0 += per_block) {
+                    const uint32_t lo = t[2 * b0 + 1], hi = t[2 * std::min(b0 + per_block, n) - 1];
+                    L.columns = std::max(L.columns, (int)(hi & 0xffffu) + 4 * (int)(hi >> 16) - (int)(lo & 0xffffu) + 4);
+                }
+            }
+            c->pair_launch.push_back(L);
+        } else {
+            for (int s : mine) smp[s].N = 0;
+        }
+        first_item += (int)kv.second.size() * c->Rc;
+    }
+    std::vector<ItemDev> rest;
+    std::vector<int> others;
+    std::map<int, int> counts;
+    for (int s = 0; s < c->S; ++s)
+        if (smp[s].N == 0) {
+            others.push_back(s);
+            counts[c->N[s]] += 1;
+        }
+    c->rest = SweepLaunch{};
+    if (!others.empty()) {
+        int block = 0;
+        std::map<int, int> copies;
+        streaming_tile(c, counts, &block, &copies);
+        if (lay_items(c, block, copies, others, &rest, &c->rest) != RLPT_OK) return hipErrorInvalidValue;
+    }
+    c->pf_rest = c->pf;
+    c->pf_rest.items = reinterpret_cast<const ItemDev*>(b + r.p_rest);
+    hipError_t e = upload(b, r.p_samples, smp, c->stream);
+    if (e == hipSuccess) e = upload(b, r.p_rest, rest, c->stream);
+    if (e == hipSuccess) e = upload(b, r.p_modes, pm, c->stream);
+    if (e == hipSuccess) e = upload(b, r.p_rank, rank, c->stream);
+    if (e == hipSuccess) e = upload(b, r.p_tile, tile, c->stream);
+    if (e == hipSuccess) e = upload(b, r.p_first, first, c->stream);
+    if (e == hipSuccess) e = launch_zero(b + r.p_list, r.p_end - r.p_list, c->stream);
+    if (e == hipSuccess) e = launch_pairs_tables(c->pf, c->pairs, c->sh, c->S, c->max_N, max_quads, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);  // the host vectors end here
+    return e;
 }
 
 void drop_events(rlpt_ctx* c) {
@@ -775,15 +999,13 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
         std::map<int, int> counts;
         for (int s = 0; s < c->S; ++s) counts[c->N[s]] += 1;
         // the tune registry holds streaming-sweep timings; cached contexts use the built-in tile
-        if (cfg->block_threads > 0 || cfg->copies_per_block > 0 || c->sh.cached ||
-            !tune_choose(counts, cfg->precision, cfg->shared_pairs, &block, &copies)) {
+        if (cfg->block_threads > 0 || cfg->copies_per_block > 0 || c->sh.cached) {
             auto tile = [&](int n) { return c->sh.cached ? default_tile_cached(n) : default_tile(n); };
             block = cfg->block_threads > 0 ? cfg->block_threads : tile(c->max_N).block;
             for (const auto& nc : counts)
                 copies[nc.first] = cfg->copies_per_block > 0 ? cfg->copies_per_block : tile(nc.first).copies;
-            // the one-wave-per-copy path of short lists packs copies by itself
-            if (cfg->block_threads <= 0 && cfg->copies_per_block <= 0 && !c->sh.cached && !c->sh.short_lists)
-                spread_tile(counts, c->Rc, 512, &block, &copies);
+        } else {
+            streaming_tile(c, counts, &block, &copies);
         }
         rc = build_items(c, block, copies);
         if (rc) {
@@ -846,6 +1068,10 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
     if (cfg->precision == RLPT_FP64) up(r.beta, b64);
     else up(r.beta, b32);
     up(r.beta64, b64);
+    const std::vector<ItemDev> by_slot = slot_items(c);
+    up(r.slot_items, by_slot);
+    const std::vector<int> served = pair_samples(*cfg, graphs, n_graphs);
+    if (!served.empty() && e == hipSuccess) e = build_pairs(c, graphs, served, b, r);
     if (e == hipSuccess) e = launch_zero(c->acc_region, c->acc_region_bytes, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {

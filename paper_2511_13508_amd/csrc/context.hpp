@@ -8,6 +8,7 @@
 
 #include "internal.hpp"
 #include "mlp.hpp"
+#include "pairs.hpp"
 
 using rlpt::DevPtrs;
 using rlpt::ItemDev;
@@ -28,6 +29,12 @@ struct rlpt_ctx {
     SweepLaunch launch{};
     DevPtrs<float> pf{};
     DevPtrs<double> pd{};
+    // pair-space sweep: its tables and one launch per N it serves; the samples
+    // it does not serve are swept from their lists (rest)
+    rlpt::PairDev pairs{};
+    std::vector<rlpt::PairLaunch> pair_launch;
+    DevPtrs<float> pf_rest{};
+    SweepLaunch rest{};
     // regions of the workspace
     void* ws = nullptr;
     size_t ws_bytes = 0;

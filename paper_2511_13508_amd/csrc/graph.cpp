@@ -17,6 +17,7 @@
 #include <unordered_set>
 
 #include "internal.hpp"
+#include "pairs.hpp"
 #include "philox.hpp"
 
 namespace {
@@ -72,6 +73,63 @@ bool sparse_terms(rlpt_graph* g, const rlpt_graph_desc* d) {
         ++kept;
     }
     return kept == c;
+}
+
+// Band structure of the couplings in pair space: pairs sorted by the sum of
+// their frequencies, and for each pair the ranks of the pairs whose sum lies
+// within gamma of its own (a hair wider, so that rounding in the filter's test
+// cannot put a term outside).  32 rows are stored over the columns of them all
+// (matrix-core tiles).  Left empty where the band would hold mostly
+// zeros (sparse graphs).
+void pair_band(rlpt_graph* g) {
+    const int N = g->N;
+    const double* w = g->omega.data();
+    const double tol = g->gamma * (1.0 + 1e-9) + 1e-12;
+    const int P = N * (N - 1) / 2;
+    std::vector<std::pair<double, uint32_t>> order;
+    order.reserve(P);
+    for (int p = 0; p < N; ++p)
+        for (int s = p + 1; s < N; ++s) order.push_back({w[p] + w[s], (uint32_t)(p | s << 8)});
+    std::sort(order.begin(), order.end());
+    std::vector<int> lo(P), hi(P);
+    for (int a = 0, l = 0, h = 0; a < P; ++a) {
+        while (order[l].first <= order[a].first - tol) ++l;
+        while (h < P && order[h].first < order[a].first + tol) ++h;
+        lo[a] = l;
+        hi[a] = h;
+    }
+    std::vector<uint32_t> tile;
+    size_t off = 0;
+    for (int a = 0; a < P; a += 32) {  // rows [a, a + 32): columns [lo of the first, hi of the last)
+        const int last = std::min(P, a + 32) - 1;
+        const uint32_t n4 = (uint32_t)(hi[last] - lo[a] + 3) / 4;
+        tile.push_back((uint32_t)off);
+        tile.push_back((uint32_t)lo[a] | n4 << 16);
+        off += (size_t)n4 * 4 * 32;
+    }
+    // per source, its entries by target, in units of 16: three per list entry,
+    // role 0 padded to 32 and role 1 to 16 for each target; unit 0 is zero
+    std::vector<uint32_t> first(N + 1);
+    uint32_t at = 1, most = 0, widest = 0;
+    for (int l = 0; l <= N; ++l) {
+        first[l] = at;
+        if (l < N) at += (3 * (g->mode_start[l + 1] - g->mode_start[l]) + 46 * (uint32_t)N + 15) / 16;
+        most = std::max(most, at - first[l]);
+    }
+    for (int a = 0; a < P; ++a) widest = std::max(widest, (uint32_t)(hi[a] - lo[a]));
+    if (off > 8 * (size_t)g->n_terms() + 16384 || off > 0xffffffffull ||
+        most >= 1u << rlpt::kStartBits || (widest + 31) / 32 >= 1u << (16 - rlpt::kStartBits))
+        return;
+    g->pair_first.swap(first);
+    g->band_entries = off;
+    g->pair_tile.swap(tile);
+    g->pair_modes.resize(P);
+    g->pair_rank.assign((size_t)N * N, 0);
+    for (int a = 0; a < P; ++a) {
+        const uint32_t v = order[a].second, p = v & 255u, s = v >> 8;
+        g->pair_modes[a] = (uint16_t)v;
+        g->pair_rank[p * N + s] = g->pair_rank[s * N + p] = (uint16_t)a;
+    }
 }
 
 }  // namespace
@@ -204,6 +262,7 @@ extern "C" int rlpt_graph_build(const rlpt_graph_desc* d, rlpt_graph** out) {
                 g->chunk_start[l + 1] = (uint32_t)g->cx.size();
             }
         }
+        if (N <= kMaxChunkModes && d->mean_degree <= 0) pair_band(g);
     } catch (const std::bad_alloc&) {
         delete g;
         return fail(RLPT_E_NOMEM, "rlpt_graph_build: out of host memory");

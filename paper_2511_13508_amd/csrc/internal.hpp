@@ -30,6 +30,13 @@ struct rlpt_graph {
     std::vector<uint8_t> cx;           // [chunks]
     std::vector<uint16_t> cyz;         // [4 * chunks]
     std::vector<double> cJ;            // [4 * chunks] (0 for padding)
+    // pairs p < s sorted by w_p + w_s (complete graphs, N <= 256; empty otherwise):
+    // terms couple pairs of nearby rank, so the couplings form a band
+    std::vector<uint16_t> pair_modes;  // [n_pairs] p | s << 8
+    std::vector<uint16_t> pair_rank;   // [N][N] rank of pair {l, x}
+    std::vector<uint32_t> pair_tile;   // [ceil(n_pairs / 32)][2] offset in the band, first column | columns / 4 << 16
+    size_t band_entries = 0;           // stored band values
+    std::vector<uint32_t> pair_first;  // [N + 1] bounds of each source's per-target entries, in 16s
     int64_t n_terms() const { return (int64_t)J.size(); }
 };
 

@@ -21,131 +21,12 @@
 #include <mutex>
 #include <math.h>
 
+#include "device.hpp"
 #include "internal.hpp"
-#include "philox.hpp"
+#include "lists.hpp"
 
 namespace rlpt {
 namespace {
-
-template <typename R>
-struct V2;
-template <>
-struct V2<float> {
-    using T = float2;
-};
-template <>
-struct V2<double> {
-    using T = double2;
-};
-template <typename R>
-using R2 = typename V2<R>::T;
-
-template <typename R>
-__device__ inline R2<R> mk2(R x, R y) {
-    R2<R> v;
-    v.x = x;
-    v.y = y;
-    return v;
-}
-
-template <typename R>
-__device__ inline R pi_v() {
-    return (R)3.14159265358979323846;
-}
-
-__device__ inline void sincos_r(float x, float* s, float* c) { sincosf(x, s, c); }
-__device__ inline void sincos_r(double x, double* s, double* c) { sincos(x, s, c); }
-
-// cross-lane moves within rows of 16 lanes (DPP: quad_perm [1,0,3,2] = 0xB1,
-// [2,3,0,1] = 0x4E, row_half_mirror = 0x141, row_mirror = 0x140) and reads of
-// one lane's value into every lane (v_readlane, the lane index wave-uniform)
-template <int CTRL>
-__device__ inline float dpp_move(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
-template <int CTRL>
-__device__ inline double dpp_move(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-__device__ inline float read_lane(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
-__device__ inline double read_lane(double v, int l) {
-    const long long b = __double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(b & 0xffffffffll), l);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), l);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ inline int read_lane(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
-__device__ inline uint32_t read_lane(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
-
-// sum over each row of 16 lanes, in every lane of the row
-template <typename R>
-__device__ inline R row_sum(R v) {
-    v += dpp_move<0xB1>(v);
-    v += dpp_move<0x4E>(v);
-    v += dpp_move<0x141>(v);
-    v += dpp_move<0x140>(v);
-    return v;
-}
-
-// row broadcasts (DPP row_bcast:15 = 0x142 into rows 1 and 3, row_bcast:31 =
-// 0x143 into rows 2 and 3); lanes of the other rows receive 0
-template <int CTRL, int ROWS>
-__device__ inline float dpp_bcast(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xF, false));
-}
-template <int CTRL, int ROWS>
-__device__ inline double dpp_bcast(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, ROWS, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xF, false);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-// sum over the wave, the same value in every lane (all lanes active)
-template <typename R>
-__device__ inline R wave_sum(R v) {
-    v = row_sum(v);
-    return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
-}
-
-// the same sum, valid in lane 63 only, without lane reads: rows 1 and 3 add
-// the totals of rows 0 and 2, then row 3 adds row 1's; (r3 + r2) + (r1 + r0)
-// rounds exactly as wave_sum's (r0 + r1) + (r2 + r3)
-template <typename R>
-__device__ inline R wave_sum_last(R v) {
-    v = row_sum(v);
-    v += dpp_bcast<0x142, 0xA>(v);
-    v += dpp_bcast<0x143, 0xC>(v);
-    return v;
-}
-
-// contribution J conj(a_x) a_y a_z of one packed entry
-template <typename R>
-__device__ inline void field_term(uint32_t e, R j, const R2<R>* __restrict__ a, R& fr, R& fi) {
-    const R2<R> ax = a[e & 1023u];
-    const R2<R> ay = a[(e >> 10) & 1023u];
-    const R2<R> az = a[e >> 20];
-    const R pr = ax.x * ay.x + ax.y * ay.y;
-    const R pi = ax.x * ay.y - ax.y * ay.x;
-    const R qr = pr * az.x - pi * az.y;
-    const R qi = pr * az.y + pi * az.x;
-    fr += j * qr;
-    fi += j * qi;
-}
-
-template <typename R>
-struct J4;
-template <>
-struct J4<float> {
-    using T = float4;
-};
-template <>
-struct J4<double> {
-    using T = double4;
-};
 
 // partial field of one mode's list, entries [beg, end) (multiples of 4),
 // thread t of nt threads takes every nt-th group of 4 entries
@@ -179,29 +60,6 @@ __device__ inline void field_partial(const uint32_t* __restrict__ idx, const R* 
         field_term<R>(i0.z, j0.z, a, fr, fi);
         field_term<R>(i0.w, j0.w, a, fr, fi);
     }
-}
-
-// chunked layout: a chunk holds 4 entries sharing the partner x; the field
-// contribution is conj(a_x) * sum_i J_i a_{y_i} a_{z_i}
-template <typename R>
-__device__ inline void chunk_pair(uint32_t v, R j, const R2<R>* __restrict__ a, R& gr, R& gi) {
-    const R2<R> ay = a[v & 0xffu];
-    const R2<R> az = a[(v >> 8) & 0xffu];
-    gr += j * (ay.x * az.x - ay.y * az.y);
-    gi += j * (ay.x * az.y + ay.y * az.x);
-}
-
-template <typename R>
-__device__ inline void chunk_term(uint32_t x, uint2 yz, typename J4<R>::T j, const R2<R>* __restrict__ a, R& fr,
-                                  R& fi) {
-    R gr = 0, gi = 0;
-    chunk_pair<R>(yz.x & 0xffffu, j.x, a, gr, gi);
-    chunk_pair<R>(yz.x >> 16, j.y, a, gr, gi);
-    chunk_pair<R>(yz.y & 0xffffu, j.z, a, gr, gi);
-    chunk_pair<R>(yz.y >> 16, j.w, a, gr, gi);
-    const R2<R> ax = a[x];
-    fr += ax.x * gr + ax.y * gi;
-    fi += ax.x * gi - ax.y * gr;
 }
 
 template <typename R>
@@ -243,103 +101,6 @@ __device__ inline void mode_field_lds(const DevPtrs<R>& P, const uint32_t* lb, i
         field_partial_chunk<R>(P.cx, P.cyz, P.cJ, lb[l], lb[l + 1], a, t, nt, fr, fi);
     else
         field_partial<R>(P.idx, P.J, lb[l], lb[l + 1], a, t, nt, fr, fi);
-}
-
-// workgroup barrier that waits for LDS operations only (s_waitcnt lgkmcnt(0)
-// with vmcnt and expcnt at their maxima, 0xC07F): global loads issued before
-// it stay in flight.  Only for loops whose global memory traffic is loads.
-__device__ inline void block_sync_lds() {
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    __builtin_amdgcn_s_barrier();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
-// list chunks of one mode held in registers ahead of their step: thread t of a
-// group of nt owns chunks beg + t + m * nt, m < PF (the host picks PF so that
-// every list of the launch fits); consumed in the order the streaming loop
-// of field_partial_chunk would take them
-template <typename R, int PF>
-struct ChunkRegs {
-    uint32_t x[PF];
-    uint2 yz[PF];
-    typename J4<R>::T J[PF];
-    uint32_t n;  // chunks of this thread
-};
-
-template <typename R, int PF>
-__device__ inline void chunk_prefetch(const DevPtrs<R>& P, const uint32_t* lb, int l, int t, int nt,
-                                      ChunkRegs<R, PF>& rg) {
-    using JT = typename J4<R>::T;
-    const uint32_t beg = lb[l], end = lb[l + 1];
-    const JT* __restrict__ Jv = reinterpret_cast<const JT*>(P.cJ);
-    rg.n = 0;
-#pragma unroll
-    for (int m = 0; m < PF; ++m) {
-        const uint32_t c = beg + t + (uint32_t)m * nt;
-        if (c < end) {
-            rg.x[m] = P.cx[c];
-            rg.yz[m] = P.cyz[c];
-            rg.J[m] = Jv[c];
-            rg.n = m + 1;
-        }
-    }
-}
-
-template <typename R, int PF>
-__device__ inline void chunk_consume(const ChunkRegs<R, PF>& rg, const R2<R>* __restrict__ a, R& fr, R& fi) {
-#pragma unroll
-    for (int m = 0; m < PF; ++m)
-        if ((uint32_t)m < rg.n) chunk_term<R>(rg.x[m], rg.yz[m], rg.J[m], a, fr, fi);
-}
-
-// energy change of the two-mode update from the two fields of one snapshot:
-// dE = -2 Re(conj(aj_new - aj_old) F_j) - 2 Re(conj(ak_new - ak_old) F_k)
-template <typename R>
-__device__ inline R pair_delta(R2<R> ajo, R2<R> ajn, R2<R> ako, R2<R> akn, R2<R> Fj, R2<R> Fk) {
-    const R djr = ajn.x - ajo.x, dji = ajn.y - ajo.y;
-    const R dkr = akn.x - ako.x, dki = akn.y - ako.y;
-    return (R)-2 * (djr * Fj.x + dji * Fj.y) - (R)2 * (dkr * Fk.x + dki * Fk.y);
-}
-
-// state-independent part of step s of sweep w for one copy (sec. III.A):
-// distinct j, k; unit phasors of the new phases; sqrt(cos theta), sqrt(sin theta);
-// acceptance uniform
-template <typename R>
-struct StepDraw {
-    int32_t jk;  // j | k << 16
-    R ejr, eji, ekr, eki, cj, sk, u;
-};
-
-template <typename R>
-__device__ inline StepDraw<R> draw_step(uint64_t seed, int64_t pair_stream, int64_t copy_id, int64_t sweep,
-                                        int step, int N, int rho) {
-    const Philox4 wp = philox4x64((uint64_t)step, (uint64_t)sweep, (uint64_t)pair_stream, 0, seed, kTagPair);
-    const Philox4 wm = philox4x64((uint64_t)step, (uint64_t)sweep, (uint64_t)copy_id, 0, seed, kTagMove);
-    const int j = index_below(wp.v[0], N);
-    int k = index_below(wp.v[1], N - 1);
-    k += (k >= j) ? 1 : 0;
-    StepDraw<R> d;
-    d.jk = j | (k << 16);
-    const R two_pi = (R)2 * pi_v<R>();
-    R s, c;
-    sincos_r(two_pi * uniform01<R>(wm.v[0]), &s, &c);
-    d.ejr = c;
-    d.eji = s;
-    sincos_r(two_pi * uniform01<R>(wm.v[1]), &s, &c);
-    d.ekr = c;
-    d.eki = s;
-    if (rho == 2) {  // sin^2 theta uniform: A_j' = K sqrt(1 - u), A_k' = K sqrt(u)
-        const R u = uniform01<R>(wm.v[2]);
-        d.cj = sqrt((R)1 - u);
-        d.sk = sqrt(u);
-    } else {  // theta uniform: A_j' = K sqrt(cos theta), A_k' = K sqrt(sin theta)
-        sincos_r((R)0.5 * pi_v<R>() * uniform01<R>(wm.v[2]), &s, &c);
-        d.cj = sqrt(c > (R)0 ? c : (R)0);
-        d.sk = sqrt(s > (R)0 ? s : (R)0);
-    }
-    d.u = uniform01<R>(wm.v[3]);
-    return d;
 }
 
 // LDS bytes of the sample's list bounds (max_N + 1 offsets), ahead of the copy groups
@@ -630,15 +391,6 @@ __global__ __launch_bounds__(BLOCK) void k_stream_lists(DevPtrs<float> P, ShapeI
 // streaming sweep.  The host takes this path only when no padded list is
 // longer than 32 * kShortSlots entries.
 constexpr int kShortSlots = 4;
-
-// keep the compiler from moving LDS accesses across a write by one lane that
-// all lanes then read (the hardware runs one wave's LDS accesses in order);
-// emits no wait, so global loads in flight stay in flight
-__device__ inline void wave_sync() {
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_wave_barrier();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
 
 // a step's draws plus the list bounds of its two modes
 template <typename R>

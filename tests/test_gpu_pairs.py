@@ -1,0 +1,97 @@
+"""GPU: the pair-space sweep (all fields of a sweep from one banded product,
+corrected where an update is accepted) against the CPU FP64 oracle, at the
+sizes where its tables and tiles change: the smallest N it serves, odd N, the
+largest N whose product fits a workgroup's LDS and the next, N = 256; copies
+that do not fill a matrix-core tile; both constraints and pair schedules;
+degenerate frequency sums, single splits and a wider linewidth; several sweeps
+per launch; mixed N in one context."""
+import numpy as np
+import pytest
+
+from paper_2511_13508_amd import rlpt
+from tests import synth
+from tests.gpu_util import make_ctx, oracle_pt
+
+pytestmark = pytest.mark.gpu
+
+SEED = 2511135080 + 1200
+
+
+def run_both(oracle, Ns, T, reps, sweeps, graph={}, **cfg):
+    temps = synth.geometric_temps(0.3, 1.5, T)
+    graphs = [rlpt.Graph(N, SEED + i, **graph) for i, N in enumerate(Ns)]
+    ctx = make_ctx(graphs, temps, n_temps=T, n_reps=reps, precision=rlpt.FP32, n_bins=20, **cfg)
+    ctx.init(6)
+    ctx.sweep(sweeps)
+    ctx.check()
+    ors = []
+    for mu, N in enumerate(Ns):
+        pt = oracle_pt(oracle, oracle.Graph(N, SEED + mu, **graph), temps, mu, ctx.cfg, 6)
+        pt.run(sweeps)
+        ors.append(pt)
+    return ctx, ors
+
+
+def compare_fp32(ctx, ors):
+    """FP32 states and energies of the same chain: proposals are FP32 (a few
+    units of 6e-8 relative to amplitudes of order one per update of a mode,
+    within 2e-5), energies sums of ~N updates (1e-4); a copy may separate at an
+    acceptance decided within the FP32 rounding of dE, at most one per sample."""
+    a = ctx.get_state() if len(set(ctx.Ns)) == 1 else None
+    E, temp_of = ctx.energies()
+    at = 0
+    for mu, pt in enumerate(ors):
+        N = ctx.Ns[mu]
+        g = (a[at:at + ctx.R * N] if a is not None else ctx.get_state(mu * ctx.R, ctx.R)).reshape(ctx.R, N)
+        at += ctx.R * N
+        bad = 0
+        for c in range(ctx.R):
+            ok = np.allclose(g[c], pt.a[c], rtol=0, atol=2e-5) and temp_of[mu * ctx.R + c] == pt.temp_of[c]
+            bad += not (ok and abs(E[mu * ctx.R + c] - pt.E[c]) <= 1e-4 * max(1.0, abs(pt.E[c])))
+        assert bad <= 1, (N, bad)
+
+
+@pytest.mark.parametrize("N,T,reps,samples", [(88, 5, 1, 2), (97, 7, 3, 1), (136, 4, 2, 2), (137, 5, 1, 3),
+                                              (181, 17, 1, 1), (255, 3, 1, 1), (256, 8, 2, 1)])
+def test_pair_sweep_sizes(oracle, N, T, reps, samples):
+    compare_fp32(*run_both(oracle, [N] * samples, T, reps, 3, resync_interval=2))
+
+
+@pytest.mark.parametrize("N,cfg", [(96, dict(rho=2)), (150, dict(rho=2)), (96, dict(shared_pairs=1)),
+                                   (150, dict(shared_pairs=1)), (120, dict(swap_interval=3, resync_interval=0)),
+                                   (160, dict(swap_interval=3, resync_interval=0)),
+                                   (96, dict(list_layout=rlpt.LAYOUT_PACKED)),
+                                   (144, dict(list_layout=rlpt.LAYOUT_PACKED))])
+def test_pair_sweep_options(oracle, N, cfg):
+    compare_fp32(*run_both(oracle, [N], 6, 2, 3, **cfg))
+
+
+@pytest.mark.parametrize("N,graph", [(96, dict(omega_kind=rlpt.OMEGA_COMB)), (140, dict(omega_kind=rlpt.OMEGA_COMB)),
+                                     (96, dict(split_mask=rlpt.SPLIT_A)), (140, dict(split_mask=rlpt.SPLIT_B)),
+                                     (96, dict(gamma=0.02))])
+def test_pair_sweep_graphs(oracle, N, graph):
+    compare_fp32(*run_both(oracle, [N], 4, 1, 2, graph=graph))
+
+
+def test_pair_sweep_mixed_sizes(oracle):
+    """Classes the pair-space sweep serves beside classes swept from their lists."""
+    compare_fp32(*run_both(oracle, [32, 128, 64, 200, 128, 90], 4, 2, 2))
+
+
+@pytest.mark.parametrize("Ns", [[100], [176], [48, 112]])
+def test_pair_sweep_replays(Ns):
+    """Eager sweeps, one launch of several sweeps and HIP-graph replay give the same bits."""
+    temps = synth.geometric_temps(0.4, 1.5, 4)
+    graphs = [rlpt.Graph(N, SEED + 40 + i) for i, N in enumerate(Ns)]
+    kw = dict(n_temps=4, n_reps=2, precision=rlpt.FP32, swap_interval=3, resync_interval=6, measure_interval=3, n_bins=8)
+    ctxs = [make_ctx(graphs, temps, **kw) for _ in range(3)]
+    for c in ctxs:
+        c.init(2)
+    for _ in range(12):
+        ctxs[0].sweep(1)
+    ctxs[1].sweep(12)
+    ctxs[2].run_graph(6, 2)
+    a, E = [np.concatenate([c.get_state(i * c.R, c.R) for i in range(c.S)]) for c in ctxs], [c.energies() for c in ctxs]
+    for i in (1, 2):
+        assert np.array_equal(a[0], a[i])
+        assert np.array_equal(E[0][0], E[i][0]) and np.array_equal(E[0][1], E[i][1])
