@@ -502,7 +502,9 @@ int enqueue_sweeps(rlpt_ctx* c, int64_t done, int64_t n, int64_t* swaps_added) {
             }
             HIP_TRY(hipEventRecord(ev.first, c->stream), "event record");
         }
-        if (c->pair_launch.empty()) {
+        if (c->ahead.n_items > 0) {
+            HIP_TRY(launch_sweep_ahead(cfg.precision, c->ptrs(), c->sh, c->ahead, (int)step, c->stream), "sweep launch");
+        } else if (c->pair_launch.empty()) {
             HIP_TRY(launch_sweep(cfg.precision, c->ptrs(), c->sh, c->launch, (int)step, c->stream), "sweep launch");
         } else {
             for (int w = 0; w < (int)step; ++w)
@@ -778,6 +780,45 @@ hipError_t build_pairs(rlpt_ctx* c, const rlpt_graph* const* g, const std::vecto
     if (e == hipSuccess) e = launch_pairs_tables(c->pf, c->pairs, c->sh, c->S, c->max_N, max_quads, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);  // the host vectors end here
     return e;
+}
+
+// short lists and few copies: several steps of a copy at a time (ahead.hip).
+// A copy takes 4 to 16 waves, so it pays while the chip has room for every
+// copy's at once; past that the waves of one copy only delay the others (us
+// per sweep, one wave per copy -> several, on an MI355X: N = 1024 of mean
+// degree 32, 320 copies 412 -> 191, 640 416 -> 285, 1280 527 -> 525; N = 16,
+// 16 copies 19 -> 16, 640 18 -> 21).  Chunked lists: up to two chunks per lane
+// (N = 32, 8 copies 28 -> 19, 384 30 -> 25, 1024 32 -> 37; N = 48 45 -> 47).
+void plan_ahead(rlpt_ctx* c, const ItemDev* items) {
+    if (c->sh.cached || c->cfg.block_threads > 0 || c->cfg.copies_per_block > 0) return;
+    AheadLaunch L{};
+    L.items = items;
+    L.max_N = c->max_N;
+    if (c->sh.layout == kLayoutChunked) {
+        uint32_t longest = 0;
+        for (uint32_t n : c->max_chunks) longest = std::max(longest, n);
+        L.chunks = (int)(longest + 63) / 64;
+        L.block = 512;
+        if (L.chunks > 2) return;
+    } else if (c->sh.short_lists) {
+        L.block = 1024;
+        // no wave without a step: the window is half the waves
+        while (L.block > 256 && L.block / 128 > c->max_N / 2) L.block /= 2;
+    } else {
+        return;
+    }
+    while (L.block > 256 && ahead_lds_bytes(c->cfg.precision, L.block, c->max_N) > 160 * 1024) L.block /= 2;
+    const size_t lds = ahead_lds_bytes(c->cfg.precision, L.block, c->max_N);
+    if (lds > 160 * 1024) return;
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
+    // a long sweep gains more than a short one's fixed part costs
+    const int per_cu2 = L.chunks > 0 ? 1 : L.max_N > 128 ? 6 : 3;  // copies per two compute units
+    if (c->n_copies > per_cu2 * cus / 2) return;
+    L.n_items = c->n_copies;
+    c->ahead = L;
 }
 
 void drop_events(rlpt_ctx* c) {
@@ -1071,7 +1112,11 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
     const std::vector<ItemDev> by_slot = slot_items(c);
     up(r.slot_items, by_slot);
     const std::vector<int> served = pair_samples(*cfg, graphs, n_graphs);
-    if (!served.empty() && e == hipSuccess) e = build_pairs(c, graphs, served, b, r);
+    if (!served.empty()) {
+        if (e == hipSuccess) e = build_pairs(c, graphs, served, b, r);
+    } else {
+        plan_ahead(c, reinterpret_cast<const ItemDev*>(b + r.slot_items));
+    }
     if (e == hipSuccess) e = launch_zero(c->acc_region, c->acc_region_bytes, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {

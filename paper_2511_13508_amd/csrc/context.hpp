@@ -6,6 +6,7 @@
 #include <utility>
 #include <vector>
 
+#include "ahead.hpp"
 #include "internal.hpp"
 #include "mlp.hpp"
 #include "pairs.hpp"
@@ -35,6 +36,7 @@ struct rlpt_ctx {
     std::vector<rlpt::PairLaunch> pair_launch;
     DevPtrs<float> pf_rest{};
     SweepLaunch rest{};
+    rlpt::AheadLaunch ahead{};  // sweep of short lists (0 items: another kernel)
     // regions of the workspace
     void* ws = nullptr;
     size_t ws_bytes = 0;

@@ -1,0 +1,62 @@
+"""GPU: sweeps of short lists, several steps of a copy decided at a time,
+against the CPU FP64 oracle: fewer steps than a window, windows that do not
+divide the steps, lists of exactly the longest length that takes this sweep,
+more copies than it serves, one and two chunks per lane."""
+import numpy as np
+import pytest
+
+from paper_2511_13508_amd import rlpt
+from tests import synth
+from tests.gpu_util import make_ctx, oracle_pt
+from tests.test_gpu_parity import compare_fp64
+from tests.test_gpu_pairs import compare_fp32
+
+pytestmark = pytest.mark.gpu
+
+SEED = 2511135080 + 1300
+
+
+def run_both(oracle, Ns, z, T, reps, sweeps, **cfg):
+    temps = synth.geometric_temps(0.3, 1.5, T)
+    graphs = [rlpt.Graph(N, SEED + i, mean_degree=z) for i, N in enumerate(Ns)]
+    ctx = make_ctx(graphs, temps, n_temps=T, n_reps=reps, n_bins=10, **cfg)
+    ctx.init(4)
+    ctx.sweep(sweeps)
+    ctx.check()
+    ors = []
+    for mu, N in enumerate(Ns):
+        pt = oracle_pt(oracle, oracle.Graph(N, SEED + mu, mean_degree=z), temps, mu, ctx.cfg, 4)
+        pt.run(sweeps)
+        ors.append(pt)
+    return ctx, ors
+
+
+@pytest.mark.parametrize("Ns,z,T,reps,cfg", [
+    ([6, 9, 5], 0, 4, 2, {}), ([17], 0, 3, 1, dict(swap_interval=4)), ([15], 0, 3, 2, dict(rho=2)),
+    ([16], 0, 40, 20, {}),  # more copies than the chip has room for several waves each
+    ([300, 33, 1023], 9, 3, 2, dict(shared_pairs=1)), ([1024], 32, 2, 1, dict(swap_interval=3)),
+    ([32], 0, 3, 2, {}), ([40, 33], 0, 3, 1, dict(swap_interval=2))])
+def test_ahead_trajectory_fp64(oracle, Ns, z, T, reps, cfg):
+    compare_fp64(*run_both(oracle, Ns, z, T, reps, 24, precision=rlpt.FP64, resync_interval=12, **cfg))
+
+
+@pytest.mark.parametrize("Ns,z,T,reps", [([14], 0, 5, 2), ([24], 0, 4, 2), ([32, 38], 0, 6, 2), ([700, 1001], 20, 5, 1)])
+def test_ahead_fp32(oracle, Ns, z, T, reps):
+    compare_fp32(*run_both(oracle, Ns, z, T, reps, 4, precision=rlpt.FP32))
+
+
+def test_longest_list_of_the_short_sweep():
+    """128 entries per list take the short sweep, one more does not; both
+    agree with the streaming kernel on the same FP64 chain."""
+    temps = synth.geometric_temps(0.4, 1.5, 3)
+    for z in (92, 96, 100, 108, 116):  # the longest list of these samples crosses 128
+        g = [rlpt.Graph(64, SEED + 30, mean_degree=z)]
+        ctxs = [make_ctx(g, temps, n_temps=3, n_reps=2, precision=rlpt.FP64, n_bins=4, **kw)
+                for kw in (dict(list_layout=rlpt.LAYOUT_PACKED),
+                           dict(list_layout=rlpt.LAYOUT_CHUNKED, block_threads=64, copies_per_block=1))]
+        for c in ctxs:
+            c.init(9)
+            c.sweep(12)
+        # the same decisions; energies differ by the order of FP64 sums of ~100 terms
+        assert np.allclose(ctxs[0].get_state(), ctxs[1].get_state(), rtol=0, atol=1e-12), z
+        assert np.allclose(ctxs[0].energies()[0], ctxs[1].energies()[0], rtol=1e-11, atol=1e-11), z
