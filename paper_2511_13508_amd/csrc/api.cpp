@@ -107,7 +107,7 @@ struct Layout {
 struct Regions {
     size_t samples, items, mode_start, idx, J, chunk_start, cx, cyz, cJ, pair_start, pidx, pJ, fields, ell_start, gidx16, gidx32, gJ, c0, quads, Jq, amp, E, E64, drift, temp_of, copy_at, beta, beta64;
     size_t acc_begin, acc, swap_acc, obs, hist, hist_I, spec, series_e, series_q, meas_cnt, counters, acc_end;
-    size_t scratch, scratch_doubles, rs_part, mlp, total;
+    size_t scratch, scratch_doubles, rs_part, arrived, mlp, total;
     size_t slot_items;  // one item per copy, in the order of temperature slots
     size_t p_samples, p_rest, p_modes, p_rank, p_tile, p_first, p_desc, p_fields, p_draws, p_order, p_after, p_prod, p_list, p_band, p_end;
 };
@@ -362,6 +362,7 @@ Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layo
     r.scratch_doubles = std::max<size_t>(2 * amp, 8192);
     r.scratch = L.take(r.scratch_doubles * 8);
     r.rs_part = L.take(copies * kResyncParts * 8);
+    r.arrived = L.take((S + 1) * 4);
     r.slot_items = L.take(copies * sizeof(ItemDev));
     const std::vector<int> served = pair_samples(cfg, g, S);
     if (!served.empty()) {
@@ -438,6 +439,7 @@ void fill_ptrs(DevPtrs<R>& P, unsigned char* b, const Regions& r) {
     P.meas_cnt = reinterpret_cast<int32_t*>(b + r.meas_cnt);
     P.counters = reinterpret_cast<Counters*>(b + r.counters);
     P.rs_part = reinterpret_cast<double*>(b + r.rs_part);
+    P.arrived = reinterpret_cast<int32_t*>(b + r.arrived);
 }
 
 void fill_pair_ptrs(PairDev& Q, unsigned char* b, const Regions& r, int max_N) {
@@ -523,15 +525,27 @@ int enqueue_sweeps(rlpt_ctx* c, int64_t done, int64_t n, int64_t* swaps_added) {
         }
         const int64_t after = cur + step;
         const bool swap = c->T > 1 && after % cfg.swap_interval == 0;
-        if (swap) HIP_TRY(launch_swap(cfg.precision, c->ptrs(), c->sh, c->stream), "swap launch");
-        HIP_TRY(launch_tick(c->ptrs(), cfg.precision, step, swap ? 1 : 0, c->stream), "tick launch");
+        const bool resync = cfg.resync_interval > 0 && after % cfg.resync_interval == 0;
+        bool measure = measuring_at(c, after);
         if (swap) *swaps_added += 1;
-        if (cfg.resync_interval > 0 && after % cfg.resync_interval == 0) {
+        if (c->T <= 64 && after_sweep_lds(c->sh) <= 48 * 1024 && (swap || (measure && !resync))) {
+            // one launch for all that follows a sweep (up to 64 baths: a ballot holds
+            // one pair's tests); 18 us as three launches, 12 as one at N = 64.  A
+            // recomputation comes between the swap round and the measurement, which
+            // is then launched after it; a lone counter update has its own kernel
+            HIP_TRY(launch_after_sweep(cfg.precision, c->ptrs(), c->sh, swap ? 1 : 0, measure && !resync ? 1 : 0, step,
+                                       c->stream), "swap and measure launch");
+            measure = measure && resync;
+        } else {
+            if (swap) HIP_TRY(launch_swap(cfg.precision, c->ptrs(), c->sh, c->stream), "swap launch");
+            HIP_TRY(launch_tick(c->ptrs(), cfg.precision, step, swap ? 1 : 0, c->stream), "tick launch");
+        }
+        if (resync) {
             HIP_TRY(launch_resync(cfg.precision, c->ptrs(), c->sh, c->n_copies, 0, c->stream), "resync launch");
             int rc = refresh_fields(c);
             if (rc) return rc;
         }
-        if (measuring_at(c, after)) HIP_TRY(launch_measure(cfg.precision, c->ptrs(), c->sh, c->stream), "measure launch");
+        if (measure) HIP_TRY(launch_measure(cfg.precision, c->ptrs(), c->sh, c->stream), "measure launch");
         k += step;
     }
     return RLPT_OK;
@@ -1118,6 +1132,7 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
         plan_ahead(c, reinterpret_cast<const ItemDev*>(b + r.slot_items));
     }
     if (e == hipSuccess) e = launch_zero(c->acc_region, c->acc_region_bytes, c->stream);
+    if (e == hipSuccess) e = launch_zero(b + r.arrived, ((size_t)n_graphs + 1) * 4, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         delete c;

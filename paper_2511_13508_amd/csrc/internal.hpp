@@ -138,9 +138,12 @@ struct DevPtrs {
     double* spec;             // [S][T][spec_stride] per-mode intensity |a_k|^2 summed over measurements, replicas
     int32_t* meas_cnt;        // [S][T]
     Counters* counters;
+    int32_t* arrived;         // [S] blocks of a sample, [1] samples that the launch after a sweep is done with
+                              // (0 between launches)
     double* rs_part;          // [copies][kResyncParts] partial FP64 energies of a recomputation
 };
 
+constexpr int kAfterBaths = 8;   // baths of one sample that a workgroup measures after a sweep
 constexpr int kResyncParts = 8;  // term ranges of one energy recomputation (workgroups per copy group)
 
 // offsets (in doubles) of the [S][T] accumulator blocks inside DevPtrs::obs
@@ -202,6 +205,11 @@ hipError_t launch_energy_static(int precision, const void* ptrs, const ShapeInfo
 hipError_t launch_resync(int precision, const void* ptrs, const ShapeInfo& sh, int n_copies, int mode,
                          hipStream_t st);
 hipError_t launch_measure(int precision, const void* ptrs, const ShapeInfo& sh, hipStream_t st);
+// swap round (swap = 1), counters and measurement (measure = 1) in one launch;
+// T <= 64 and after_sweep_lds() within 48 KiB
+size_t after_sweep_lds(const ShapeInfo& sh);
+hipError_t launch_after_sweep(int precision, const void* ptrs, const ShapeInfo& sh, int swap, int measure,
+                              int64_t d_sweeps, hipStream_t st);
 // recompute the cached local fields of every copy from the per-mode lists
 hipError_t launch_fields_all(int precision, const void* ptrs, const ShapeInfo& sh, int n_copies, hipStream_t st);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);

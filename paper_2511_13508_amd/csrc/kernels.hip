@@ -1104,84 +1104,290 @@ __global__ void k_zero(uint32_t* p, size_t n) {
 }
 
 // ---------------------------------------------------------------- observables
-// one block of 64 threads per (sample, bath): energy moments, IPR Y_2 and Y_4
-// of every replica, overlap of every replica pair and its histogram
-template <typename R>
-__global__ __launch_bounds__(64) void k_measure(DevPtrs<R> P, ShapeInfo sh) {
-    const int st = blockIdx.x;  // sample * T + t
-    const int mu = st / sh.n_temps, t = st % sh.n_temps;
+// one of `n` uniform values, by lane
+template <int n>
+__device__ inline int lane_pick(const int (&v)[n], int lane) {
+    int x = v[0];
+#pragma unroll
+    for (int i = 1; i < n; ++i) x = lane == i ? v[i] : x;
+    return x;
+}
+
+// h[bins[i]] += 1 for the first `count` entries: one lane per distinct bin
+// (counts are whole numbers, so their sum is exact in any order)
+template <int n>
+__device__ inline void count_bins(double* h, const int (&bins)[n], int count, int lane) {
+    const int mine = lane_pick(bins, lane);
+    bool first = lane < count;
+    double add = 0.0;
+#pragma unroll
+    for (int i = 0; i < n; ++i)
+        if (i < count && bins[i] == mine) {
+            add += 1.0;
+            first = first && i >= lane;
+        }
+    if (first) h[mine] += add;
+}
+
+// the accumulators of one (sample, bath), a lane each
+__device__ inline void add_moments(double* o, int S_T, int st, int lane, double n, double eS, double eQ, double y2S,
+                                   double y4S, double qn, double qS, double qQ, double q4) {
+    const int at[9] = {kEN, kESum, kESq, kY2, kY4, kQN, kQSum, kQSq, kQ4};
+    const double val[9] = {n, eS, eQ, y2S, y4S, qn, qS, qQ, q4};
+    int slot = at[0];
+    double v = val[0];
+#pragma unroll
+    for (int i = 1; i < 9; ++i) {
+        slot = lane == i ? at[i] : slot;
+        v = lane == i ? val[i] : v;
+    }
+    if (lane < 9) o[slot * S_T + st] += v;
+}
+
+__device__ inline int bin_of(double x, int n_bins) {
+    const int b = (int)floor(x * n_bins);
+    return b < 0 ? 0 : (b >= n_bins ? n_bins - 1 : b);
+}
+
+// one bath of one sample, by one wave: energy moments, IPR Y_2 and Y_4 of every
+// replica, overlap of every replica pair and their histograms.  copy_of(r): the
+// copy of ladder r at this bath.  A chain of dependent memory accesses and
+// wave sums bounds it, so up to LM replicas are read and summed together; more
+// replicas go one after another.
+template <typename R, typename CopyOf>
+__device__ inline void measure_bath(const DevPtrs<R>& P, const ShapeInfo& sh, int mu, int t, int lane, CopyOf copy_of) {
+    constexpr int LM = 3, PM = LM * (LM - 1) / 2;
+    const int st = mu * sh.n_temps + t;
     const SampleDev sd = P.samples[mu];
-    const int N = sd.N;
-    const int lane = threadIdx.x;
+    const int N = sd.N, L = sh.n_reps;
     const int S_T = sh.n_samples * sh.n_temps;
     const int m = P.meas_cnt[st];
+    double* spec = P.spec + (size_t)st * sh.spec_stride;  // each lane owns its modes
+    double* hist_I = P.hist_I + (size_t)st * sh.n_bins;
+    double* hist = P.hist + (size_t)st * sh.n_bins;
+    const auto amps = [&](int c) {
+        return reinterpret_cast<const R2<R>*>(P.amp) + sd.amp_base + (c - (int64_t)mu * sh.copies_per_sample) * N;
+    };
     double eS = 0, eQ = 0, y2S = 0, y4S = 0, e0 = 0;
-    for (int r = 0; r < sh.n_reps; ++r) {
-        const int c = P.copy_at[((size_t)mu * sh.n_reps + r) * sh.n_temps + t];
-        const int64_t local = c - (int64_t)mu * sh.copies_per_sample;
-        const R* a = P.amp + 2 * (sd.amp_base + local * N);
-        double s1 = 0, s2 = 0, s4 = 0;
-        double* spec = P.spec + (size_t)st * sh.spec_stride;  // each lane owns its modes
-        for (int k = lane; k < N; k += 64) {
-            const double x = a[2 * k], y = a[2 * k + 1];
-            const double I = x * x + y * y;
-            s1 += I;
-            s2 += I * I;
-            s4 += (I * I) * (I * I);
-            spec[k] += I;
-        }
-        s1 = wave_sum(s1);
-        s2 = wave_sum(s2);
-        s4 = wave_sum(s4);
-        const double E = (double)P.E[c];
-        if (r == 0) e0 = E;
-        eS += E;
-        eQ += E * E;
-        y2S += s2 / (s1 * s1);
-        y4S += s4 / (s2 * s2);
-        if (lane == 0) {  // distribution of the total intensity I = sum |a|^2
-            int bI = (int)floor(s1 / (double)N * sh.n_bins);
-            bI = bI < 0 ? 0 : (bI >= sh.n_bins ? sh.n_bins - 1 : bI);
-            P.hist_I[(size_t)st * sh.n_bins + bI] += 1.0;
-        }
-    }
     double qS = 0, qQ = 0, q4 = 0, qn = 0, q01 = 0;
-    for (int r = 0; r < sh.n_reps; ++r)
-        for (int r2 = r + 1; r2 < sh.n_reps; ++r2) {
-            const int c1 = P.copy_at[((size_t)mu * sh.n_reps + r) * sh.n_temps + t];
-            const int c2 = P.copy_at[((size_t)mu * sh.n_reps + r2) * sh.n_temps + t];
-            const R* x = P.amp + 2 * (sd.amp_base + (c1 - (int64_t)mu * sh.copies_per_sample) * N);
-            const R* y = P.amp + 2 * (sd.amp_base + (c2 - (int64_t)mu * sh.copies_per_sample) * N);
-            double q = 0;
-            for (int k = lane; k < N; k += 64) q += (double)x[2 * k] * y[2 * k] + (double)x[2 * k + 1] * y[2 * k + 1];
-            q = wave_sum(q) / (double)N;
-            qS += q;
-            qQ += q * q;
-            q4 += (q * q) * (q * q);
-            qn += 1.0;
-            if (r == 0 && r2 == 1) q01 = q;
-            if (lane == 0) {
-                int b = (int)floor((q + 1.0) * 0.5 * sh.n_bins);
-                b = b < 0 ? 0 : (b >= sh.n_bins ? sh.n_bins - 1 : b);
-                P.hist[(size_t)st * sh.n_bins + b] += 1.0;
+    if (L <= LM) {
+        const R2<R>* a[LM];
+        double E[LM], s1[LM], s2[LM], s4[LM], q[PM];
+#pragma unroll
+        for (int r = 0; r < LM; ++r) {
+            const int c = copy_of(r < L ? r : 0);
+            a[r] = amps(c);
+            E[r] = (double)P.E[c];
+            s1[r] = s2[r] = s4[r] = 0;
+        }
+#pragma unroll
+        for (int i = 0; i < PM; ++i) q[i] = 0;
+        for (int k = lane; k < N; k += 64) {
+            double x[LM], y[LM], sp = spec[k];
+#pragma unroll
+            for (int r = 0; r < LM; ++r) {
+                const R2<R> v = a[r][k];
+                x[r] = v.x;
+                y[r] = v.y;
+            }
+            int i = 0;
+#pragma unroll
+            for (int r = 0; r < LM; ++r) {
+                const double I = x[r] * x[r] + y[r] * y[r];
+                s1[r] += I;
+                s2[r] += I * I;
+                s4[r] += (I * I) * (I * I);
+                if (r < L) sp += I;
+#pragma unroll
+                for (int r2 = r + 1; r2 < LM; ++r2) q[i++] += x[r] * x[r2] + y[r] * y[r2];
+            }
+            spec[k] = sp;
+        }
+        int bI[LM], bq[PM];
+#pragma unroll
+        for (int r = 0; r < LM; ++r) {
+            s1[r] = wave_sum(s1[r]);
+            s2[r] = wave_sum(s2[r]);
+            s4[r] = wave_sum(s4[r]);
+            bI[r] = bin_of(s1[r] / (double)N, sh.n_bins);
+        }
+        int i = 0;
+#pragma unroll
+        for (int r = 0; r < LM; ++r) {
+            if (r < L) {
+                eS += E[r];
+                eQ += E[r] * E[r];
+                y2S += s2[r] / (s1[r] * s1[r]);
+                y4S += s4[r] / (s2[r] * s2[r]);
+            }
+#pragma unroll
+            for (int r2 = r + 1; r2 < LM; ++r2, ++i) {
+                q[i] = wave_sum(q[i]) / (double)N;
+                bq[i] = bin_of((q[i] + 1.0) * 0.5, sh.n_bins);
+                if (r2 < L) {
+                    qS += q[i];
+                    qQ += q[i] * q[i];
+                    q4 += (q[i] * q[i]) * (q[i] * q[i]);
+                    qn += 1.0;
+                }
             }
         }
+        e0 = E[0];
+        q01 = q[0];
+        count_bins(hist_I, bI, L, lane);
+        if (L == LM) count_bins(hist, bq, PM, lane);
+        else if (L == 2 && lane == 0) hist[bq[0]] += 1.0;
+    } else {
+        for (int r = 0; r < L; ++r) {
+            const int c = copy_of(r);
+            const R2<R>* a = amps(c);
+            double s1 = 0, s2 = 0, s4 = 0;
+            for (int k = lane; k < N; k += 64) {
+                const double x = a[k].x, y = a[k].y;
+                const double I = x * x + y * y;
+                s1 += I;
+                s2 += I * I;
+                s4 += (I * I) * (I * I);
+                spec[k] += I;
+            }
+            s1 = wave_sum(s1);
+            s2 = wave_sum(s2);
+            s4 = wave_sum(s4);
+            const double E = (double)P.E[c];
+            if (r == 0) e0 = E;
+            eS += E;
+            eQ += E * E;
+            y2S += s2 / (s1 * s1);
+            y4S += s4 / (s2 * s2);
+            if (lane == 0) hist_I[bin_of(s1 / (double)N, sh.n_bins)] += 1.0;
+        }
+        for (int r = 0; r < L; ++r)
+            for (int r2 = r + 1; r2 < L; ++r2) {
+                const R2<R>*x = amps(copy_of(r)), *y = amps(copy_of(r2));
+                double q = 0;
+                for (int k = lane; k < N; k += 64) q += (double)x[k].x * y[k].x + (double)x[k].y * y[k].y;
+                q = wave_sum(q) / (double)N;
+                qS += q;
+                qQ += q * q;
+                q4 += (q * q) * (q * q);
+                qn += 1.0;
+                if (r == 0 && r2 == 1) q01 = q;
+                if (lane == 0) hist[bin_of((q + 1.0) * 0.5, sh.n_bins)] += 1.0;
+            }
+    }
+    add_moments(P.obs, S_T, st, lane, (double)L, eS, eQ, y2S, y4S, qn, qS, qQ, q4);
     if (lane == 0) {
-        double* o = P.obs;
-        o[kEN * S_T + st] += (double)sh.n_reps;
-        o[kESum * S_T + st] += eS;
-        o[kESq * S_T + st] += eQ;
-        o[kY2 * S_T + st] += y2S;
-        o[kY4 * S_T + st] += y4S;
-        o[kQN * S_T + st] += qn;
-        o[kQSum * S_T + st] += qS;
-        o[kQSq * S_T + st] += qQ;
-        o[kQ4 * S_T + st] += q4;
         if (m < sh.series_len) {
             P.series_e[(size_t)st * sh.series_len + m] = e0;
-            if (sh.n_reps > 1) P.series_q[(size_t)st * sh.series_len + m] = q01;
+            if (L > 1) P.series_q[(size_t)st * sh.series_len + m] = q01;
         }
         P.meas_cnt[st] = m + 1;
+    }
+}
+
+// one block of 64 threads per (sample, bath)
+template <typename R>
+__global__ __launch_bounds__(64) void k_measure(DevPtrs<R> P, ShapeInfo sh) {
+    const int mu = blockIdx.x / sh.n_temps, t = blockIdx.x % sh.n_temps;
+    measure_bath(P, sh, mu, t, threadIdx.x,
+                 [&](int r) { return P.copy_at[((size_t)mu * sh.n_reps + r) * sh.n_temps + t]; });
+}
+
+// ---------------------------------------------------------------- after a sweep
+// What follows most sweeps, in one launch: the swap round, the counters and
+// the measurement.  A block measures kAfterBaths baths of one sample, a wave
+// each, and decides the sample's whole swap round itself (nothing crosses
+// samples); the sample's last block to finish writes the ladders, when the
+// others have read them, and the last of all advances the counters.
+// The swap round's chain decides pair i with the copy that earlier decisions
+// carried to bath i, one of those that started at baths 0..i: the acceptance
+// test of every pair with each of them is taken in parallel (lane = the bath
+// where the copy started), which leaves a walk over bits.
+// T <= 64 (one wave's ballot).  Bound by launches and chains of dependent
+// accesses, not by bytes: us after a sweep, swap + counters + measurement as
+// three launches -> this one, on an MI355X: 8 samples of N = 64, 24 baths, 2
+// replicas 17.9 -> 11.8; 50 sweeps of N = 16 in FP64 (8 baths, 2 replicas)
+// 1346 -> 1152 in all.
+template <typename R>
+__global__ __launch_bounds__(64 * kAfterBaths) void k_after_sweep(DevPtrs<R> P, ShapeInfo sh, int swap, int measure,
+                                                                  int groups, int64_t d_sweeps) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int kThreads = 64 * kAfterBaths;
+    const int T = sh.n_temps, L = sh.n_reps, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int mu = blockIdx.x / groups, group = blockIdx.x % groups;
+    double* e = reinterpret_cast<double*>(smem);                                         // [L][T] energies
+    double* u = e + (size_t)L * T;                                                       // [L][T] uniforms
+    unsigned long long* can = reinterpret_cast<unsigned long long*>(u + (size_t)L * T);  // [L][T] accepting starts
+    int32_t* at = reinterpret_cast<int32_t*>(can + (size_t)L * T);                       // [L][T] copies
+    int32_t* at2 = at + (size_t)L * T;                                                   // [L][T] copies afterwards
+    __shared__ int last;
+    __shared__ double db[64];  // b_i - b_{i+1}
+    int32_t* copy_at = P.copy_at + (size_t)mu * L * T;
+    const int64_t round = P.counters->swaps_done;
+    if (tid + 1 < T) db[tid] = P.beta64[tid] - P.beta64[tid + 1];
+    for (int i = tid; i < L * T; i += kThreads) {
+        const int c = copy_at[i];
+        at[i] = c;
+        at2[i] = c;
+        if (swap) {
+            e[i] = (double)P.E[c];
+            const Philox4 w = philox4x64((uint64_t)(i % T), (uint64_t)round, (uint64_t)mu * L + i / T, 0, sh.run_seed,
+                                         kTagSwap);
+            u[i] = uniform01<double>(w.v[0]);
+        }
+    }
+    __syncthreads();
+    if (swap) {
+        for (int q = wave; q < L * (T - 1); q += kAfterBaths) {
+            const int r = q / (T - 1), i = q % (T - 1);
+            const double x = db[i] * (e[r * T + min(lane, i)] - e[r * T + i + 1]);
+            const unsigned long long m = __ballot((x >= 0.0) || (u[r * T + i] < exp(x)));
+            if (lane == 0) can[r * T + i] = m;
+        }
+        __syncthreads();
+        for (int r = wave; r < L; r += kAfterBaths) {
+            // lane i holds pair i; cur: the bath where the copy now at bath i started
+            const unsigned long long m = can[r * T + min(lane, T - 2)];
+            const uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
+            int cur = 0, from = 0;
+            bool took = false;
+            for (int i = 0; i + 1 < T; ++i) {
+                const uint64_t w = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, i) << 32 |
+                                   (uint32_t)__builtin_amdgcn_readlane(lo, i);
+                const bool acc = w >> cur & 1;
+                if (lane == i) {
+                    from = acc ? i + 1 : cur;
+                    took = acc;
+                }
+                if (!acc) cur = i + 1;
+            }
+            if (lane == T - 1) from = cur;
+            if (lane < T) {
+                at2[r * T + lane] = at[r * T + from];
+                can[r * T + lane] = took ? 1ull : 0ull;
+            }
+        }
+        __syncthreads();
+    }
+    const int t = group * kAfterBaths + wave;
+    if (measure && t < T) measure_bath(P, sh, mu, t, lane, [&](int r) { return at2[r * T + t]; });
+    // the copies and the round's number were read before the barriers above
+    if (tid == 0) last = atomicAdd(&P.arrived[mu], 1) == groups - 1;
+    __syncthreads();
+    if (!last) return;
+    if (swap)
+        for (int i = tid; i < L * T; i += kThreads) {
+            copy_at[i] = at2[i];
+            P.temp_of[at2[i]] = i % T;
+            if (i % T + 1 < T && can[i]) P.swap_acc[((size_t)mu * L + i / T) * (T - 1) + i % T] += 1ull;
+        }
+    if (tid == 0) {
+        P.arrived[mu] = 0;
+        if (atomicAdd(&P.arrived[sh.n_samples], 1) == sh.n_samples - 1) {
+            P.arrived[sh.n_samples] = 0;
+            P.counters->sweeps_done += d_sweeps;
+            P.counters->swaps_done += swap;
+        }
     }
 }
 
@@ -1491,6 +1697,23 @@ static hipError_t measure_t(const void* ptrs, const ShapeInfo& sh, hipStream_t s
 }
 hipError_t launch_measure(int precision, const void* ptrs, const ShapeInfo& sh, hipStream_t st) {
     return precision == RLPT_FP64 ? measure_t<double>(ptrs, sh, st) : measure_t<float>(ptrs, sh, st);
+}
+
+template <typename R>
+static hipError_t after_sweep_t(const void* ptrs, const ShapeInfo& sh, int swap, int measure, int64_t d_sweeps,
+                                hipStream_t st) {
+    const int groups = measure ? (sh.n_temps + kAfterBaths - 1) / kAfterBaths : 1;
+    hipLaunchKernelGGL(k_after_sweep<R>, dim3(sh.n_samples * groups), dim3(64 * kAfterBaths), after_sweep_lds(sh), st,
+                       *static_cast<const DevPtrs<R>*>(ptrs), sh, swap, measure, groups, d_sweeps);
+    return hipGetLastError();
+}
+
+size_t after_sweep_lds(const ShapeInfo& sh) { return (size_t)sh.n_reps * sh.n_temps * 32; }
+
+hipError_t launch_after_sweep(int precision, const void* ptrs, const ShapeInfo& sh, int swap, int measure,
+                              int64_t d_sweeps, hipStream_t st) {
+    return precision == RLPT_FP64 ? after_sweep_t<double>(ptrs, sh, swap, measure, d_sweeps, st)
+                                  : after_sweep_t<float>(ptrs, sh, swap, measure, d_sweeps, st);
 }
 
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st) {
