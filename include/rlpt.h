@@ -152,8 +152,11 @@ typedef struct rlpt_config {
                                  streaming sweep up to rounding order (each target's field
                                  change is gathered in a fixed order).  Fields are recomputed
                                  from scratch at init, every recomputation, rlpt_set_state and
-                                 learned rounds.
-                                 Needs 12 * n_terms more list entries of 4 + 4|8 bytes and
+                                 learned rounds.  FP32 contexts whose samples are all dense
+                                 and of 88 to 256 modes, without an explicit launch tile, form
+                                 the fields of every sweep from the amplitudes instead, which
+                                 is faster; a checkpoint holds fields in either case.
+                                 Otherwise needs 12 * n_terms more list entries of 4 + 4|8 bytes and
                                  (N^2 + 1) * 4 bytes per sample. */
     int32_t rho;              /* global constraint sum_k |a_k|^rho = N (eq. SmoothedCubic): 4 (default;
                                  0 reads as 4), or 2 for the spherical constraint of fixed total

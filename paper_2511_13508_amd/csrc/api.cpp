@@ -267,14 +267,17 @@ size_t pair_copies(const rlpt_config& cfg, int N) {
 // -> 115, 128 261 -> 186, 200 972 -> 502).  The tables take about 5 times the
 // lists' memory (the per-pair entries), so past kPairTableBytes the context
 // keeps to the lists.
+// Contexts in cached-field mode take it when it serves every sample (us per
+// sweep, cached fields -> pairs, 640 copies of 8 samples: N = 96 410 -> 121,
+// 128 600 -> 198, 256 1638 -> 979; 8 copies of one: 249 -> 74, 339 -> 101, 1103
+// -> 522); their fields are then formed from the amplitudes in every sweep and
+// written only for a checkpoint.
 constexpr int kPairModes = 88;
 constexpr size_t kPairTableBytes = (size_t)64 << 30;
 
 std::vector<int> pair_samples(const rlpt_config& cfg, const rlpt_graph* const* g, int S) {
     std::vector<int> served;
-    if (cfg.precision != RLPT_FP32 || cfg.field_mode != RLPT_FIELDS_STREAM || cfg.block_threads > 0 ||
-        cfg.copies_per_block > 0)
-        return served;
+    if (cfg.precision != RLPT_FP32 || cfg.block_threads > 0 || cfg.copies_per_block > 0) return served;
     size_t bytes = 0;
     for (int i = 0; i < S; ++i) {
         if (g[i]->N < kPairModes || g[i]->pair_modes.empty()) continue;
@@ -283,6 +286,7 @@ std::vector<int> pair_samples(const rlpt_config& cfg, const rlpt_graph* const* g
                  kListUnit * (size_t)g[i]->pair_first.back() * sizeof(PairEntry);
     }
     if (bytes > kPairTableBytes) served.clear();
+    if (cfg.field_mode == RLPT_FIELDS_CACHED && (int)served.size() < S) served.clear();
     return served;
 }
 
@@ -296,7 +300,9 @@ int check_graphs(const rlpt_graph* const* g, int n) {
 Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layout) {
     const size_t rb = cfg.precision == RLPT_FP64 ? 8 : 4;
     const size_t T = cfg.n_temps, reps = cfg.n_reps, Rc = T * reps, copies = Rc * S;
-    const bool cached = cfg.field_mode == RLPT_FIELDS_CACHED;
+    const std::vector<int> served = pair_samples(cfg, g, S);
+    // tables of the cached-field sweep: only where it runs
+    const bool cached = cfg.field_mode == RLPT_FIELDS_CACHED && served.empty();
     size_t modes = 0, entries = 0, chunks = 0, quads = 0, amp = 0, pairs = 0, pair_entries = 0;
     size_t ell_starts = 0, ell_total = 0, c0n = 0;
     int max_N = 0;
@@ -331,7 +337,7 @@ Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layo
     r.pair_start = L.take(cached ? pairs * 4 : 0);
     r.pidx = L.take(cached ? pair_entries * 4 : 0);
     r.pJ = L.take(cached ? pair_entries * rb : 0);
-    r.fields = L.take(cached ? amp * 2 * rb : 0);
+    r.fields = L.take(cfg.field_mode == RLPT_FIELDS_CACHED ? amp * 2 * rb : 0);
     r.ell_start = L.take(ell_starts * 4);
     r.gidx16 = L.take(layout == kLayoutChunked ? ell_total * 2 : 0);
     r.gidx32 = L.take(layout == kLayoutChunked ? 0 : ell_total * 4);
@@ -364,7 +370,6 @@ Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layo
     r.rs_part = L.take(copies * kResyncParts * 8);
     r.arrived = L.take((S + 1) * 4);
     r.slot_items = L.take(copies * sizeof(ItemDev));
-    const std::vector<int> served = pair_samples(cfg, g, S);
     if (!served.empty()) {
         size_t np = 0, rank = 0, tiles = 0, band = 0, list = 0, prod = 0, desc = 0;
         for (int i : served) {
@@ -474,8 +479,9 @@ bool measuring_at(const rlpt_ctx* c, int64_t n) {
 }
 
 // cached-field mode: recompute every copy's fields from its amplitudes
-int refresh_fields(rlpt_ctx* c) {
-    if (!c->sh.cached) return RLPT_OK;
+// (the pair-space sweep forms its own)
+int refresh_fields(rlpt_ctx* c, bool saving = false) {
+    if (!c->sh.cached || (!c->pair_launch.empty() && !saving)) return RLPT_OK;
     HIP_TRY(launch_fields_all(c->cfg.precision, c->ptrs(), c->sh, c->n_copies, c->stream), "fields launch");
     return RLPT_OK;
 }
@@ -919,6 +925,7 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
     int layout = 0;
     if ((rc = choose_layout(*cfg, graphs, n_graphs, &layout))) return rc;
     const Regions r = plan(*cfg, graphs, n_graphs, layout);
+    const std::vector<int> served = pair_samples(*cfg, graphs, n_graphs);
     if (workspace_bytes < r.total) return fail(RLPT_E_NOMEM, "workspace smaller than rlpt_workspace_size()");
     rlpt_ctx* c = new (std::nothrow) rlpt_ctx;
     if (!c) return fail(RLPT_E_NOMEM, "out of host memory");
@@ -1025,7 +1032,7 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
             quads.push_back(u);
         }
         Jq.insert(Jq.end(), g->J.begin(), g->J.end());
-        if (c->sh.cached) {
+        if (c->sh.cached && served.empty()) {
             sd.pair_base = (int64_t)pstart.size();
             sd.ell_base = (int64_t)estart.size();
             sd.c0_base = (int64_t)c0tab.size();
@@ -1125,7 +1132,6 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
     up(r.beta64, b64);
     const std::vector<ItemDev> by_slot = slot_items(c);
     up(r.slot_items, by_slot);
-    const std::vector<int> served = pair_samples(*cfg, graphs, n_graphs);
     if (!served.empty()) {
         if (e == hipSuccess) e = build_pairs(c, graphs, served, b, r);
     } else {
@@ -1546,6 +1552,7 @@ void ckpt_header(const rlpt_ctx* c, CkptHeader* h) {
 int rlpt_checkpoint_save(rlpt_ctx* c, const char* path) {
     if (!c || !path) return fail(RLPT_E_ARG, "NULL argument");
     if (!c->inited) return fail(RLPT_E_STATE, "rlpt_init has not been called");
+    if (int rc = refresh_fields(c, true)) return rc;
     HIP_TRY(hipStreamSynchronize(c->stream), "stream synchronize");
     CkptHeader h;
     ckpt_header(c, &h);

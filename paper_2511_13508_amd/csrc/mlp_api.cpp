@@ -180,7 +180,8 @@ int mlp_enqueue_round(rlpt_ctx* c) {
     }
     HIP_TRY2(mlp_forward_proposal(M, c->pf, c->sh, M.Or, c->stream), "learned forward");
     HIP_TRY2(mlp_accept(M, c->pf, c->sh, s, c->stream), "learned accept");
-    if (c->sh.cached) HIP_TRY2(launch_fields_all(c->cfg.precision, c->ptrs(), c->sh, c->n_copies, c->stream), "fields");
+    if (c->sh.cached && c->pair_launch.empty())
+        HIP_TRY2(launch_fields_all(c->cfg.precision, c->ptrs(), c->sh, c->n_copies, c->stream), "fields");
     return RLPT_OK;
 }
 

@@ -95,3 +95,33 @@ def test_pair_sweep_replays(Ns):
     for i in (1, 2):
         assert np.array_equal(a[0], a[i])
         assert np.array_equal(E[0][0], E[i][0]) and np.array_equal(E[0][1], E[i][1])
+
+
+@pytest.mark.parametrize("Ns,cfg", [([88, 88], {}), ([97], dict(rho=2)), ([201], dict(list_layout=rlpt.LAYOUT_PACKED)),
+                                    ([256], dict(shared_pairs=1)), ([96, 40], {})])
+def test_cached_field_mode(oracle, Ns, cfg):
+    """The cached-field mode follows the same chain, served by the pair-space
+    sweep or, with a sample below its smallest N, by its own."""
+    compare_fp32(*run_both(oracle, Ns, 5, 2, 3, field_mode=rlpt.FIELDS_CACHED, resync_interval=2, **cfg))
+
+
+@pytest.mark.parametrize("first", [0, 1])
+def test_cached_checkpoint_across_sweeps(oracle, tmp_path, first):
+    """A checkpoint holds the fields of its amplitudes whichever sweep wrote it:
+    the other one (an explicit launch tile belongs to the cached-field sweep)
+    continues the oracle's chain from it."""
+    N, T, reps = 96, 5, 2
+    temps = synth.geometric_temps(0.3, 1.5, T)
+    g = rlpt.Graph(N, SEED)
+    kw = dict(n_temps=T, n_reps=reps, n_bins=20, field_mode=rlpt.FIELDS_CACHED, resync_interval=0)
+    ctxs = [make_ctx([g], temps, **kw), make_ctx([g], temps, block_threads=128, copies_per_block=1, **kw)]
+    a, b = ctxs[first], ctxs[1 - first]
+    a.init(6)
+    a.sweep(2)
+    a.checkpoint_save(str(tmp_path / "c"))
+    b.checkpoint_load(str(tmp_path / "c"))
+    b.sweep(2)
+    b.check()
+    pt = oracle_pt(oracle, oracle.Graph(N, SEED), temps, 0, b.cfg, 6)
+    pt.run(4)
+    compare_fp32(b, [pt])
