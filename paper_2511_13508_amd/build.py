@@ -36,7 +36,7 @@ def build(verbose: bool = False) -> str:
     hipcc = shutil.which("hipcc") or os.path.join(ROCM, "bin", "hipcc")
     os.makedirs(BUILD_DIR, exist_ok=True)
     objs = []
-    for src in ("kernels.hip", "ahead.hip", "pairs.hip", "mlp.hip"):
+    for src in ("kernels.hip", "ahead.hip", "pairs.hip", "energy.hip", "mlp.hip"):
         obj = os.path.join(BUILD_DIR, src + ".o")
         _run([hipcc, *HIP_FLAGS, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
         objs.append(obj)

@@ -108,6 +108,7 @@ struct Regions {
     size_t samples, items, mode_start, idx, J, chunk_start, cx, cyz, cJ, pair_start, pidx, pJ, fields, ell_start, gidx16, gidx32, gJ, c0, quads, Jq, amp, E, E64, drift, temp_of, copy_at, beta, beta64;
     size_t acc_begin, acc, swap_acc, obs, hist, hist_I, spec, series_e, series_q, meas_cnt, counters, acc_end;
     size_t scratch, scratch_doubles, rs_part, arrived, mlp, total;
+    size_t en_samples, en_pairs, en_rank, en_tile, en_band, en_end;
     size_t slot_items;  // one item per copy, in the order of temperature slots
     size_t p_samples, p_rest, p_modes, p_rank, p_tile, p_first, p_desc, p_fields, p_draws, p_order, p_after, p_prod, p_list, p_band, p_end;
 };
@@ -290,6 +291,27 @@ std::vector<int> pair_samples(const rlpt_config& cfg, const rlpt_graph* const* g
     return served;
 }
 
+// Ranges of the banded energy recomputation, which every context with a band
+// takes (energy.hip has the figures; it is faster at every size): 0 where the
+// terms are summed one by one, that is with a sample without a band (sparse
+// graphs, N > 256) or band tables past kPairTableBytes.
+int energy_parts(const rlpt_config& cfg, const rlpt_graph* const* g, int S) {
+    size_t bytes = 0;
+    int tiles = 1;
+    for (int i = 0; i < S; ++i) {
+        if (g[i]->pair_modes.empty()) return 0;
+        bytes += (size_t)g[i]->energy_tile.back() * 512;
+        tiles = std::max(tiles, (int)g[i]->energy_tile.size() - 1);
+    }
+    if (bytes > kPairTableBytes) return 0;
+    // a tile per wave at least; otherwise about five blocks per compute unit,
+    // and partial energies that fit the static scratch
+    const size_t Rc = (size_t)cfg.n_temps * cfg.n_reps, blocks = (Rc + 15) / 16 * S;
+    const size_t fit = kStaticScratchBytes / (Rc * S * sizeof(double));
+    const size_t want = std::min<size_t>(kEnergyParts, std::max<size_t>(2, (1280 + blocks - 1) / blocks));
+    return (int)std::min({want, std::max<size_t>(fit, 1), (size_t)(tiles + 3) / 4});
+}
+
 int check_graphs(const rlpt_graph* const* g, int n) {
     if (!g || n < 1) return fail(RLPT_E_ARG, "need at least one graph");
     for (int i = 0; i < n; ++i)
@@ -367,7 +389,23 @@ Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layo
     r.acc_end = L.off;
     r.scratch_doubles = std::max<size_t>(2 * amp, 8192);
     r.scratch = L.take(r.scratch_doubles * 8);
-    r.rs_part = L.take(copies * kResyncParts * 8);
+    const int en_parts = energy_parts(cfg, g, S);
+    r.rs_part = L.take(copies * std::max(en_parts, kResyncParts) * 8);
+    if (en_parts > 0) {
+        size_t np = 0, rank = 0, tiles = 0, band = 0;
+        for (int i = 0; i < S; ++i) {
+            np += g[i]->pair_modes.size();
+            rank += g[i]->pair_rank.size();
+            tiles += g[i]->energy_tile.size();
+            band += (size_t)g[i]->energy_tile.back() * 64;
+        }
+        r.en_samples = L.take(S * sizeof(EnergySample));
+        r.en_pairs = L.take(np * 2);
+        r.en_rank = L.take(rank * 2);
+        r.en_tile = L.take(tiles * 4);
+        r.en_band = L.take(band * 8);
+        r.en_end = L.off;
+    }
     r.arrived = L.take((S + 1) * 4);
     r.slot_items = L.take(copies * sizeof(ItemDev));
     if (!served.empty()) {
@@ -445,6 +483,11 @@ void fill_ptrs(DevPtrs<R>& P, unsigned char* b, const Regions& r) {
     P.counters = reinterpret_cast<Counters*>(b + r.counters);
     P.rs_part = reinterpret_cast<double*>(b + r.rs_part);
     P.arrived = reinterpret_cast<int32_t*>(b + r.arrived);
+    P.en_samples = reinterpret_cast<const EnergySample*>(b + r.en_samples);
+    P.en_pairs = reinterpret_cast<const uint16_t*>(b + r.en_pairs);
+    P.en_rank = reinterpret_cast<const uint16_t*>(b + r.en_rank);
+    P.en_tile = reinterpret_cast<const uint32_t*>(b + r.en_tile);
+    P.en_band = reinterpret_cast<double*>(b + r.en_band);
 }
 
 void fill_pair_ptrs(PairDev& Q, unsigned char* b, const Regions& r, int max_N) {
@@ -802,6 +845,42 @@ hipError_t build_pairs(rlpt_ctx* c, const rlpt_graph* const* g, const std::vecto
     return e;
 }
 
+// tables of the banded energy recomputation (the terms are on the device)
+hipError_t build_energy(rlpt_ctx* c, const rlpt_graph* const* g, unsigned char* b, const Regions& r) {
+    std::vector<EnergySample> smp;
+    std::vector<uint16_t> pairs, rank;
+    std::vector<uint32_t> tile;
+    EnergySample at{};
+    int64_t max_quads = 0;
+    int columns = 0;
+    for (int s = 0; s < c->S; ++s) {
+        smp.push_back(at);
+        const std::vector<uint32_t>& t = g[s]->energy_tile;
+        const int64_t n = (int64_t)t.size() - 1;
+        for (int p = 0; p < c->sh.en_parts; ++p) {
+            const int64_t t0 = n * p / c->sh.en_parts, t1 = n * (p + 1) / c->sh.en_parts;
+            if (t0 < t1) columns = std::max(columns, (int)(16 * (t1 - t0) + 4 * (t[t1] - t[t1 - 1])));
+        }
+        at.pair_base += (int64_t)g[s]->pair_modes.size();
+        at.rank_base += (int64_t)g[s]->pair_rank.size();
+        at.tile_base += (int64_t)t.size();
+        at.band_base += 64 * (int64_t)t.back();
+        pairs.insert(pairs.end(), g[s]->pair_modes.begin(), g[s]->pair_modes.end());
+        rank.insert(rank.end(), g[s]->pair_rank.begin(), g[s]->pair_rank.end());
+        tile.insert(tile.end(), t.begin(), t.end());
+        max_quads = std::max<int64_t>(max_quads, g[s]->n_terms());
+    }
+    c->sh.en_columns = columns;
+    hipError_t e = upload(b, r.en_samples, smp, c->stream);
+    if (e == hipSuccess) e = upload(b, r.en_pairs, pairs, c->stream);
+    if (e == hipSuccess) e = upload(b, r.en_rank, rank, c->stream);
+    if (e == hipSuccess) e = upload(b, r.en_tile, tile, c->stream);
+    if (e == hipSuccess) e = launch_zero(b + r.en_band, r.en_end - r.en_band, c->stream);
+    if (e == hipSuccess) e = launch_energy_fill(c->cfg.precision, c->ptrs(), c->sh, max_quads, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);  // the host vectors end here
+    return e;
+}
+
 // short lists and few copies: several steps of a copy at a time (ahead.hip).
 // A copy takes 4 to 16 waves, so it pays while the chip has room for every
 // copy's at once; past that the waves of one copy only delay the others (us
@@ -1132,6 +1211,8 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
     up(r.beta64, b64);
     const std::vector<ItemDev> by_slot = slot_items(c);
     up(r.slot_items, by_slot);
+    c->sh.en_parts = energy_parts(*cfg, graphs, n_graphs);
+    if (c->sh.en_parts > 0 && e == hipSuccess) e = build_energy(c, graphs, b, r);
     if (!served.empty()) {
         if (e == hipSuccess) e = build_pairs(c, graphs, served, b, r);
     } else {

@@ -120,6 +120,12 @@ void pair_band(rlpt_graph* g) {
     if (off > 8 * (size_t)g->n_terms() + 16384 || off > 0xffffffffull ||
         most >= 1u << rlpt::kStartBits || (widest + 31) / 32 >= 1u << (16 - rlpt::kStartBits))
         return;
+    uint32_t units = 0;
+    for (int a = 0; a < P; a += 16) {  // rows [a, a + 16): columns [a, hi of the last)
+        g->energy_tile.push_back(units);
+        units += (uint32_t)(hi[std::min(P, a + 16) - 1] - a + 3) / 4;
+    }
+    g->energy_tile.push_back(units);
     g->pair_first.swap(first);
     g->band_entries = off;
     g->pair_tile.swap(tile);

@@ -36,6 +36,7 @@ struct rlpt_graph {
     std::vector<uint16_t> pair_rank;   // [N][N] rank of pair {l, x}
     std::vector<uint32_t> pair_tile;   // [ceil(n_pairs / 32)][2] offset in the band, first column | columns / 4 << 16
     size_t band_entries = 0;           // stored band values
+    std::vector<uint32_t> energy_tile; // [ceil(n_pairs / 16) + 1] bounds of each 16 rows' values above the diagonal, in 64s
     std::vector<uint32_t> pair_first;  // [N + 1] bounds of each source's per-target entries, in 16s
     int64_t n_terms() const { return (int64_t)J.size(); }
 };
@@ -91,6 +92,14 @@ struct Counters {
     int32_t pad;
 };
 
+// one sample's tables of the banded energy recomputation
+struct EnergySample {
+    int64_t pair_base;  // pairs by rank: p | s << 8
+    int64_t rank_base;  // [N][N] rank of a pair
+    int64_t tile_base;  // [tiles + 1] bounds of each row tile's band values, in 64s
+    int64_t band_base;  // band values
+};
+
 // pointers into the caller's workspace
 template <typename R>
 struct DevPtrs {
@@ -140,11 +149,17 @@ struct DevPtrs {
     Counters* counters;
     int32_t* arrived;         // [S] blocks of a sample, [1] samples that the launch after a sweep is done with
                               // (0 between launches)
-    double* rs_part;          // [copies][kResyncParts] partial FP64 energies of a recomputation
+    double* rs_part;          // [copies][parts] partial FP64 energies of a recomputation
+    const EnergySample* en_samples;
+    const uint16_t* en_pairs;
+    const uint16_t* en_rank;
+    const uint32_t* en_tile;
+    double* en_band;
 };
 
 constexpr int kAfterBaths = 8;   // baths of one sample that a workgroup measures after a sweep
 constexpr int kResyncParts = 8;  // term ranges of one energy recomputation (workgroups per copy group)
+constexpr int kEnergyParts = 64; // most ranges of the banded recomputation (one wave sums them)
 
 // offsets (in doubles) of the [S][T] accumulator blocks inside DevPtrs::obs
 enum ObsField { kEN = 0, kESum, kESq, kY2, kY4, kQN, kQSum, kQSq, kQ4, kNumObs };
@@ -162,6 +177,8 @@ struct ShapeInfo {
     int32_t by_slot;            // items name temperature slots (hottest first), copies found via copy_at
     int32_t rho;                // constraint sum |a|^rho = N: 4 (smoothed cubic) or 2 (spherical)
     int32_t short_lists;        // every list fits one wave's registers: the one-wave-per-copy sweep
+    int32_t en_parts;           // ranges of the banded energy recomputation (0: by terms)
+    int32_t en_columns;         // most pairs that one of them spans
     int32_t spec_stride;        // row length of the intensity spectrum accumulator (largest N)
     uint64_t run_seed;
     double renorm_tol;
@@ -197,11 +214,15 @@ hipError_t launch_tick(const void* ptrs_any, int precision, int64_t d_sweeps, in
 // mode 1: FP64 energies into E64 only; mode 2: store E = H without checks
 // FP64 energies of every copy into E[n_copies] (device) with the partial sums
 // in the library's static device scratch: no allocation, no host transfer.
-// hipErrorInvalidValue when n_copies x kResyncParts partials exceed it.
+// hipErrorInvalidValue when n_copies x kResyncParts partials exceed it.  (The
+// banded recomputation takes as many ranges as fit.)
 constexpr size_t kStaticScratchBytes = (size_t)2 << 20;
 hipError_t static_scratch_address(void** out);
 hipError_t launch_energy_static(int precision, const void* ptrs, const ShapeInfo& sh, int n_copies, double* E,
                                 hipStream_t st);
+// banded FP64 energies (energy.hip): the table and the partial energies
+hipError_t launch_energy_fill(int precision, const void* ptrs, const ShapeInfo& sh, int64_t max_quads, hipStream_t st);
+hipError_t launch_energy_band(int precision, const void* ptrs, const ShapeInfo& sh, hipStream_t st);
 hipError_t launch_resync(int precision, const void* ptrs, const ShapeInfo& sh, int n_copies, int mode,
                          hipStream_t st);
 hipError_t launch_measure(int precision, const void* ptrs, const ShapeInfo& sh, hipStream_t st);

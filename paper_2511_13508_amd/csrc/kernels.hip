@@ -928,8 +928,8 @@ __global__ __launch_bounds__(256) void k_init(DevPtrs<R> P, ShapeInfo sh) {
 // one block per copy: H = -2 sum_q J_q Re(conj a_p conj a_s a_m a_n) and
 // S = sum |a|^4 in FP64.  mode 0: drift check, renormalise when
 // |S/N - 1| > renorm_tol (H scales by N/S), store E; mode 1: E64 only.
-// FP64 energy recomputation in two stages.  Stage one: the copies of one
-// sample in groups of up to kResyncCopies (FP64 amplitudes in LDS) and the
+// FP64 energy recomputation in two stages.  Stage one, for samples without a
+// band (energy.hip serves the others): the copies of one sample in groups of up to kResyncCopies (FP64 amplitudes in LDS) and the
 // sample's by-term list cut into kResyncParts ranges; a workgroup streams one
 // range once for its whole group and leaves each copy's partial energy.
 constexpr int kResyncCopies = 8;
@@ -1009,8 +1009,8 @@ __global__ __launch_bounds__(64) void k_resync_fin(DevPtrs<R> P, ShapeInfo sh, i
         s4 += sh.rho == 2 ? u : u * u;
     }
     const double St = wave_sum(s4);
-    double Ht = 0.0;
-    for (int p = 0; p < kResyncParts; ++p) Ht += P.rs_part[(int64_t)c * kResyncParts + p];
+    const int parts = sh.en_parts > 0 ? sh.en_parts : kResyncParts;
+    double Ht = wave_sum(lane < parts ? P.rs_part[(int64_t)c * parts + lane] : 0.0);
     double f = 1.0;
     if (mode == 0 && fabs(St / (double)N - 1.0) > sh.renorm_tol && St > 0.0)
         f = sh.rho == 2 ? sqrt((double)N / St) : pow((double)N / St, 0.25);
@@ -1623,6 +1623,12 @@ hipError_t launch_tick(const void* ptrs, int precision, int64_t d_sweeps, int64_
 template <typename R>
 static hipError_t resync_t(const void* ptrs, const ShapeInfo& sh, int n_copies, int mode, hipStream_t st) {
     const DevPtrs<R>& P = *static_cast<const DevPtrs<R>*>(ptrs);
+    if (sh.en_parts > 0) {
+        const hipError_t e = launch_energy_band(sizeof(R) == 8 ? RLPT_FP64 : RLPT_FP32, ptrs, sh, st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_resync_fin<R>, dim3(n_copies), dim3(64), 0, st, P, sh, mode);
+        return hipGetLastError();
+    }
     // copy groups sized for the largest N of the context (spec_stride); n_copies = samples x copies per sample
     const int group = resync_group(sh.spec_stride);
     const int groups = (sh.copies_per_sample + group - 1) / group;
