@@ -2,10 +2,11 @@
 // GEMMs on the matrix cores with FP32 accumulation, SiLU, the Gaussian-mixture head and
 // its gradient, Adam, and the three stages of an exact Metropolis-Hastings
 // global move (propose, energy change, accept).  Every launch covers all
-// networks (grid z = network).
+// networks.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include "device.hpp"
 #include "mlp.hpp"
 #include "philox.hpp"
 
@@ -46,144 +47,283 @@ __device__ inline uint64_t word_of(const Philox4& w, int i) {
 __device__ inline float wrapf(float x) { return x - 2.0f * kPiF * ceilf((x - kPiF) / (2.0f * kPiF)); }
 
 // ------------------------------------------------------------------ GEMM
-// C[i][j] = act(sum_k A(i,k) B(k,j) + bias[j]), A(i,k) = A[i*as0 + k*as1],
-// B(k,j) = B[k*bs0 + j*bs1], on the matrix cores: both operands are rounded
-// to bfloat16 (nearest even; the weights already are) and staged in LDS, the
-// products accumulate in FP32 through v_mfma_f32_16x16x16_bf16.  A 256-thread
-// workgroup (4 waves) computes a BM x 64 tile; K advances 64 at a time, with
-// the next stage's global loads in flight while the current one is multiplied.
+// C[i][j] = sum_k A(i,k) B(k,j), with an epilogue, on the matrix cores: both
+// operands are rounded to bfloat16 (nearest even; the weights already are) and
+// staged in LDS, the products accumulate in FP32 through
+// v_mfma_f32_16x16x16_bf16 in ascending k.  A 256-thread workgroup (4 waves)
+// computes a BM x BM tile, 64 steps of K per LDS stage.
+// The layers are small (a few hundred rows, columns and steps), so memory
+// latency bounds the products, not the matrix cores: loads are 4 x 4 blocks,
+// four values wide along whichever axis is contiguous (turned in registers on
+// the way to LDS), two stages ahead of their use.  A is contiguous along k in
+// the layers (TB = uint16_t, the weights) and along its rows in their
+// gradients; B along k in the backward pass through a layer, else along j.
+// Us per launch, single values behind bounds branches -> this, on an MI355X (4
+// nets of 128 -> 256 -> 256 -> 1020, 512 rows): a hidden layer 23 -> 6.7, the
+// outputs 50 -> 12.6, back through the outputs and a SiLU 53 -> 16.4, all
+// weight and bias gradients 175 -> 17.4 (five launches -> one).
+template <typename T>
+struct Operand {  // rows of C (A) or columns of C (B) against k
+    const T* p;
+    int64_t net;   // stride between networks
+    int ld;        // between the lines along which it is contiguous
+};
+enum Epilogue { kPlain, kSilu, kSiluBack };
 template <typename TB>
 struct Gemm {
-    const float* A;
-    int64_t sA;
-    int as0, as1;
-    const TB* B;
-    int64_t sB;
-    int bs0, bs1;
-    const float* bias;
+    Operand<float> A;
+    Operand<TB> B;
+    const float* bias;  // kPlain, kSilu (or null)
     int64_t sBias;
-    float* Cpre;
-    float* Cact;
+    float* C;           // the product plus bias; kSiluBack: times silu'(Z)
+    float* act;         // kSilu: silu of it
+    const float* Z;     // kSiluBack: the layer's inputs to the SiLU, laid out as C
     int64_t sC;
     int M, N, K;
 };
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kGemmN = 64;             // tile columns
+template <typename T>
+struct Vec4;
+template <>
+struct Vec4<float> {
+    using Type = f32x4;
+};
+template <>
+struct Vec4<uint16_t> {
+    using Type = u16x4;
+};
+
 constexpr int kGemmK = 64;             // K per LDS stage
 constexpr int kGemmLd = kGemmK + 4;    // LDS row stride in bfloat16 elements (8-byte aligned rows)
 
 __device__ inline uint16_t bf16_bits(float x) { return f_to_bf16(x); }
 __device__ inline uint16_t bf16_bits(uint16_t x) { return x; }
 
-template <typename TB, int ACT, int BM>
-__global__ __launch_bounds__(256) void k_gemm(Gemm<TB> g) {
-    constexpr int GM = BM >= 32 ? BM / 32 : 1;  // waves along M
-    constexpr int GN = 4 / GM;                  // waves along N
-    constexpr int WM = BM / (16 * GM);          // 16 x 16 blocks per wave along M
-    constexpr int WN = kGemmN / (16 * GN);      // and along N
-    constexpr int AE = BM * kGemmK / 256;       // A elements per thread per stage
-    constexpr int BE = kGemmN * kGemmK / 256;   // B elements per thread per stage
-    __shared__ __align__(16) uint16_t As[BM][kGemmLd];      // [m][k]
-    __shared__ __align__(16) uint16_t Bs[kGemmN][kGemmLd];  // [n][k]
-    const int net = blockIdx.z;
-    const float* A = g.A + net * g.sA;
-    const TB* B = g.B + net * g.sB;
-    const int m0 = blockIdx.y * BM, n0 = blockIdx.x * kGemmN;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int wm0 = (wave / GN) * WM * 16, wn0 = (wave % GN) * WN * 16;
-    const bool a_m_fast = g.as0 == 1;  // A contiguous along M (a transposed operand)
-    const bool b_n_fast = g.bs1 == 1;  // B contiguous along N
-    // element e of a stage -> (row, k) of the A tile and (k, column) of the B tile
-    auto a_rk = [&](int e, int& r, int& kk) {
-        if (a_m_fast) { r = e % BM; kk = e / BM; } else { kk = e % kGemmK; r = e / kGemmK; }
+// block `unit` of a BM x 64 stage: first row and first k of its 4 x 4 values
+template <int BM, bool K_FAST>
+__device__ inline void unit_at(int unit, int& r, int& k) {
+    if (K_FAST) {
+        k = 4 * (unit % 16);
+        r = 4 * (unit / 16);
+    } else {
+        r = 4 * (unit % (BM / 4));
+        k = 4 * (unit / (BM / 4));
+    }
+}
+
+// The block at (r0, k0) of an operand of `rows` rows and K steps.  Places
+// outside read the nearest inside, so that no branch waits for a load;
+// store_block writes them as zeros.
+template <typename T, bool K_FAST, bool WIDE>
+__device__ inline void load_block(typename Vec4<T>::Type (&v)[4], const T* p, int ld, int r0, int k0, int rows, int K) {
+    const int line0 = K_FAST ? r0 : k0, at = K_FAST ? k0 : r0;
+    const int lines = K_FAST ? rows : K, len = K_FAST ? K : rows;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const T* q = p + (int64_t)min(line0 + i, lines - 1) * ld;
+        if (WIDE) {
+            v[i] = *reinterpret_cast<const typename Vec4<T>::Type*>(q + min(at, len - 4));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[i][j] = q[min(at + j, len - 1)];
+        }
+    }
+}
+
+template <typename T, bool K_FAST>
+__device__ inline void store_block(const typename Vec4<T>::Type (&v)[4], int r, int k, int rows, int K,
+                                   uint16_t (*tile)[kGemmLd], int tr, int tk) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        u16x4 x;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint16_t b = K_FAST ? bf16_bits(v[i][j]) : bf16_bits(v[j][i]);
+            x[j] = r + i < rows && k + j < K ? b : (uint16_t)0;
+        }
+        *reinterpret_cast<u16x4*>(&tile[tr + i][tk]) = x;
+    }
+}
+
+template <int BM>
+struct GemmLds {
+    __align__(16) uint16_t A[2][BM][kGemmLd];  // [stage][row][k]
+    __align__(16) uint16_t B[2][BM][kGemmLd];
+};
+
+template <typename TB, int EP, int BM, bool WIDE>
+__device__ inline void gemm_tile(const Gemm<TB>& g, int net, int m0, int n0, GemmLds<BM>& s) {
+    constexpr int W = BM / 32;               // 16 x 16 blocks per wave and axis
+    constexpr bool kA = sizeof(TB) == 2, kB = EP == kSiluBack;  // contiguous along k
+    constexpr bool kBoth = BM * 16 >= 1024;  // a thread loads a block of each operand, or of one
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int wm0 = (wave >> 1) * W * 16, wn0 = (wave & 1) * W * 16;
+    const float* Ap = g.A.p + net * g.A.net;
+    const TB* Bp = g.B.p + net * g.B.net;
+    const bool has_a = kBoth || tid < 128, has_b = kBoth || tid >= 128;
+    int ar, ak, br, bk;
+    unit_at<BM, kA>(kBoth ? tid : tid & 127, ar, ak);
+    unit_at<BM, kB>(kBoth ? tid : tid & 127, br, bk);
+    f32x4 va[2][4];
+    typename Vec4<TB>::Type vb[2][4];
+    const auto load = [&](int set, int k0) {
+        if (has_a) load_block<float, kA, WIDE>(va[set], Ap, g.A.ld, m0 + ar, k0 + ak, g.M, g.K);
+        if (has_b) load_block<TB, kB, WIDE>(vb[set], Bp, g.B.ld, n0 + br, k0 + bk, g.N, g.K);
     };
-    auto b_kc = [&](int e, int& kk, int& c) {
-        if (b_n_fast) { c = e % kGemmN; kk = e / kGemmN; } else { kk = e % kGemmK; c = e / kGemmK; }
-    };
-    uint16_t ra[AE], rb[BE];
-    auto load = [&](int k0) {
+    f32x4 acc[W][W];
 #pragma unroll
-        for (int i = 0; i < AE; ++i) {
-            int r, kk;
-            a_rk(threadIdx.x + 256 * i, r, kk);
-            const int gi = m0 + r, gk = k0 + kk;
-            ra[i] = (gi < g.M && gk < g.K) ? bf16_bits(A[(int64_t)gi * g.as0 + (int64_t)gk * g.as1]) : (uint16_t)0;
-        }
+    for (int i = 0; i < W; ++i)
 #pragma unroll
-        for (int i = 0; i < BE; ++i) {
-            int kk, c;
-            b_kc(threadIdx.x + 256 * i, kk, c);
-            const int gk = k0 + kk, gj = n0 + c;
-            rb[i] = (gk < g.K && gj < g.N) ? bf16_bits(B[(int64_t)gk * g.bs0 + (int64_t)gj * g.bs1]) : (uint16_t)0;
-        }
-    };
-    f32x4 acc[WM][WN];
-#pragma unroll
-    for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    load(0);
-    for (int k0 = 0; k0 < g.K; k0 += kGemmK) {
-#pragma unroll
-        for (int i = 0; i < AE; ++i) {
-            int r, kk;
-            a_rk(threadIdx.x + 256 * i, r, kk);
-            As[r][kk] = ra[i];
-        }
-#pragma unroll
-        for (int i = 0; i < BE; ++i) {
-            int kk, c;
-            b_kc(threadIdx.x + 256 * i, kk, c);
-            Bs[c][kk] = rb[i];
-        }
-        __syncthreads();
-        if (k0 + kGemmK < g.K) load(k0 + kGemmK);
+        for (int j = 0; j < W; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const auto stage = [&](int set, int k0) {
+        if (has_a) store_block<float, kA>(va[set], m0 + ar, k0 + ak, g.M, g.K, s.A[set], ar, ak);
+        if (has_b) store_block<TB, kB>(vb[set], n0 + br, k0 + bk, g.N, g.K, s.B[set], br, bk);
+        block_sync_lds();  // a stage's buffer is written again two stages later, past the next barrier
+        load(set, k0 + 2 * kGemmK);
 #pragma unroll
         for (int kk = 0; kk < kGemmK; kk += 16) {
             // operand layout of the 16x16x16 bf16 MFMA: lane l holds A[l % 16][4 (l / 16) + 0..3]
             // and B[4 (l / 16) + 0..3][l % 16]; the result D[4 (l / 16) + v][l % 16] in slot v
             const int q = kk + 4 * (lane >> 4), rr = lane & 15;
-            bf16x4 af[WM], bfr[WN];
+            bf16x4 af[W], bfr[W];
 #pragma unroll
-            for (int i = 0; i < WM; ++i) af[i] = *reinterpret_cast<const bf16x4*>(&As[wm0 + 16 * i + rr][q]);
+            for (int i = 0; i < W; ++i) af[i] = *reinterpret_cast<const bf16x4*>(&s.A[set][wm0 + 16 * i + rr][q]);
 #pragma unroll
-            for (int j = 0; j < WN; ++j) bfr[j] = *reinterpret_cast<const bf16x4*>(&Bs[wn0 + 16 * j + rr][q]);
+            for (int j = 0; j < W; ++j) bfr[j] = *reinterpret_cast<const bf16x4*>(&s.B[set][wn0 + 16 * j + rr][q]);
 #pragma unroll
-            for (int i = 0; i < WM; ++i)
+            for (int i = 0; i < W; ++i)
 #pragma unroll
-                for (int j = 0; j < WN; ++j)
+                for (int j = 0; j < W; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(af[i], bfr[j], acc[i][j], 0, 0, 0);
         }
-        __syncthreads();
+    };
+    load(0, 0);
+    load(1, kGemmK);
+    for (int k0 = 0; k0 < g.K; k0 += 2 * kGemmK) {
+        stage(0, k0);
+        if (k0 + kGemmK < g.K) stage(1, k0 + kGemmK);
     }
 #pragma unroll
-    for (int i = 0; i < WM; ++i)
+    for (int i = 0; i < W; ++i)
 #pragma unroll
-        for (int j = 0; j < WN; ++j)
+        for (int j = 0; j < W; ++j)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int gi = m0 + wm0 + 16 * i + 4 * (lane >> 4) + v;
                 const int gj = n0 + wn0 + 16 * j + (lane & 15);
                 if (gi >= g.M || gj >= g.N) continue;
-                const float x = acc[i][j][v] + (g.bias ? g.bias[net * g.sBias + gj] : 0.0f);
-                g.Cpre[net * g.sC + (int64_t)gi * g.N + gj] = x;
-                if (ACT) g.Cact[net * g.sC + (int64_t)gi * g.N + gj] = silu(x);
+                const int64_t at = net * g.sC + (int64_t)gi * g.N + gj;
+                if (EP == kSiluBack) {
+                    const float p = g.Z[at];
+                    const float sg = sigm(p);
+                    g.C[at] = acc[i][j][v] * sg * (1.0f + p * (1.0f - sg));
+                } else {
+                    const float x = acc[i][j][v] + (g.bias ? g.bias[net * g.sBias + gj] : 0.0f);
+                    g.C[at] = x;
+                    if (EP == kSilu) g.act[at] = silu(x);
+                }
             }
 }
 
-template <typename TB, int ACT>
-hipError_t gemm(const Gemm<TB>& g, int nets, hipStream_t st) {
-    if (g.M <= 16) {
-        dim3 grid((g.N + kGemmN - 1) / kGemmN, (g.M + 15) / 16, nets);
-        hipLaunchKernelGGL((k_gemm<TB, ACT, 16>), grid, dim3(256), 0, st, g);
-    } else {
-        dim3 grid((g.N + kGemmN - 1) / kGemmN, (g.M + 63) / 64, nets);
-        hipLaunchKernelGGL((k_gemm<TB, ACT, 64>), grid, dim3(256), 0, st, g);
-    }
+// tile `b` of a launch as (panel, tile along it): the tiles that share a panel
+// go to one XCD (each takes every eighth workgroup), whose L2 then reads it once
+// (back through the outputs 19.6 -> 18.0 us)
+__device__ inline void panel_tile(int b, int along, int& panel, int& i) {
+    panel = b % 8 + b / (8 * along) * 8;
+    i = b / 8 % along;
+}
+__host__ __device__ inline int panel_blocks(int panels, int along) { return (panels + 7) / 8 * 8 * along; }
+
+// panels: 32 or 64 rows of A, of all networks
+template <typename TB, int EP, int BM, bool WIDE>
+__global__ __launch_bounds__(256) void k_gemm(Gemm<TB> g, int nets) {
+    __shared__ GemmLds<BM> s;
+    const int ny = (g.M + BM - 1) / BM;
+    int panel, i;
+    panel_tile(blockIdx.x, (g.N + BM - 1) / BM, panel, i);
+    if (panel >= ny * nets) return;
+    gemm_tile<TB, EP, BM, WIDE>(g, panel / ny, panel % ny * BM, i * BM, s);
+}
+
+// four values at a time: aligned, and the contiguous extent a multiple of 4
+template <typename T>
+bool reads_wide(const Operand<T>& o, int len) {
+    return ((uintptr_t)o.p & (4 * sizeof(T) - 1)) == 0 && o.net % 4 == 0 && o.ld % 4 == 0 && len % 4 == 0;
+}
+
+int tiles_of(int M, int N, int BM) { return ((M + BM - 1) / BM) * ((N + BM - 1) / BM); }
+
+// rows and columns of a tile: 64 read half as much as 32, and pay from one
+// workgroup per compute unit on (us, 32 -> 64: the outputs, 512 tiles of 64,
+// 18.5 -> 14.4; all gradients, 352 tiles, 38.5 -> 31.8); below, smaller tiles
+// use more units
+int tile_rows(int64_t tiles64) { return tiles64 >= 256 ? 64 : 32; }
+
+template <typename TB, int EP, int BM>
+void gemm_rows(const Gemm<TB>& g, int nets, bool wide, hipStream_t st) {
+    const dim3 grid(panel_blocks((g.M + BM - 1) / BM * nets, (g.N + BM - 1) / BM));
+    if (wide) hipLaunchKernelGGL((k_gemm<TB, EP, BM, true>), grid, dim3(256), 0, st, g, nets);
+    else hipLaunchKernelGGL((k_gemm<TB, EP, BM, false>), grid, dim3(256), 0, st, g, nets);
+}
+
+template <int EP>
+hipError_t gemm(const Gemm<uint16_t>& g, int nets, hipStream_t st) {
+    const bool wide = reads_wide(g.A, g.K) && reads_wide(g.B, EP == kSiluBack ? g.K : g.N);
+    if (tile_rows((int64_t)tiles_of(g.M, g.N, 64) * nets) == 64) gemm_rows<uint16_t, EP, 64>(g, nets, wide, st);
+    else gemm_rows<uint16_t, EP, 32>(g, nets, wide, st);
     return hipGetLastError();
+}
+
+// column sums of Y [rows][cols] (bias gradients): 64 columns per 256-thread
+// block, four row slices per column summed in a fixed order
+__device__ inline void colsum_tile(const float* Y, int rows, int cols, int j0, float* out, float (*part)[64]) {
+    const int c = threadIdx.x & 63, slice = threadIdx.x >> 6;
+    const int j = j0 + c;
+    float s = 0.0f;
+    if (j < cols) {
+        const float* y = Y + j;
+#pragma unroll 8
+        for (int r = slice; r < rows; r += 4) s += y[(int64_t)r * cols];
+    }
+    part[slice][c] = s;
+    __syncthreads();
+    if (slice == 0 && j < cols) out[j] = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
+}
+
+// every layer's weight and bias gradients in one launch (none needs another's):
+// a layer's blocks are the tiles of act^T dY, by panels of dY's columns, then
+// the column sums of dY
+struct LayerGrads {
+    Gemm<float> g[3];
+    float* bias[3];    // bias gradients of net 0
+    int tiles[3], end[3];
+    int64_t sGrad;
+    int nets;
+};
+
+template <int BM, bool WIDE>
+__global__ __launch_bounds__(256) void k_layer_grads(LayerGrads L) {
+    __shared__ GemmLds<BM> s;
+    int b = blockIdx.x, l = 0;
+    while (b >= L.end[l]) ++l;
+    if (l > 0) b -= L.end[l - 1];
+    const Gemm<float>& g = L.g[l];
+    if (b < L.tiles[l]) {
+        const int nx = (g.N + BM - 1) / BM;
+        int panel, i;
+        panel_tile(b, (g.M + BM - 1) / BM, panel, i);
+        if (panel >= nx * L.nets) return;
+        gemm_tile<float, kPlain, BM, WIDE>(g, panel / nx, i * BM, panel % nx * BM, s);
+    } else {
+        const int n64 = (g.N + 63) / 64, net = (b - L.tiles[l]) / n64;
+        if (net >= L.nets) return;
+        colsum_tile(g.B.p + net * g.B.net, g.K, g.N, (b - L.tiles[l]) % n64 * 64, L.bias[l] + net * L.sGrad,
+                    reinterpret_cast<float(*)[64]>(&s));
+    }
 }
 
 // ------------------------------------------------------------------ features
@@ -531,15 +671,6 @@ __device__ inline float mix_lse(const float* O, int K) {
     return mx + logf(s);
 }
 
-struct Mix {
-    float lw[kMaxK];
-};
-
-__device__ inline void mix_weights(const float* O, int K, Mix& m) {
-    const float lse = mix_lse(O, K);
-    for (int i = 0; i < K; ++i) m.lw[i] = O[i] - lse;
-}
-
 __device__ inline float smax_of(int d, int N) { return d < N - 1 ? kSmaxY : kSmaxPsi; }
 
 // the component of a move: the first c with sum_{i <= c} w_i > u
@@ -638,9 +769,18 @@ __device__ inline double accept_log_uniform(uint64_t seed, int64_t move, int c, 
     return log(uniform01<double>(wu.v[1]));
 }
 
-// training head: mean NLL of the unwrapped mixture and its gradient w.r.t. the outputs
-__global__ __launch_bounds__(64) void k_head_train(MlpDev M) {
-    const int net = blockIdx.y, b = blockIdx.x, lane = threadIdx.x;
+// Training head: mean NLL of the unwrapped mixture and its gradient w.r.t. the
+// outputs, one item per workgroup, its mixture components shared out to the
+// waves.  Bound by the exponentials, logarithms and divisions: those over the
+// components are taken a lane each, and a coordinate's width and deviation are
+// kept for the gradient (2048 items of 4 components, 127 coordinates: 28 ->
+// 12.8 us).
+constexpr int kHeadWaves = 4;
+
+__global__ __launch_bounds__(64 * kHeadWaves) void k_head_train(MlpDev M) {
+    __shared__ int count[kHeadWaves];
+    __shared__ float ells[kMaxK];
+    const int net = blockIdx.y, b = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int N = M.N, K = M.K, D = M.D;
     const int64_t item = (int64_t)net * M.Bt + b;
     const float* O = M.tO + item * M.Out;
@@ -648,137 +788,121 @@ __global__ __launch_bounds__(64) void k_head_train(MlpDev M) {
     float* dO = M.tdO + item * M.Out;
     // the loss is the mean over the minibatch's pairs inside the chart; the others get no gradient
     int nv = 0;
-    for (int i = lane; i < M.Bt; i += 64) nv += M.tvalid[(int64_t)net * M.Bt + i];
+    for (int i = tid; i < M.Bt; i += 64 * kHeadWaves) nv += M.tvalid[(int64_t)net * M.Bt + i];
     nv = (int)wsum((float)nv);  // exact: an integer count far below 2^24
-    if (!M.tvalid[item] || nv == 0) {
-        for (int o = lane; o < M.Out; o += 64) dO[o] = 0.0f;
-        if (lane == 0) M.tloss[item] = 0.0f;
-        return;
-    }
-    if (M.m > 0) {  // subset move: the likelihood of the subset's coordinates only
-        const int m = M.m, nd = 2 * m - 1;
-        const int* S = M.tsub + item * kMaxSubset;
-        for (int o = lane; o < M.Out; o += 64) dO[o] = 0.0f;
-        __syncthreads();  // the zeros are written before the subset's channels
-        Mix mw;
-        mix_weights(O, K, mw);
-        float ell[kMaxK], best = -INFINITY;
-        for (int mc = 0; mc < K; ++mc) {
-            float part = 0.0f;
-            for (int d = lane; d < nd; d += 64) {
-                const int ch = subset_channel(S, d, m, N);
-                const float sg = smax_of(ch, N) * sigm(O[K + K * D + mc * D + ch]);
-                const float z = (dl[d] - O[K + mc * D + ch]) / sg;
-                part += logf(sg) + 0.5f * kLog2Pi + 0.5f * z * z;
-            }
-            ell[mc] = mw.lw[mc] - wsum(part);
-            best = fmaxf(best, ell[mc]);
-        }
-        float se = 0.0f;
-        for (int mc = 0; mc < K; ++mc) se += expf(ell[mc] - best);
-        const float logp = best + logf(se);
-        const float inv = 1.0f / (float)nv;
-        for (int mc = 0; mc < K; ++mc) {
-            const float r = expf(ell[mc] - logp);
-            if (lane == 0) dO[mc] = (expf(mw.lw[mc]) - r) * inv;
-            for (int d = lane; d < nd; d += 64) {
-                const int ch = subset_channel(S, d, m, N);
-                const float sm = smax_of(ch, N);
-                const float sg = sm * sigm(O[K + K * D + mc * D + ch]);
-                const float z = (dl[d] - O[K + mc * D + ch]) / sg;
-                dO[K + mc * D + ch] = -r * z / sg * inv;
-                dO[K + K * D + mc * D + ch] = -r * (z * z - 1.0f) * (1.0f - sg / sm) * inv;
-            }
-        }
-        if (lane == 0) M.tloss[item] = -logp;
-        return;
-    }
-    Mix mw;
-    mix_weights(O, K, mw);
-    float ell[kMaxK], best = -INFINITY;
-    for (int m = 0; m < K; ++m) {
-        float part = 0.0f;
-        for (int d = lane; d < D; d += 64) {
-            const float sg = smax_of(d, N) * sigm(O[K + K * D + m * D + d]);
-            const float z = (dl[d] - O[K + m * D + d]) / sg;
-            part += logf(sg) + 0.5f * kLog2Pi + 0.5f * z * z;
-        }
-        ell[m] = mw.lw[m] - wsum(part);
-        best = fmaxf(best, ell[m]);
-    }
-    float s = 0.0f;
-    for (int m = 0; m < K; ++m) s += expf(ell[m] - best);
-    const float logp = best + logf(s);
-    const float inv = 1.0f / (float)nv;
-    for (int m = 0; m < K; ++m) {
-        const float r = expf(ell[m] - logp);
-        if (lane == 0) dO[m] = (expf(mw.lw[m]) - r) * inv;
-        for (int d = lane; d < D; d += 64) {
-            const float sm = smax_of(d, N);
-            const float sg = sm * sigm(O[K + K * D + m * D + d]);
-            const float z = (dl[d] - O[K + m * D + d]) / sg;
-            dO[K + m * D + d] = -r * z / sg * inv;
-            dO[K + K * D + m * D + d] = -r * (z * z - 1.0f) * (1.0f - sg / sm) * inv;
-        }
-    }
-    if (lane == 0) M.tloss[item] = -logp;
-}
-
-__global__ void k_silu_back(const float* dH, const float* P, float* dP, int64_t n) {
-    const int64_t net = blockIdx.y;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const float p = P[net * n + i];
-        const float s = sigm(p);
-        dP[net * n + i] = dH[net * n + i] * s * (1.0f + p * (1.0f - s));
-    }
-}
-
-// column sums of Y [rows][cols] (bias gradients): 64 columns per 256-thread
-// block, four row slices per column summed in a fixed order
-__global__ __launch_bounds__(256) void k_colsum(const float* Y, int rows, int cols, int64_t sY, float* out,
-                                                int64_t sOut) {
-    __shared__ float part[4][64];
-    const int net = blockIdx.y;
-    const int c = threadIdx.x & 63, slice = threadIdx.x >> 6;
-    const int j = blockIdx.x * 64 + c;
-    float s = 0.0f;
-    if (j < cols) {
-        const float* y = Y + net * sY + j;
-#pragma unroll 8
-        for (int r = slice; r < rows; r += 4) s += y[(int64_t)r * cols];
-    }
-    part[slice][c] = s;
+    if (lane == 0) count[wave] = nv;
     __syncthreads();
-    if (slice == 0 && j < cols) out[net * sOut + j] = (part[0][c] + part[1][c]) + (part[2][c] + part[3][c]);
+    nv = 0;
+    for (int w = 0; w < kHeadWaves; ++w) nv += count[w];
+    const bool none = !M.tvalid[item] || nv == 0;
+    // subset move (m > 0): the likelihood of the subset's coordinates only
+    const int m = M.m, nd = m > 0 ? 2 * m - 1 : D;
+    const int* S = M.tsub + item * kMaxSubset;
+    if (none || m > 0)
+        for (int o = tid; o < M.Out; o += 64 * kHeadWaves) dO[o] = 0.0f;
+    if (none) {
+        if (tid == 0) M.tloss[item] = 0.0f;
+        return;
+    }
+    const auto channel = [&](int d) { return m > 0 ? subset_channel(S, d, m, N) : d; };
+    // the same sums as a loop over the components makes, an exponential per lane
+    const auto lane_of = [](float v, int i) {
+        return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
+    };
+    const auto log_sum = [&](float v) {
+        float best = -INFINITY, s = 0.0f;
+        for (int i = 0; i < K; ++i) best = fmaxf(best, lane_of(v, i));
+        const float e = expf(v - best);
+        for (int i = 0; i < K; ++i) s += lane_of(e, i);
+        return best + logf(s);
+    };
+    const float own = O[min(lane, K - 1)];  // lane c: component c
+    const float lw = own - log_sum(own);
+    constexpr int kKept = 4;  // widths and deviations kept between the two passes, 64 coordinates each
+    float sgs[kKept], zs[kKept];
+    const auto at = [&](int mc, int d, float& sg, float& z) {
+        const int ch = channel(d);
+        sg = smax_of(ch, N) * sigm(O[K + K * D + mc * D + ch]);
+        z = (dl[d] - O[K + mc * D + ch]) / sg;
+    };
+    for (int mc = wave; mc < K; mc += kHeadWaves) {
+        float part = 0.0f;
+        const auto add = [&](float sg, float z) { part += logf(sg) + 0.5f * kLog2Pi + 0.5f * z * z; };
+#pragma unroll
+        for (int i = 0; i < kKept; ++i)
+            if (lane + 64 * i < nd) {
+                at(mc, lane + 64 * i, sgs[i], zs[i]);
+                add(sgs[i], zs[i]);
+            }
+        for (int d = lane + 64 * kKept; d < nd; d += 64) {
+            float sg, z;
+            at(mc, d, sg, z);
+            add(sg, z);
+        }
+        const float sum = wsum(part);
+        if (lane == 0) ells[mc] = sum;
+    }
+    __syncthreads();  // also: the zeros are written before the subset's channels
+    const float ell = lw - ells[min(lane, K - 1)];
+    const float logp = log_sum(ell);
+    const float inv = 1.0f / (float)nv;
+    const float rs = expf(ell - logp), ws = expf(lw);
+    const bool kept = K <= kHeadWaves;  // a wave's only component
+    for (int mc = wave; mc < K; mc += kHeadWaves) {
+        const float r = lane_of(rs, mc);
+        if (lane == 0) dO[mc] = (lane_of(ws, mc) - r) * inv;
+        const auto put = [&](int d, float sg, float z) {
+            const int ch = channel(d);
+            const float sm = smax_of(ch, N);
+            dO[K + mc * D + ch] = -r * z / sg * inv;
+            dO[K + K * D + mc * D + ch] = -r * (z * z - 1.0f) * (1.0f - sg / sm) * inv;
+        };
+#pragma unroll
+        for (int i = 0; i < kKept; ++i)
+            if (lane + 64 * i < nd) {
+                if (!kept) at(mc, lane + 64 * i, sgs[i], zs[i]);
+                put(lane + 64 * i, sgs[i], zs[i]);
+            }
+        for (int d = lane + 64 * kKept; d < nd; d += 64) {
+            float sg, z;
+            at(mc, d, sg, z);
+            put(d, sg, z);
+        }
+    }
+    if (tid == 0) M.tloss[item] = -logp;
 }
 
-// where parameter p of a net sits in the fragment copy (-1: a bias)
-__device__ inline int64_t fragment_at(const MlpDev& M, int64_t p) {
-    if (p >= M.oW1 && p < M.ob1) {
-        const int64_t q = p - M.oW1;
-        return frag_at(0, M.In, (int)(q / M.H), (int)(q % M.H));
+// where parameter p of a net sits in the fragment copy (-1: a bias); a net has
+// fewer than 2^31 parameters, so the divisions are 32-bit
+__device__ inline int64_t fragment_at(const MlpDev& M, uint32_t p) {
+    const uint32_t H = (uint32_t)M.H, Out = (uint32_t)M.Out;
+    if (p < (uint32_t)M.ob1) {
+        const uint32_t q = p - (uint32_t)M.oW1;
+        return frag_at(0, M.In, (int)(q / H), (int)(q % H));
     }
-    if (p >= M.oW2 && p < M.ob2) {
-        const int64_t q = p - M.oW2;
-        return frag_at(frag_w2(M), M.H, (int)(q / M.H), (int)(q % M.H));
+    if (p >= (uint32_t)M.oW2 && p < (uint32_t)M.ob2) {
+        const uint32_t q = p - (uint32_t)M.oW2;
+        return frag_at(frag_w2(M), M.H, (int)(q / H), (int)(q % H));
     }
-    if (p >= M.oW3 && p < M.ob3) {
-        const int64_t q = p - M.oW3;
-        return frag_at(frag_w3(M), M.H, (int)(q / M.Out), (int)(q % M.Out));
+    if (p >= (uint32_t)M.oW3 && p < (uint32_t)M.ob3) {
+        const uint32_t q = p - (uint32_t)M.oW3;
+        return frag_at(frag_w3(M), M.H, (int)(q / Out), (int)(q % Out));
     }
     return -1;
 }
-__device__ inline void store_bf16(const MlpDev& M, int64_t i, float w) {  // i over nets x NP
+__device__ inline void store_bf16(const MlpDev& M, int64_t net, uint32_t p, float w) {
     const uint16_t b = f_to_bf16(w);
-    M.wbf[i] = b;
+    M.wbf[net * M.NP + p] = b;
     if (M.In % 32 != 0 || M.H % 32 != 0) return;  // no fragment order for this shape (the fused path is off)
-    const int64_t net = i / M.NP, f = fragment_at(M, i - net * M.NP);
+    const int64_t f = fragment_at(M, p);
     if (f >= 0) M.wbt[net * M.NPt + f] = b;
 }
 
+// a net per blockIdx.y
 __global__ void k_adam(MlpDev M, float lr, float c1, float c2) {
-    const int64_t n = (int64_t)M.nets * M.NP;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t net = blockIdx.y, at = net * M.NP;
+    for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < (uint32_t)M.NP; p += gridDim.x * blockDim.x) {
+        const int64_t i = at + p;
         const float g = M.grad[i];
         const float m = 0.9f * M.am[i] + 0.1f * g;
         const float v = 0.999f * M.av[i] + 0.001f * g * g;
@@ -786,14 +910,14 @@ __global__ void k_adam(MlpDev M, float lr, float c1, float c2) {
         M.av[i] = v;
         const float w = M.master[i] - lr * (m / c1) / (sqrtf(v / c2) + 1e-8f);
         M.master[i] = w;
-        store_bf16(M, i, w);
+        store_bf16(M, net, p, w);
     }
 }
 
 __global__ void k_sync_bf16(MlpDev M) {
-    const int64_t n = (int64_t)M.nets * M.NP;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        store_bf16(M, i, M.master[i]);
+    const int64_t net = blockIdx.y;
+    for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < (uint32_t)M.NP; p += gridDim.x * blockDim.x)
+        store_bf16(M, net, p, M.master[net * M.NP + p]);
 }
 
 // ------------------------------------------------------------------ the move
@@ -1381,74 +1505,89 @@ hipError_t mlp_forward(const MlpDev& M, int train, int into_reverse, hipStream_t
     float* P2 = train ? M.tP2 : M.P2;
     float* H2 = train ? M.tH2 : M.H2;
     float* O = train ? M.tO : (into_reverse ? M.Or : M.Of);
-    Gemm<uint16_t> g{};
-    g.A = X; g.sA = (int64_t)B * M.In; g.as0 = M.In; g.as1 = 1;
-    g.B = M.wbf + M.oW1; g.sB = M.NP; g.bs0 = M.H; g.bs1 = 1;
-    g.bias = M.master + M.ob1; g.sBias = M.NP;
-    g.Cpre = P1; g.Cact = H1; g.sC = (int64_t)B * M.H; g.M = B; g.N = M.H; g.K = M.In;
-    hipError_t e = gemm<uint16_t, 1>(g, M.nets, st);
+    const auto layer = [&](const float* A, int in, int64_t w, int64_t b, int out, float* C, float* act) {
+        Gemm<uint16_t> g{};
+        g.A = {A, (int64_t)B * in, in};
+        g.B = {M.wbf + w, M.NP, out};
+        g.bias = M.master + b;
+        g.sBias = M.NP;
+        g.C = C;
+        g.act = act;
+        g.sC = (int64_t)B * out;
+        g.M = B;
+        g.N = out;
+        g.K = in;
+        return act ? gemm<kSilu>(g, M.nets, st) : gemm<kPlain>(g, M.nets, st);
+    };
+    hipError_t e = layer(X, M.In, M.oW1, M.ob1, M.H, P1, H1);
     if (e != hipSuccess) return e;
-    g.A = H1; g.sA = (int64_t)B * M.H; g.as0 = M.H;
-    g.B = M.wbf + M.oW2; g.bs0 = M.H;
-    g.bias = M.master + M.ob2;
-    g.Cpre = P2; g.Cact = H2; g.K = M.H;
-    if ((e = gemm<uint16_t, 1>(g, M.nets, st)) != hipSuccess) return e;
-    g.A = H2;
-    g.B = M.wbf + M.oW3; g.bs0 = M.Out;
-    g.bias = M.master + M.ob3;
-    g.Cpre = O; g.Cact = nullptr; g.sC = (int64_t)B * M.Out; g.N = M.Out; g.K = M.H;
-    return gemm<uint16_t, 0>(g, M.nets, st);
+    if ((e = layer(H1, M.H, M.oW2, M.ob2, M.H, P2, H2)) != hipSuccess) return e;
+    return layer(H2, M.H, M.oW3, M.ob3, M.Out, O, nullptr);
 }
 
 hipError_t mlp_backward(const MlpDev& M, hipStream_t st) {
     hipError_t e;
     const int B = M.Bt;
-    hipLaunchKernelGGL(k_head_train, dim3(B, M.nets), dim3(64), 0, st, M);
+    hipLaunchKernelGGL(k_head_train, dim3(B, M.nets), dim3(64 * kHeadWaves), 0, st, M);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    auto wgrad = [&](const float* act, int in, const float* dY, int out, int64_t off) {
-        Gemm<float> g{};
-        g.A = act; g.sA = (int64_t)B * in; g.as0 = 1; g.as1 = in;
-        g.B = dY; g.sB = (int64_t)B * out; g.bs0 = out; g.bs1 = 1;
-        g.bias = nullptr; g.Cpre = M.grad + off; g.sC = M.NP; g.M = in; g.N = out; g.K = B;
-        return gemm<float, 0>(g, M.nets, st);
-    };
-    auto bgrad = [&](const float* dY, int out, int64_t off) {
-        hipLaunchKernelGGL(k_colsum, dim3((out + 63) / 64, M.nets), dim3(256), 0, st, dY, B, out, (int64_t)B * out,
-                           M.grad + off, M.NP);
-        return hipGetLastError();
-    };
-    auto xgrad = [&](const float* dY, int out, int64_t woff, int in, float* dX) {
+    // gradients at the hidden layers' SiLU inputs: dZ2 in tdB, dZ1 in tdA
+    const auto hidden = [&](const float* dY, int out, int64_t w, const float* Z, float* dZ) {
         Gemm<uint16_t> g{};
-        g.A = dY; g.sA = (int64_t)B * out; g.as0 = out; g.as1 = 1;
-        g.B = M.wbf + woff; g.sB = M.NP; g.bs0 = 1; g.bs1 = out;
-        g.bias = nullptr; g.Cpre = dX; g.sC = (int64_t)B * in; g.M = B; g.N = in; g.K = out;
-        return gemm<uint16_t, 0>(g, M.nets, st);
+        g.A = {dY, (int64_t)B * out, out};
+        g.B = {M.wbf + w, M.NP, out};
+        g.C = dZ;
+        g.Z = Z;
+        g.sC = (int64_t)B * M.H;
+        g.M = B;
+        g.N = M.H;
+        g.K = out;
+        return gemm<kSiluBack>(g, M.nets, st);
     };
-    auto sback = [&](const float* dH, const float* P, float* dP) {
-        const int64_t n = (int64_t)B * M.H;
-        hipLaunchKernelGGL(k_silu_back, dim3((unsigned)((n + 255) / 256), M.nets), dim3(256), 0, st, dH, P, dP, n);
-        return hipGetLastError();
-    };
-    if ((e = wgrad(M.tH2, M.H, M.tdO, M.Out, M.oW3)) != hipSuccess) return e;
-    if ((e = bgrad(M.tdO, M.Out, M.ob3)) != hipSuccess) return e;
-    if ((e = xgrad(M.tdO, M.Out, M.oW3, M.H, M.tdA)) != hipSuccess) return e;
-    if ((e = sback(M.tdA, M.tP2, M.tdB)) != hipSuccess) return e;
-    if ((e = wgrad(M.tH1, M.H, M.tdB, M.H, M.oW2)) != hipSuccess) return e;
-    if ((e = bgrad(M.tdB, M.H, M.ob2)) != hipSuccess) return e;
-    if ((e = xgrad(M.tdB, M.H, M.oW2, M.H, M.tdA)) != hipSuccess) return e;
-    if ((e = sback(M.tdA, M.tP1, M.tdB)) != hipSuccess) return e;
-    if ((e = wgrad(M.tX, M.In, M.tdB, M.H, M.oW1)) != hipSuccess) return e;
-    return bgrad(M.tdB, M.H, M.ob1);
+    if ((e = hidden(M.tdO, M.Out, M.oW3, M.tP2, M.tdB)) != hipSuccess) return e;
+    if ((e = hidden(M.tdB, M.H, M.oW2, M.tP1, M.tdA)) != hipSuccess) return e;
+    LayerGrads L{};
+    L.sGrad = M.NP;
+    L.nets = M.nets;
+    const float* act[3] = {M.tH2, M.tH1, M.tX};
+    const float* dY[3] = {M.tdO, M.tdB, M.tdA};
+    const int in[3] = {M.H, M.H, M.In}, out[3] = {M.Out, M.H, M.H};
+    const int64_t w[3] = {M.oW3, M.oW2, M.oW1}, b[3] = {M.ob3, M.ob2, M.ob1};
+    int64_t tiles64 = 0;
+    for (int l = 0; l < 3; ++l) tiles64 += (int64_t)tiles_of(in[l], out[l], 64) * M.nets;
+    const int BM = tile_rows(tiles64);
+    bool wide = true;
+    for (int l = 0, at = 0; l < 3; ++l) {
+        Gemm<float>& g = L.g[l];
+        g.A = {act[l], (int64_t)B * in[l], in[l]};
+        g.B = {dY[l], (int64_t)B * out[l], out[l]};
+        g.C = M.grad + w[l];
+        g.sC = M.NP;
+        g.M = in[l];
+        g.N = out[l];
+        g.K = B;
+        wide = wide && reads_wide(g.A, g.M) && reads_wide(g.B, g.N);
+        L.bias[l] = M.grad + b[l];
+        L.tiles[l] = panel_blocks((out[l] + BM - 1) / BM * M.nets, (in[l] + BM - 1) / BM);
+        L.end[l] = at += L.tiles[l] + ((out[l] + 63) / 64 * M.nets + 7) / 8 * 8;
+    }
+    const dim3 grid(L.end[2]);
+    if (BM == 64 && wide) hipLaunchKernelGGL((k_layer_grads<64, true>), grid, dim3(256), 0, st, L);
+    else if (BM == 64) hipLaunchKernelGGL((k_layer_grads<64, false>), grid, dim3(256), 0, st, L);
+    else if (wide) hipLaunchKernelGGL((k_layer_grads<32, true>), grid, dim3(256), 0, st, L);
+    else hipLaunchKernelGGL((k_layer_grads<32, false>), grid, dim3(256), 0, st, L);
+    return hipGetLastError();
 }
+
+static int param_blocks(const MlpDev& M) { return (int)(M.NP / 256 < 2048 ? M.NP / 256 + 1 : 2048); }
 
 hipError_t mlp_adam(const MlpDev& M, float lr, int64_t t, hipStream_t st) {
     const float c1 = 1.0f - powf(0.9f, (float)t), c2 = 1.0f - powf(0.999f, (float)t);
-    hipLaunchKernelGGL(k_adam, dim3(1024), dim3(256), 0, st, M, lr, c1, c2);
+    hipLaunchKernelGGL(k_adam, dim3(param_blocks(M), M.nets), dim3(256), 0, st, M, lr, c1, c2);
     return hipGetLastError();
 }
 
 hipError_t mlp_sync_bf16(const MlpDev& M, hipStream_t st) {
-    hipLaunchKernelGGL(k_sync_bf16, dim3(1024), dim3(256), 0, st, M);
+    hipLaunchKernelGGL(k_sync_bf16, dim3(param_blocks(M), M.nets), dim3(256), 0, st, M);
     return hipGetLastError();
 }
 
