@@ -403,7 +403,7 @@ Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layo
         r.en_pairs = L.take(np * 2);
         r.en_rank = L.take(rank * 2);
         r.en_tile = L.take(tiles * 4);
-        r.en_band = L.take(band * 8);
+        r.en_band = L.take(band * 8 + kBandSlack * 4);
         r.en_end = L.off;
     }
     r.arrived = L.take((S + 1) * 4);
@@ -432,7 +432,7 @@ Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layo
         r.p_after = L.take(copies * (max_N / 2 + 1) * 2);
         r.p_prod = L.take(prod * 8);
         r.p_list = L.take(list * sizeof(PairEntry));
-        r.p_band = L.take(band * 4);
+        r.p_band = L.take((band + kBandSlack) * 4);
         r.p_end = L.off;
     }
     r.mlp = L.off;
@@ -801,7 +801,7 @@ hipError_t build_pairs(rlpt_ctx* c, const rlpt_graph* const* g, const std::vecto
             L.first = first_item;
             L.samples = (int)mine.size();
             L.n = L.samples * c->Rc;
-            const int per_block = 4 * pairs_tiles_per_wave(kv.first);
+            const int per_block = pairs_product_waves(kv.first) * pairs_tiles_per_wave(kv.first);
             for (int s : mine) {
                 const std::vector<uint32_t>& t = g[s]->pair_tile;
                 const int n = (int)t.size() / 2;

@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256) void k_energy_band(DevPtrs<R> P, ShapeInfo sh,
     const SampleDev sd = P.samples[mu];
     const EnergySample es = P.en_samples[mu];
     const int N = sd.N, np = N * (N - 1) / 2, n_tiles = (np + kRows - 1) / kRows, Rc = sh.copies_per_sample;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, quad = lane >> 4;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, col = lane & 15, quad = lane >> 4;
     const int t0 = (int)((int64_t)n_tiles * part / parts), t1 = (int)((int64_t)n_tiles * (part + 1) / parts);
     const int c = group * kCols + col;
     R2<R>* a = reinterpret_cast<R2<R>*>(smem);  // [mode][16 copies]
@@ -83,24 +83,32 @@ __global__ __launch_bounds__(256) void k_energy_band(DevPtrs<R> P, ShapeInfo sh,
         };
         for (int t = t0 + wave; t < t1; t += 4) {
             const int n4 = (int)(tile[t + 1] - tile[t]);
-            const double* A = P.en_band + es.band_base + (size_t)tile[t] * 64 + lane;
+            // (reads up to kBandSlack words past the tile's values, unused)
+            const double* A = P.en_band + es.band_base + (size_t)tile[t] * 64;
             const uint32_t* pq = pm + (t * kRows - first);
             f64x4 gr = {0, 0, 0, 0}, gi = gr;
             double ra[8];  // eight operands ahead of their use
 #pragma unroll
-            for (int u = 0; u < 8; ++u) ra[u] = A[(size_t)min(u, n4 - 1) * 64];
-            for (int q0 = 0; q0 < n4; q0 += 8) {
+            for (int u = 0; u < 8; ++u) ra[u] = (A + u * 64)[lane];
+            const auto step = [&](int q, double j) {
+                double br, bi;
+                product(pq[4 * q + quad], br, bi);
+                gr = __builtin_amdgcn_mfma_f64_16x16x4f64(j, br, gr, 0, 0, 0);
+                gi = __builtin_amdgcn_mfma_f64_16x16x4f64(j, bi, gi, 0, 0, 0);
+            };
+            int q0 = 0;
+            for (; q0 + 8 <= n4; q0 += 8) {  // no branch inside: the next loads stay in flight
+                A += 8 * 64;
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    if (q0 + u >= n4) break;
                     const double j = ra[u];
-                    ra[u] = A[(size_t)min(q0 + u + 8, n4 - 1) * 64];
-                    double br, bi;
-                    product(pq[4 * (q0 + u) + quad], br, bi);
-                    gr = __builtin_amdgcn_mfma_f64_16x16x4f64(j, br, gr, 0, 0, 0);
-                    gi = __builtin_amdgcn_mfma_f64_16x16x4f64(j, bi, gi, 0, 0, 0);
+                    ra[u] = (A + u * 64)[lane];
+                    step(q0 + u, j);
                 }
             }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (q0 + u < n4) step(q0 + u, ra[u]);
             // lane (quad, col) holds rows quad, 4 + quad, 8 + quad, 12 + quad of copy col
 #pragma unroll
             for (int r = 0; r < 4; ++r) {

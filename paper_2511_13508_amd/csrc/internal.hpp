@@ -159,6 +159,7 @@ struct DevPtrs {
 
 constexpr int kAfterBaths = 8;   // baths of one sample that a workgroup measures after a sweep
 constexpr int kResyncParts = 8;  // term ranges of one energy recomputation (workgroups per copy group)
+constexpr int kBandSlack = 8 * 128;  // 32-bit words past a band that the banded products may read
 constexpr int kEnergyParts = 64; // most ranges of the banded recomputation (one wave sums them)
 
 // offsets (in doubles) of the [S][T] accumulator blocks inside DevPtrs::obs

@@ -64,16 +64,17 @@ __device__ inline void chunk_prefetch(const DevPtrs<R>& P, const uint32_t* lb, i
     using JT = typename J4<R>::T;
     const uint32_t beg = lb[l], end = lb[l + 1];
     const JT* __restrict__ Jv = reinterpret_cast<const JT*>(P.cJ);
+    // a lane past the list's end reads chunk 0: a load behind a branch would
+    // keep the registers' old values alive and wait for the loads before it
     rg.n = 0;
 #pragma unroll
     for (int m = 0; m < PF; ++m) {
         const uint32_t c = beg + t + (uint32_t)m * nt;
-        if (c < end) {
-            rg.x[m] = P.cx[c];
-            rg.yz[m] = P.cyz[c];
-            rg.J[m] = Jv[c];
-            rg.n = m + 1;
-        }
+        const uint32_t at = c < end ? c : 0;
+        rg.x[m] = P.cx[at];
+        rg.yz[m] = P.cyz[at];
+        rg.J[m] = Jv[at];
+        rg.n += c < end ? 1 : 0;
     }
 }
 

@@ -194,12 +194,13 @@ __device__ inline void draw_sweep(const PairDev& Q, const ShapeInfo& sh, int sam
 // Blocks past the product's draw the copies' sweeps.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void k_pair_product(DevPtrs<float> P, PairDev Q, ShapeInfo sh, int first_item,
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_pair_product(DevPtrs<float> P, PairDev Q, ShapeInfo sh, int first_item,
                                                       int samples, int groups, int n_product, int per_wave, int ahead) {
     extern __shared__ __align__(16) unsigned char smem[];
     if ((int)blockIdx.x >= n_product) {
         const ItemDev it = Q.items[first_item + blockIdx.x - n_product];
-        draw_sweep<256>(Q, sh, it.sample, it.first_copy, P.counters->sweeps_done + ahead, Q.samples[it.sample].N,
+        draw_sweep<BLOCK>(Q, sh, it.sample, it.first_copy, P.counters->sweeps_done + ahead, Q.samples[it.sample].N,
                                reinterpret_cast<int*>(smem));
         return;
     }
@@ -214,46 +215,55 @@ __global__ __launch_bounds__(256) void k_pair_product(DevPtrs<float> P, PairDev 
     {
         const int c = group * kCopyTile + col;
         const float2* amp = reinterpret_cast<const float2*>(P.amp) + P.samples[sample].amp_base + (int64_t)min(c, R - 1) * N;
-        for (int m = tid >> 4; m < N; m += 16) a[m * kCopyTile + col] = c < R ? amp[m] : make_float2(0.0f, 0.0f);
+        for (int m = tid >> 4; m < N; m += BLOCK / 16) a[m * kCopyTile + col] = c < R ? amp[m] : make_float2(0.0f, 0.0f);
     }
     // the pairs of the block's columns
-    const int t0 = chunk * 4 * per_wave, t1 = min(t0 + 4 * per_wave, ps.n_tiles) - 1;
+    const int t0 = chunk * (BLOCK / 64) * per_wave, t1 = min(t0 + BLOCK / 64 * per_wave, ps.n_tiles) - 1;
     const uint2 b0 = Q.tile[ps.tile_base + t0], b1 = Q.tile[ps.tile_base + t1];
     const int first = (int)(b0.y & 0xffffu), end = (int)(b1.y & 0xffffu) + 4 * (int)(b1.y >> 16);
     uint32_t* pm = reinterpret_cast<uint32_t*>(a + N * kCopyTile);  // LDS offsets of the two modes' rows
-    for (int i = tid; i < end - first + 4; i += 256) {  // a tile's columns are whole 4s
+    for (int i = tid; i < end - first + 4; i += BLOCK) {  // a tile's columns are whole 4s
         const uint32_t v = Q.pm[ps.pm_base + min(first + i, np - 1)];
         pm[i] = (v & 255u) * (kCopyTile * 8) | (v >> 8) * (kCopyTile * 8) << 16;
     }
     __syncthreads();
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // scalar: a tile's bounds and its operand's address
     for (int i = 0; i < per_wave; ++i) {
-        const int t = (chunk * 4 + wave) * per_wave + i;
+        const int t = (chunk * (BLOCK / 64) + wave_u) * per_wave + i;
         if (t >= ps.n_tiles) break;
         const uint2 blk = Q.tile[ps.tile_base + t];
         const int k0 = (int)(blk.y & 0xffffu), n4 = (int)(blk.y >> 16);
-        const float2* A = reinterpret_cast<const float2*>(Q.band + ps.band_base + blk.x) + lane;
+        // (reads up to kBandSlack values past the tile's, unused)
+        const float2* A = reinterpret_cast<const float2*>(Q.band + ps.band_base + blk.x);
         f32x4 r0 = {0, 0, 0, 0}, i0 = r0, r1 = r0, i1 = r0;
         // eight operands ahead of their use
         float2 ra[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) ra[u] = A[min(u, n4 - 1) * 64];
+        for (int u = 0; u < 8; ++u) ra[u] = (A + u * 64)[lane];
         const uint32_t* pq = pm + (k0 - first) + quad;
-        for (int q0 = 0; q0 < n4; q0 += 8) {
+        const auto step = [&](int q, float2 j) {
+            const uint32_t v = pq[4 * q];
+            const float2 x = *reinterpret_cast<const float2*>(smem + (v & 0xffffu) + 8 * col);
+            const float2 y = *reinterpret_cast<const float2*>(smem + (v >> 16) + 8 * col);
+            const float br = x.x * y.x - x.y * y.y, bi = x.x * y.y + x.y * y.x;
+            r0 = __builtin_amdgcn_mfma_f32_16x16x4f32(j.x, br, r0, 0, 0, 0);
+            i0 = __builtin_amdgcn_mfma_f32_16x16x4f32(j.x, bi, i0, 0, 0, 0);
+            r1 = __builtin_amdgcn_mfma_f32_16x16x4f32(j.y, br, r1, 0, 0, 0);
+            i1 = __builtin_amdgcn_mfma_f32_16x16x4f32(j.y, bi, i1, 0, 0, 0);
+        };
+        int q0 = 0;
+        for (; q0 + 8 <= n4; q0 += 8) {  // no branch inside: the next loads stay in flight
+            A += 8 * 64;
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                if (q0 + u >= n4) break;
                 const float2 j = ra[u];
-                const uint32_t v = pq[4 * (q0 + u)];
-                const float2 x = *reinterpret_cast<const float2*>(smem + (v & 0xffffu) + 8 * col);
-                const float2 y = *reinterpret_cast<const float2*>(smem + (v >> 16) + 8 * col);
-                ra[u] = A[min(q0 + u + 8, n4 - 1) * 64];
-                const float br = x.x * y.x - x.y * y.y, bi = x.x * y.y + x.y * y.x;
-                r0 = __builtin_amdgcn_mfma_f32_16x16x4f32(j.x, br, r0, 0, 0, 0);
-                i0 = __builtin_amdgcn_mfma_f32_16x16x4f32(j.x, bi, i0, 0, 0, 0);
-                r1 = __builtin_amdgcn_mfma_f32_16x16x4f32(j.y, br, r1, 0, 0, 0);
-                i1 = __builtin_amdgcn_mfma_f32_16x16x4f32(j.y, bi, i1, 0, 0, 0);
+                ra[u] = (A + u * 64)[lane];
+                step(q0 + u, j);
             }
         }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q0 + u < n4) step(q0 + u, ra[u]);
         // lane (quad, col) holds rows 4 quad .. 4 quad + 3 of copy col
         const int c = group * kCopyTile + col;
         float2* G = Q.prod + ps.prod_base;
@@ -279,7 +289,8 @@ __global__ __launch_bounds__(256) void k_pair_reduce(DevPtrs<float> P, PairDev Q
     const int group = (blockIdx.x / samples) % groups, chunk = blockIdx.x / (samples * groups);
     const PairSample ps = Q.samples[sample];
     const int N = ps.N, np = ps.n_pairs, R = sh.copies_per_sample;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, quad = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, quad = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float2* a = reinterpret_cast<float2*>(smem);
     const int c = group * kCopyTile + col;
     const int64_t at = P.samples[sample].amp_base + (int64_t)min(c, R - 1) * N;
@@ -689,18 +700,23 @@ hipError_t decide_b(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& 
 }  // namespace
 
 // a block's prologue (16 copies into LDS) is worth several row tiles per wave once there are many
-int pairs_tiles_per_wave(int N) { return N * (N - 1) / 2 >= 512 * kPairTile ? 4 : 1; }
+int pairs_product_waves(int N) { return N * (N - 1) / 2 >= 512 * kPairTile ? 8 : 4; }
+int pairs_tiles_per_wave(int N) { return N * (N - 1) / 2 >= 512 * kPairTile ? 2 : 1; }
 
 hipError_t launch_sweep_pairs(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& sh, const PairLaunch& L,
                               int ahead, hipStream_t st) {
     const int groups = (sh.copies_per_sample + kCopyTile - 1) / kCopyTile;
     const int tiles = (L.N * (L.N - 1) / 2 + kPairTile - 1) / kPairTile;
     const int per_wave = pairs_tiles_per_wave(L.N);
-    const int chunks = (tiles + 4 * per_wave - 1) / (4 * per_wave);
+    const int chunks = (tiles + pairs_product_waves(L.N) * per_wave - 1) / (pairs_product_waves(L.N) * per_wave);
     const int n_product = chunks * groups * L.samples;
     const size_t lds = (size_t)L.N * kCopyTile * sizeof(float2) + (size_t)L.columns * 4;
-    hipLaunchKernelGGL(k_pair_product, dim3(n_product + L.n), dim3(256), lds, st, P, Q, sh, L.first, L.samples, groups,
-                       n_product, per_wave, ahead);
+    if (pairs_product_waves(L.N) == 8)
+        hipLaunchKernelGGL(k_pair_product<512>, dim3(n_product + L.n), dim3(512), lds, st, P, Q, sh, L.first, L.samples,
+                           groups, n_product, per_wave, ahead);
+    else
+        hipLaunchKernelGGL(k_pair_product<256>, dim3(n_product + L.n), dim3(256), lds, st, P, Q, sh, L.first, L.samples,
+                           groups, n_product, per_wave, ahead);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (L.N > kGatherModes) {

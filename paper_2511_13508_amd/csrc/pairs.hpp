@@ -77,6 +77,7 @@ struct PairLaunch {
     int columns;  // most columns (and 4) that the row tiles of one product workgroup span
 };
 
+int pairs_product_waves(int N);   // waves per workgroup of the banded product
 int pairs_tiles_per_wave(int N);  // row tiles per wave of the banded product
 
 // fills band, desc and list of every sample (on the stream) from the context's
