@@ -558,11 +558,19 @@ int enqueue_sweeps(rlpt_ctx* c, int64_t done, int64_t n, int64_t* swaps_added) {
         } else if (c->pair_launch.empty()) {
             HIP_TRY(launch_sweep(cfg.precision, c->ptrs(), c->sh, c->launch, (int)step, c->stream), "sweep launch");
         } else {
-            for (int w = 0; w < (int)step; ++w)
+            for (int w = 0; w < (int)step; ++w) {
                 for (const PairLaunch& L : c->pair_launch)
-                    HIP_TRY(launch_sweep_pairs(c->pf, c->pairs, c->sh, L, w, c->stream), "sweep launch");
-            if (c->rest.n_items > 0)
-                HIP_TRY(launch_sweep(RLPT_FP32, &c->pf_rest, c->sh, c->rest, (int)step, c->stream), "sweep launch");
+                    HIP_TRY(launch_pair_fields(c->pf, c->pairs, c->sh, L, w, c->stream), "sweep launch");
+                if (c->side && w == 0) {  // the samples swept from their lists run beside the others' decisions
+                    HIP_TRY(hipEventRecord(c->fork, c->stream), "fork");
+                    HIP_TRY(hipStreamWaitEvent(c->side, c->fork, 0), "fork");
+                    HIP_TRY(launch_sweep(RLPT_FP32, &c->pf_rest, c->sh, c->rest, (int)step, c->side), "sweep launch");
+                    HIP_TRY(hipEventRecord(c->join, c->side), "join");
+                }
+                for (const PairLaunch& L : c->pair_launch)
+                    HIP_TRY(launch_pair_decide(c->pf, c->pairs, c->sh, L, c->stream), "sweep launch");
+            }
+            if (c->side) HIP_TRY(hipStreamWaitEvent(c->stream, c->join, 0), "join");
         }
         if (ev.first) {
             HIP_TRY(hipEventRecord(ev.second, c->stream), "event record");
@@ -739,14 +747,15 @@ std::map<int, std::vector<int>, std::greater<int>> samples_by_N(const rlpt_ctx* 
     return m;
 }
 
-// one item per copy: largest N first; within one N the samples in turn (each
-// XCD takes every eighth workgroup, so it reads few samples' lists), and each
-// sample's temperature slots from the hottest, which accepts the most updates
-std::vector<ItemDev> slot_items(const rlpt_ctx* c) {
+// one item per copy: group after group of samples; within a group the samples
+// in turn (each XCD takes every eighth workgroup, so it reads few samples'
+// lists), and each sample's temperature slots from the hottest, which accepts
+// the most updates
+std::vector<ItemDev> slot_items(const rlpt_ctx* c, const std::vector<std::vector<int>>& groups) {
     std::vector<ItemDev> items;
-    for (const auto& kv : samples_by_N(c))
+    for (const auto& samples : groups)
         for (int i = 0; i < c->Rc; ++i)
-            for (int s : kv.second) {
+            for (int s : samples) {
                 ItemDev it{};
                 it.first_copy = s * c->Rc + i;
                 it.n_copies = 1;
@@ -790,32 +799,41 @@ hipError_t build_pairs(rlpt_ctx* c, const rlpt_graph* const* g, const std::vecto
         first.insert(first.end(), q->pair_first.begin(), q->pair_first.end());
         max_quads = std::max<int64_t>(max_quads, q->n_terms());
     }
-    int first_item = 0;
+    // one launch for each kind of decision kernel, over samples of any N it
+    // takes (largest N first): alone, a class of few copies leaves compute units
+    // idle.  A class is served as a whole or not at all.
+    std::vector<std::vector<int>> groups(2);
     for (const auto& kv : samples_by_N(c)) {
-        std::vector<int> mine;
-        for (int s : kv.second)
-            if (smp[s].N > 0) mine.push_back(s);
-        if (mine.size() == kv.second.size()) {  // a class is served as a whole or not at all
-            PairLaunch L{};
-            L.N = kv.first;
-            L.first = first_item;
-            L.samples = (int)mine.size();
-            L.n = L.samples * c->Rc;
-            const int per_block = pairs_product_waves(kv.first) * pairs_tiles_per_wave(kv.first);
-            for (int s : mine) {
-                const std::vector<uint32_t>& t = g[s]->pair_tile;
-                const int n = (int)t.size() / 2;
-                for (int b0 = 0; b0 < n; b0 += per_block) {
-                    const uint32_t lo = t[2 * b0 + 1], hi = t[2 * std::min(b0 + per_block, n) - 1];
-                    L.columns = std::max(L.columns, (int)(hi & 0xffffu) + 4 * (int)(hi >> 16) - (int)(lo & 0xffffu) + 4);
-                }
-            }
-            c->pair_launch.push_back(L);
-        } else {
-            for (int s : mine) smp[s].N = 0;
+        bool whole = true;
+        for (int s : kv.second) whole = whole && smp[s].N > 0;
+        std::vector<int>& group = groups[kv.first > kGatherModes ? 0 : 1];
+        for (int s : kv.second) {
+            if (whole) group.push_back(s);
+            else smp[s].N = 0;
         }
-        first_item += (int)kv.second.size() * c->Rc;
     }
+    int first_item = 0;
+    for (const auto& group : groups) {
+        if (group.empty()) continue;
+        PairLaunch L{};
+        L.N = c->N[group[0]];
+        L.first = first_item;
+        L.samples = (int)group.size();
+        L.n = L.samples * c->Rc;
+        const int per_block = pairs_product_waves(L.N) * pairs_tiles_per_wave(L.N);
+        for (int s : group) {
+            const std::vector<uint32_t>& t = g[s]->pair_tile;
+            const int n = (int)t.size() / 2;
+            for (int b0 = 0; b0 < n; b0 += per_block) {
+                const uint32_t lo = t[2 * b0 + 1], hi = t[2 * std::min(b0 + per_block, n) - 1];
+                L.columns = std::max(L.columns, (int)(hi & 0xffffu) + 4 * (int)(hi >> 16) - (int)(lo & 0xffffu) + 4);
+            }
+        }
+        c->pair_launch.push_back(L);
+        first_item += L.n;
+    }
+    const std::vector<ItemDev> by_slot = slot_items(c, groups);
+    hipError_t e = upload(b, r.slot_items, by_slot, c->stream);
     std::vector<ItemDev> rest;
     std::vector<int> others;
     std::map<int, int> counts;
@@ -830,10 +848,14 @@ hipError_t build_pairs(rlpt_ctx* c, const rlpt_graph* const* g, const std::vecto
         std::map<int, int> copies;
         streaming_tile(c, counts, &block, &copies);
         if (lay_items(c, block, copies, others, &rest, &c->rest) != RLPT_OK) return hipErrorInvalidValue;
+        // a stream of the context's own for them; whatever fails here is freed by drop_side
+        if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&c->fork, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&c->join, hipEventDisableTiming);
     }
     c->pf_rest = c->pf;
     c->pf_rest.items = reinterpret_cast<const ItemDev*>(b + r.p_rest);
-    hipError_t e = upload(b, r.p_samples, smp, c->stream);
+    if (e == hipSuccess) e = upload(b, r.p_samples, smp, c->stream);
     if (e == hipSuccess) e = upload(b, r.p_rest, rest, c->stream);
     if (e == hipSuccess) e = upload(b, r.p_modes, pm, c->stream);
     if (e == hipSuccess) e = upload(b, r.p_rank, rank, c->stream);
@@ -928,6 +950,15 @@ void drop_events(rlpt_ctx* c) {
         }
     c->events.clear();
     c->spare.clear();
+}
+
+void drop_side(rlpt_ctx* c) {
+    if (c->side) (void)hipStreamSynchronize(c->side);
+    if (c->fork) (void)hipEventDestroy(c->fork);
+    if (c->join) (void)hipEventDestroy(c->join);
+    if (c->side) (void)hipStreamDestroy(c->side);
+    c->side = nullptr;
+    c->fork = c->join = nullptr;
 }
 
 void drop_graph(rlpt_ctx* c) {
@@ -1209,19 +1240,23 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
     if (cfg->precision == RLPT_FP64) up(r.beta, b64);
     else up(r.beta, b32);
     up(r.beta64, b64);
-    const std::vector<ItemDev> by_slot = slot_items(c);
-    up(r.slot_items, by_slot);
+    std::vector<ItemDev> by_slot;
     c->sh.en_parts = energy_parts(*cfg, graphs, n_graphs);
     if (c->sh.en_parts > 0 && e == hipSuccess) e = build_energy(c, graphs, b, r);
     if (!served.empty()) {
         if (e == hipSuccess) e = build_pairs(c, graphs, served, b, r);
     } else {
+        std::vector<std::vector<int>> groups;
+        for (const auto& kv : samples_by_N(c)) groups.push_back(kv.second);
+        by_slot = slot_items(c, groups);
+        up(r.slot_items, by_slot);
         plan_ahead(c, reinterpret_cast<const ItemDev*>(b + r.slot_items));
     }
     if (e == hipSuccess) e = launch_zero(c->acc_region, c->acc_region_bytes, c->stream);
     if (e == hipSuccess) e = launch_zero(b + r.arrived, ((size_t)n_graphs + 1) * 4, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
+        drop_side(c);
         delete c;
         return hip_fail(e, "rlpt_create upload");
     }
@@ -1234,6 +1269,7 @@ int rlpt_destroy(rlpt_ctx* c) {
     (void)hipStreamSynchronize(c->stream);
     drop_graph(c);
     drop_events(c);
+    drop_side(c);
     delete c;
     return RLPT_OK;
 }

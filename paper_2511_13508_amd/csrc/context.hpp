@@ -36,6 +36,8 @@ struct rlpt_ctx {
     std::vector<rlpt::PairLaunch> pair_launch;
     DevPtrs<float> pf_rest{};
     SweepLaunch rest{};
+    hipStream_t side = nullptr;  // of the rest, which runs beside them: forked from and joined to stream
+    hipEvent_t fork = nullptr, join = nullptr;
     rlpt::AheadLaunch ahead{};  // sweep of short lists (0 items: another kernel)
     // regions of the workspace
     void* ws = nullptr;

@@ -210,6 +210,7 @@ __global__ __launch_bounds__(BLOCK) void k_pair_product(DevPtrs<float> P, PairDe
     const int group = (blockIdx.x / samples) % groups, chunk = blockIdx.x / (samples * groups);
     const PairSample ps = Q.samples[sample];
     const int N = ps.N, np = ps.n_pairs, R = sh.copies_per_sample;
+    if (chunk * (BLOCK / 64) * per_wave >= ps.n_tiles) return;  // a sample smaller than the launch's largest
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 15, quad = lane >> 4;
     float2* a = reinterpret_cast<float2*>(smem);  // [mode][16 copies]
     {
@@ -703,7 +704,7 @@ hipError_t decide_b(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& 
 int pairs_product_waves(int N) { return N * (N - 1) / 2 >= 512 * kPairTile ? 8 : 4; }
 int pairs_tiles_per_wave(int N) { return N * (N - 1) / 2 >= 512 * kPairTile ? 2 : 1; }
 
-hipError_t launch_sweep_pairs(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& sh, const PairLaunch& L,
+hipError_t launch_pair_fields(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& sh, const PairLaunch& L,
                               int ahead, hipStream_t st) {
     const int groups = (sh.copies_per_sample + kCopyTile - 1) / kCopyTile;
     const int tiles = (L.N * (L.N - 1) / 2 + kPairTile - 1) / kPairTile;
@@ -724,11 +725,21 @@ hipError_t launch_sweep_pairs(const DevPtrs<float>& P, const PairDev& Q, const S
         const int blocks = (L.N + 4 * modes - 1) / (4 * modes) * groups * L.samples;
         hipLaunchKernelGGL(k_pair_reduce, dim3(blocks), dim3(256), (size_t)L.N * kCopyTile * sizeof(float2), st, P, Q, sh,
                            L.first, L.samples, groups, modes);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        return decide_b<768, 32, 4, 9, false>(P, Q, sh, L, st);
+        e = hipGetLastError();
     }
-    if (L.N < 80) return decide_b<1024, 16, 2, 6, true>(P, Q, sh, L, st);
-    return decide_b<1024, 16, 6, 10, true>(P, Q, sh, L, st);
+    return e;
+}
+
+hipError_t launch_pair_decide(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& sh, const PairLaunch& L,
+                              hipStream_t st) {
+    if (L.N > kGatherModes) return decide_b<768, 32, 4, 9, false>(P, Q, sh, L, st);
+    // A copy's chain of accepted updates is latency; 1024 threads shorten it,
+    // 512 let a compute unit (256 of them) interleave two copies' chains.  Us
+    // per sweep, 1024 -> 512: N = 96, 640 copies 121 -> 143, 960 146 -> 156, 1280
+    // 180 -> 167, 3200 461 -> 366; N = 128 198 -> 237, 255 -> 280, 331 -> 314,
+    // 809 -> 675; 1024 copies beside a list sweep 381 -> 354.
+    return L.n >= 4 * 256 ? decide_b<512, 16, 6, 10, true>(P, Q, sh, L, st)
+                          : decide_b<1024, 16, 6, 10, true>(P, Q, sh, L, st);
 }
 
 hipError_t launch_pairs_tables(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& sh, int n_samples, int max_N,

@@ -85,7 +85,9 @@ int pairs_tiles_per_wave(int N);  // row tiles per wave of the banded product
 hipError_t launch_pairs_tables(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& sh, int n_samples, int max_N,
                                int64_t max_quads, hipStream_t st);
 // one sweep of the launch's copies, `ahead` sweeps after the counters'
-hipError_t launch_sweep_pairs(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& sh, const PairLaunch& L,
+hipError_t launch_pair_fields(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& sh, const PairLaunch& L,
                               int ahead, hipStream_t st);
+hipError_t launch_pair_decide(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& sh, const PairLaunch& L,
+                              hipStream_t st);
 
 }  // namespace rlpt

@@ -125,3 +125,31 @@ def test_cached_checkpoint_across_sweeps(oracle, tmp_path, first):
     pt = oracle_pt(oracle, oracle.Graph(N, SEED), temps, 0, b.cfg, 6)
     pt.run(4)
     compare_fp32(b, [pt])
+
+
+@pytest.mark.parametrize("Ns,T,reps", [([137, 96, 30, 88, 40, 160], 4, 2), ([88, 20], 32, 32)])
+def test_mixed_sizes_side_by_side(oracle, Ns, T, reps):
+    """Samples of several N: one launch for N <= 136, one above, the smaller
+    ones swept from their lists on a second stream; and enough copies for the
+    smaller workgroups."""
+    compare_fp32(*run_both(oracle, Ns, T, reps, 2))
+
+
+def test_mixed_sizes_replay_bitwise_in_graphs():
+    """Captured segments (the second stream forked and joined inside) give the
+    eager run's bits, replay after replay, with eager sweeps between."""
+    temps = synth.geometric_temps(0.3, 1.5, 5)
+    graphs = [rlpt.Graph(N, SEED + i) for i, N in enumerate([96, 40, 140])]
+    kw = dict(n_temps=5, n_reps=2, n_bins=20, swap_interval=2, resync_interval=6, measure_interval=2)
+    a, b = (make_ctx(graphs, temps, **kw) for _ in range(2))
+    for c in (a, b):
+        c.init(3)
+    for n, segments in ((6, 2), (6, 1), (12, 2)):
+        a.run_graph(n, segments)
+        a.sweep(6)
+        b.sweep(n * segments + 6)
+        for mu in range(3):
+            assert np.array_equal(a.get_state(mu * a.R, a.R), b.get_state(mu * b.R, b.R)), (n, segments, mu)
+        assert np.array_equal(a.energies()[0], b.energies()[0])
+        assert np.array_equal(a.energies()[1], b.energies()[1])
+        assert a.counters() == b.counters()
