@@ -28,9 +28,8 @@ constexpr int kShortSlots = 4;  // entries per lane of lists no longer than 32 *
 // before it are rejected, those after it are evaluated again from the changed
 // configuration.  Step s belongs to wave s mod kWaves, so a step's lists are
 // in registers a round before it can be evaluated.
-// SHORT: packed lists of at most 32 * kShortSlots entries, half a wave each;
-// otherwise chunked lists, PF chunks per lane held ahead and the rest read in
-// the step.
+// SHORT: packed lists of at most 32 * PF entries, half a wave each; otherwise
+// chunked lists of at most PF chunks per lane.
 template <typename R, int BLOCK, bool SHORT, int PF>
 __global__ __launch_bounds__(BLOCK) void k_sweep_ahead(DevPtrs<R> P, ShapeInfo sh, const ItemDev* items, int max_N,
                                                        int n_sweeps) {
@@ -67,8 +66,8 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_ahead(DevPtrs<R> P, ShapeInfo s
     const int64_t sweep0 = P.counters->sweeps_done;
 
     // this wave's lists
-    uint32_t sv[kShortSlots];
-    R sj[kShortSlots];
+    uint32_t sv[PF];
+    R sj[PF];
     ChunkRegs<R, PF> rj, rk;
     auto take_step = [&](int s) {
         if (s >= steps) return;
@@ -77,10 +76,11 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_ahead(DevPtrs<R> P, ShapeInfo s
             const int l = lane < 32 ? j : k;
             const uint32_t b = lb[l], e = lb[l + 1];
 #pragma unroll
-            for (int i = 0; i < kShortSlots; ++i) {
+            for (int i = 0; i < PF; ++i) {
                 const uint32_t x = b + (uint32_t)((lane & 31) + 32 * i);
                 sv[i] = P.idx[x < e ? x : lb[0]];
-                sj[i] = x < e ? P.J[x] : (R)0;
+                const R J = P.J[x < e ? x : lb[0]];
+                sj[i] = x < e ? J : (R)0;
             }
         } else {
             chunk_prefetch<R, PF>(P, lb, j, lane, 64, rj);
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_ahead(DevPtrs<R> P, ShapeInfo s
                 const int j = d.jk & 0xffff, k = d.jk >> 16;
                 const R2<R> ajo = a[j], ako = a[k];
                 const R uj = ajo.x * ajo.x + ajo.y * ajo.y, uk = ako.x * ako.x + ako.y * ako.y;
-                const R K = pair_radius<R, SHORT>(uj, uk, sh.rho);
+                const R K = pair_radius<R, SHORT && PF == kShortSlots>(uj, uk, sh.rho);
                 const R2<R> ajn = mk2<R>(K * d.cj * d.ejr, K * d.cj * d.eji);
                 const R2<R> akn = mk2<R>(K * d.sk * d.ekr, K * d.sk * d.eki);
                 wave_sync();
@@ -115,20 +115,15 @@ __global__ __launch_bounds__(BLOCK) void k_sweep_ahead(DevPtrs<R> P, ShapeInfo s
                 if constexpr (SHORT) {
                     R fr = 0, fi = 0;
 #pragma unroll
-                    for (int i = 0; i < kShortSlots; ++i) field_term<R>(sv[i], sj[i], a, fr, fi);
+                    for (int i = 0; i < PF; ++i) field_term<R>(sv[i], sj[i], a, fr, fi);
                     fr = row_sum(fr);
                     fi = row_sum(fi);
                     Fj = mk2<R>(read_lane(fr, 0) + read_lane(fr, 16), read_lane(fi, 0) + read_lane(fi, 16));
                     Fk = mk2<R>(read_lane(fr, 32) + read_lane(fr, 48), read_lane(fi, 32) + read_lane(fi, 48));
                 } else {
-                    const typename J4<R>::T* Jv = reinterpret_cast<const typename J4<R>::T*>(P.cJ);
                     R jr = 0, ji = 0, kr = 0, ki = 0;
                     chunk_consume<R, PF>(rj, a, jr, ji);
                     chunk_consume<R, PF>(rk, a, kr, ki);
-                    for (uint32_t q = lb[j] + lane + 64 * PF; q < lb[j + 1]; q += 64)
-                        chunk_term<R>(P.cx[q], P.cyz[q], Jv[q], a, jr, ji);
-                    for (uint32_t q = lb[k] + lane + 64 * PF; q < lb[k + 1]; q += 64)
-                        chunk_term<R>(P.cx[q], P.cyz[q], Jv[q], a, kr, ki);
                     Fj = mk2<R>(wave_sum(jr), wave_sum(ji));
                     Fk = mk2<R>(wave_sum(kr), wave_sum(ki));
                 }
@@ -197,11 +192,13 @@ hipError_t ahead_b(const DevPtrs<R>& P, const ShapeInfo& sh, const AheadLaunch& 
 template <typename R>
 hipError_t ahead_t(const DevPtrs<R>& P, const ShapeInfo& sh, const AheadLaunch& L, int n_sweeps, hipStream_t st) {
     if (sh.layout != kLayoutChunked) {
-        if (L.block == 1024) return ahead_b<R, 1024, true, 1>(P, sh, L, n_sweeps, st);
-        if (L.block == 512) return ahead_b<R, 512, true, 1>(P, sh, L, n_sweeps, st);
-        return ahead_b<R, 256, true, 1>(P, sh, L, n_sweeps, st);
+        if (L.slots > 12) return ahead_b<R, 512, true, 16>(P, sh, L, n_sweeps, st);
+        if (L.slots > 8) return ahead_b<R, 512, true, 12>(P, sh, L, n_sweeps, st);
+        if (L.slots > kShortSlots) return ahead_b<R, 512, true, 8>(P, sh, L, n_sweeps, st);
+        if (L.block == 1024) return ahead_b<R, 1024, true, kShortSlots>(P, sh, L, n_sweeps, st);
+        if (L.block == 512) return ahead_b<R, 512, true, kShortSlots>(P, sh, L, n_sweeps, st);
+        return ahead_b<R, 256, true, kShortSlots>(P, sh, L, n_sweeps, st);
     }
-    if (L.chunks <= 1) return ahead_b<R, 512, false, 1>(P, sh, L, n_sweeps, st);
     if (L.chunks <= 2) return ahead_b<R, 512, false, 2>(P, sh, L, n_sweeps, st);
     if (L.chunks <= 4) return ahead_b<R, 512, false, 4>(P, sh, L, n_sweeps, st);
     return ahead_b<R, 512, false, 6>(P, sh, L, n_sweeps, st);

@@ -11,6 +11,7 @@ struct AheadLaunch {
     int n_items;
     int max_N;
     int block;   // packed lists: threads per workgroup
+    int slots;   // packed lists: entries per lane, half a wave per list
     int chunks;  // chunked lists: chunks per lane of the longest list
 };
 

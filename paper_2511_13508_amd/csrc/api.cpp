@@ -903,13 +903,20 @@ hipError_t build_energy(rlpt_ctx* c, const rlpt_graph* const* g, unsigned char* 
     return e;
 }
 
-// short lists and few copies: several steps of a copy at a time (ahead.hip).
-// A copy takes 4 to 16 waves, so it pays while the chip has room for every
-// copy's at once; past that the waves of one copy only delay the others (us
-// per sweep, one wave per copy -> several, on an MI355X: N = 1024 of mean
-// degree 32, 320 copies 412 -> 191, 640 416 -> 285, 1280 527 -> 525; N = 16,
-// 16 copies 19 -> 16, 640 18 -> 21).  Chunked lists: up to two chunks per lane
-// (N = 32, 8 copies 28 -> 19, 384 30 -> 25, 1024 32 -> 37; N = 48 45 -> 47).
+// few copies: several steps of a copy at a time (ahead.hip).  A copy takes 4 to
+// 16 waves, so it pays while the chip has room for every copy's at once; past
+// that the waves of one copy only delay the others.  Us per sweep, one step at
+// a time -> several, on an MI355X:
+// packed lists of up to 16 entries per lane: N = 1024 of mean degree 32, 320
+// copies 412 -> 191, 640 416 -> 285, 1280 527 -> 525; N = 16, 16 copies 18 -> 14,
+// 384 18 -> 16, 640 18 -> 21; N = 24, 8 copies 29 -> 13, 384 31 -> 18 (FP64 57 ->
+// 23);
+// chunked lists of up to 6 chunks per lane; with more than 3 a step's LDS reads
+// by one wave are its time in FP32, not the reductions and barriers it saves,
+// unless the chip is nearly empty: FP32 N = 32, 8 copies 28 -> 18, 384 30 -> 24,
+// 512 29 -> 32; N = 40, 8 copies 33 -> 22, 384 34 -> 31; N = 48, 8 copies 38 -> 28,
+// 128 41 -> 40, 384 45 -> 47; N = 64 55 -> 59; FP64 N = 40, 384 copies 73 -> 46; N =
+// 48, 8 copies 48 -> 35, 384 97 -> 61; N = 64 70 -> 73.
 void plan_ahead(rlpt_ctx* c, const ItemDev* items) {
     if (c->sh.cached || c->cfg.block_threads > 0 || c->cfg.copies_per_block > 0) return;
     AheadLaunch L{};
@@ -920,13 +927,14 @@ void plan_ahead(rlpt_ctx* c, const ItemDev* items) {
         for (uint32_t n : c->max_chunks) longest = std::max(longest, n);
         L.chunks = (int)(longest + 63) / 64;
         L.block = 512;
-        if (L.chunks > 2) return;
-    } else if (c->sh.short_lists) {
-        L.block = 1024;
+        if (L.chunks > 6) return;
+    } else {
+        L.slots = (int)(c->longest_list + 31) / 32;
+        if (L.slots > 16) return;
+        L.block = c->sh.short_lists ? 1024 : 512;
         // no wave without a step: the window is half the waves
         while (L.block > 256 && L.block / 128 > c->max_N / 2) L.block /= 2;
-    } else {
-        return;
+        if (!c->sh.short_lists && L.block < 512) return;
     }
     while (L.block > 256 && ahead_lds_bytes(c->cfg.precision, L.block, c->max_N) > 160 * 1024) L.block /= 2;
     const size_t lds = ahead_lds_bytes(c->cfg.precision, L.block, c->max_N);
@@ -936,7 +944,8 @@ void plan_ahead(rlpt_ctx* c, const ItemDev* items) {
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
         cus = 256;
     // a long sweep gains more than a short one's fixed part costs
-    const int per_cu2 = L.chunks > 0 ? 1 : L.max_N > 128 ? 6 : 3;  // copies per two compute units
+    const bool light = L.chunks <= 3 || c->cfg.precision == RLPT_FP64;
+    const int per_cu2 = L.chunks > 0 ? (light ? 3 : 1) : L.max_N > 128 ? 6 : 3;  // copies per two compute units
     if (c->n_copies > per_cu2 * cus / 2) return;
     L.n_items = c->n_copies;
     c->ahead = L;
@@ -1082,7 +1091,7 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
     c->cfg.rho = c->sh.rho;
     // short lists (sparse graphs): every padded list fits in one wave's registers
     if (layout == kLayoutPacked && !c->sh.cached) {
-        uint32_t longest = 0;
+        uint32_t& longest = c->longest_list;
         for (int s = 0; s < n_graphs; ++s)
             for (int l = 0; l < graphs[s]->N; ++l)
                 longest = std::max(longest, graphs[s]->mode_start[l + 1] - graphs[s]->mode_start[l]);

@@ -23,6 +23,7 @@ struct rlpt_ctx {
     int S = 0, T = 0, reps = 0, Rc = 0, n_copies = 0, max_N = 0;
     std::vector<int> N;
     std::vector<uint32_t> max_chunks;  // longest chunked list of each sample (0 in the packed layout)
+    uint32_t longest_list = 0;         // packed layout: entries of the longest list
     std::vector<double> temps;
     std::vector<SampleDev> samples;
     std::vector<ItemDev> items;

@@ -159,18 +159,21 @@ struct StepDraw {
 };
 
 // the step's two distinct modes j | k << 16
-__device__ inline int draw_pair(uint64_t seed, int64_t pair_stream, int64_t sweep, int step, int N) {
-    const Philox4 wp = philox4x64((uint64_t)step, (uint64_t)sweep, (uint64_t)pair_stream, 0, seed, kTagPair);
+__device__ __forceinline__ int pair_of(const Philox4& wp, int N) {
     const int j = index_below(wp.v[0], N);
     int k = index_below(wp.v[1], N - 1);
     k += (k >= j) ? 1 : 0;
     return j | (k << 16);
 }
 
+__device__ inline int draw_pair(uint64_t seed, int64_t pair_stream, int64_t sweep, int step, int N) {
+    return pair_of(philox4x64((uint64_t)step, (uint64_t)sweep, (uint64_t)pair_stream, 0, seed, kTagPair), N);
+}
+
 // part of the move's draws: 1 the phase of a_j, 2 the phase of a_k, 3 the
 // magnitudes and the acceptance uniform
 template <typename R>
-__device__ inline void move_part(const Philox4& wm, int rho, int part, StepDraw<R>& d) {
+__device__ __forceinline__ void move_part(const Philox4& wm, int rho, int part, StepDraw<R>& d) {
     const R two_pi = (R)2 * pi_v<R>();
     R s, c;
     if (part == 1) {
@@ -209,11 +212,13 @@ __device__ inline void draw_part(uint64_t seed, int64_t copy_id, int64_t sweep, 
 template <typename R>
 __device__ inline StepDraw<R> draw_step(uint64_t seed, int64_t pair_stream, int64_t copy_id, int64_t sweep,
                                         int step, int N, int rho) {
-    StepDraw<R> d;
-    d.jk = draw_pair(seed, pair_stream, sweep, step, N);
+    const Philox4 wp = philox4x64((uint64_t)step, (uint64_t)sweep, (uint64_t)pair_stream, 0, seed, kTagPair);
     const Philox4 wm = draw_move(seed, copy_id, sweep, step);
-#pragma unroll
-    for (int part = 1; part <= 3; ++part) move_part<R>(wm, rho, part, d);
+    StepDraw<R> d;
+    d.jk = pair_of(wp, N);
+    move_part<R>(wm, rho, 1, d);
+    move_part<R>(wm, rho, 2, d);
+    move_part<R>(wm, rho, 3, d);
     return d;
 }
 

@@ -60,3 +60,21 @@ def test_longest_list_of_the_short_sweep():
         # the same decisions; energies differ by the order of FP64 sums of ~100 terms
         assert np.allclose(ctxs[0].get_state(), ctxs[1].get_state(), rtol=0, atol=1e-12), z
         assert np.allclose(ctxs[0].energies()[0], ctxs[1].energies()[0], rtol=1e-11, atol=1e-11), z
+
+
+@pytest.mark.parametrize("N,T,reps,precision", [(40, 3, 1, rlpt.FP64), (48, 4, 2, rlpt.FP64), (56, 3, 1, rlpt.FP64),
+                                                (40, 6, 2, rlpt.FP32), (48, 5, 1, rlpt.FP32), (56, 4, 2, rlpt.FP32)])
+def test_ahead_three_to_six_chunks(oracle, N, T, reps, precision):
+    if precision == rlpt.FP64:
+        compare_fp64(*run_both(oracle, [N], 0, T, reps, 24, precision=precision, resync_interval=12))
+    else:
+        compare_fp32(*run_both(oracle, [N, N - 3], 0, T, reps, 4, precision=precision))
+
+
+@pytest.mark.parametrize("Ns,precision", [([19], rlpt.FP64), ([24, 21], rlpt.FP64), ([28], rlpt.FP64), ([31], rlpt.FP64),
+                                          ([20, 30], rlpt.FP32), ([26], rlpt.FP32)])
+def test_ahead_five_to_sixteen_entries(oracle, Ns, precision):
+    if precision == rlpt.FP64:
+        compare_fp64(*run_both(oracle, Ns, 0, 5, 2, 24, precision=precision, resync_interval=12))
+    else:
+        compare_fp32(*run_both(oracle, Ns, 0, 5, 2, 4, precision=precision))
