@@ -129,7 +129,11 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(DevPtrs<R> P, ShapeInfo sh, int
     const SampleDev sd = P.samples[it.sample];
     const int N = sd.N, steps = sd.n_steps;
     const int wpc = kWaves / it.n_copies;  // waves per copy
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // a scalar wave index saves FP64 instances the vector registers that keep a
+    // second workgroup off the compute unit (720 copies, us per sweep: N = 24 56
+    // -> 36, 28 65 -> 42, 80 387 -> 376); the others only lose by it (N = 64 54 -> 56)
+    const int lane = threadIdx.x & 63;
+    const int wave = sizeof(R) == 8 && !SPLIT ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
     const int g = wave / wpc;              // copy group of this wave
     const bool active = g < it.n_copies;
     const int gw = wave - g * wpc;         // wave index inside the group
