@@ -11,17 +11,20 @@ recomputation -- every part of the path.  Inputs are synthetic and already
 resident in HBM when timing starts.
 
 Prints one JSON line.  ``value`` = mode-updates/s (N mode-updates per copy
-per sweep) over the timed steps.  ``roofline`` describes the sweep kernel:
-``achieved`` = algorithmic bytes per launch (every list entry a step
-streams: 6.25 B in the chunked layout, 25 B per chunk of 4 entries sharing
-their partner mode; 8 B in the packed one) over its mean duration measured
-with HIP events on the context's stream; ``traffic`` = the fabric bytes per
-launch from the committed rocprofv3 counters of this kernel source;
+per sweep) over the timed steps.  ``roofline`` describes the sweep: for the
+pair-space sweep (the default tile) ``achieved`` = the bytes its method asks
+of memory per sweep (the banded couplings once per 16 copies, and for every
+accepted update the half of the two sources' per-target lists, 6 B per entry,
+that later steps still need) over its mean duration measured with HIP events
+on the context's stream; with an explicit launch tile, the list entries that
+the list-streaming sweep reads (6.25 B in the chunked layout, 8 B in the
+packed one).  ``traffic`` = the fabric bytes per sweep from the committed
+rocprofv3 counters of this kernel source;
 ``frac`` = traffic per second over the published 8 TB/s HBM peak, and
 ``peak`` = that peak scaled by algorithmic / fabric bytes, so that
 achieved / peak = frac (fabric bytes include Infinity-Cache hits: the HBM
-share is at most frac).  The list-stream probe (rlpt_stream_lists: the
-sweep's grid and reads with no arithmetic) is timed beside it.
+share is at most frac).  The list-stream probe (rlpt_stream_lists: the reads
+of a sweep that streams every list, with no arithmetic) is timed beside it.
 ``cpu_baseline`` times the CPU FP64 oracle on a bounded slice of the same
 workload (sample 0, all 80 copies, whole sweeps for ~10 s).
 """
@@ -41,12 +44,13 @@ sys.path.insert(0, ROOT)
 
 SEED_BASE = 2511135080 + 400  # disorder seed of sample mu: SEED_BASE + mu
 HBM_PEAK_GBS = 8000.0
-LDS_PEAK_GBS = 128 * 256 * 2.4  # 128 B per clock per CU, 256 CUs, 2.4 GHz
 METRIC = "mode-updates/s + τ_int-corrected sweeps/s (learned vs plain PT), N=256, 1 GPU"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_n256_traffic.json")
 BATCHED_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "batched_traffic.json")
-# the sweep kernel and the host code that lays out its launch (tiles, item order)
-KERNEL_SRC = [os.path.join(ROOT, "paper_2511_13508_amd", "csrc", f) for f in ("kernels.hip", "api.cpp")]
+# the sweep kernels and the host code that lays out their launches (tables, tiles, item order)
+KERNEL_SRC = [os.path.join(ROOT, "paper_2511_13508_amd", "csrc", f)
+              for f in ("kernels.hip", "pairs.hip", "pairs.hpp", "ahead.hip", "device.hpp", "lists.hpp", "api.cpp")]
+PAIR_MODES = 88  # dense FP32 samples from here on take the pair-space sweep
 
 
 def log(msg):
@@ -74,6 +78,16 @@ def traffic_for_current_kernel(launch_bytes_alg: float, path: str = TRAFFIC_FILE
     return t.get("hbm_bytes_per_launch")
 
 
+def pair_sweep_bytes(infos, N, copies, accepted):
+    """Bytes the pair-space sweep asks of memory per sweep of `copies` copies of
+    each sample with `accepted` accepted updates in all: the couplings of the
+    band (both triangles, FP32) once per 16 copies, and per accepted update
+    half of the two sources' lists (12 c / N entries of 6 B each)."""
+    band = sum(2 * inf["n_terms"] * 4 * -(-copies // 16) for inf in infos)
+    per_source = sum(12 * inf["n_terms"] / N for inf in infos) / len(infos) * 6
+    return band + accepted * per_source
+
+
 PROFILE_CMDS = {
     "kt": "rocprofv3 --kernel-trace --stats -f csv -d {OUT}/kt -o kt -- python bench.py --steps 20 --warmup 5 "
           "--tau-sweeps 0 --no-cpu-baseline --no-cached",
@@ -87,13 +101,14 @@ PROFILE_CMDS = {
              "SQ_BUSY_CYCLES SQ_INSTS_SALU --kernel-include-regex 'k_sweep<' -f csv -d {OUT}/pmc64 -o pmc -- "
              "python bench.py --workload n64",
     "sq256": "rocprofv3 --pmc SQ_WAVES SQ_INSTS_VALU SQ_INSTS_LDS SQ_LDS_BANK_CONFLICT SQ_BUSY_CYCLES SQ_WAVE_CYCLES "
-             "SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_LDS GRBM_GUI_ACTIVE --kernel-include-regex 'k_sweep<|k_stream_lists' "
+             "SQ_ACTIVE_INST_VALU SQ_ACTIVE_INST_LDS GRBM_GUI_ACTIVE --kernel-include-regex 'k_sweep<|k_pair_|k_stream_lists' "
              "-f csv -d {OUT}/sq256 -o pmc -- python bench.py --sweeps-per-step 1 --steps 4 --warmup 2 "
              "--tau-sweeps 0 --no-cpu-baseline --no-cached",
-    "pmc": "rocprofv3 --pmc {C} --kernel-include-regex 'k_sweep<|k_stream_lists' -f csv -d {OUT}/pmc_{C} -o pmc -- "
-           "python bench.py --sweeps-per-step 1 --steps 4 --warmup 2 --tau-sweeps 0 --no-cpu-baseline --no-cached",
+    # (as long as the timed run: what the sweep reads follows the acceptance, which falls while the state relaxes)
+    "pmc": "rocprofv3 --pmc {C} --kernel-include-regex 'k_sweep<|k_pair_|k_stream_lists' -f csv -d {OUT}/pmc_{C} -o pmc -- "
+           "python bench.py --steps 20 --warmup 5 --tau-sweeps 0 --no-cpu-baseline --no-cached",
     "cal": "rocprofv3 --pmc {C} -f csv -d {OUT}/cal_{C} -o cal -- python bench.py --copy-calibration",
-    "pmcb": "rocprofv3 --pmc {C} --kernel-include-regex 'k_sweep<' -f csv -d {OUT}/pmcb_{C} -o pmc -- python bench.py "
+    "pmcb": "rocprofv3 --pmc {C} --kernel-include-regex 'k_sweep<|k_pair_' -f csv -d {OUT}/pmcb_{C} -o pmc -- python bench.py "
             "--workload batched --batched-launches-only",
 }
 
@@ -111,19 +126,24 @@ def summarize_profiles(d):
             return list(csv.DictReader(f))
 
     def mean_counter(path, kernel_pred):
-        vals = [float(r["Counter_Value"]) for r in rows(path) if kernel_pred(r["Kernel_Name"])]
-        return sum(vals) / len(vals), len(vals)
+        # per kernel the mean per dispatch, summed over the kernels of a sweep
+        vals = {}
+        for r in rows(path):
+            if kernel_pred(r["Kernel_Name"]):
+                vals.setdefault(r["Kernel_Name"], []).append(float(r["Counter_Value"]))
+        n = max(len(v) for v in vals.values()) if vals else 0
+        return sum(sum(v) for v in vals.values()) / n, n
 
     lines = []
     have_headline = all(os.path.exists(os.path.join(d, x)) for x in ("kt", "pmc_FETCH_SIZE", "pmc_WRITE_SIZE",
                                                                     "cal_FETCH_SIZE", "cal_WRITE_SIZE"))
-    is_sweep = lambda n: "k_sweep<" in n  # noqa: E731
+    is_sweep = lambda n: "k_sweep<" in n or "k_pair_" in n  # noqa: E731
     is_ceiling = lambda n: "k_stream_lists" in n  # noqa: E731
     is_copy = lambda n: "copyBuffer" in n  # noqa: E731
     if have_headline:
         stats = rows(os.path.join(d, "kt", "kt_kernel_stats.csv"))
-        lines = ["# rocprofv3 kernel statistics, headline N=256 workload (8 samples x 40 T x 2 replicas, streaming sweep, "
-                 "per-copy pairs); k_stream_lists is the list-stream ceiling the bench measures beside it",
+        lines = ["# rocprofv3 kernel statistics, headline N=256 workload (8 samples x 40 T x 2 replicas, per-copy "
+                 "pairs); k_stream_lists is the list-stream probe the bench measures beside it",
                  "# command (from the repository root):",
                  "#   " + cmd("kt"), "",
                  f"{'kernel':<60} {'calls':>6} {'avg_us':>10} {'min_us':>10} {'max_us':>10} {'pct':>6}"]
@@ -135,12 +155,12 @@ def summarize_profiles(d):
         for tag, pred in (("k_sweep", is_sweep), ("k_stream_lists", is_ceiling)):
             hit = [r for r in stats if pred(r["Name"])]
             if hit:
-                avg_ns[tag] = float(hit[0]["AverageNs"])
+                avg_ns[tag] = sum(float(r["AverageNs"]) for r in hit)
         cal_f, _ = mean_counter(os.path.join(d, "cal_FETCH_SIZE", "cal_counter_collection.csv"), is_copy)
         cal_w, _ = mean_counter(os.path.join(d, "cal_WRITE_SIZE", "cal_counter_collection.csv"), is_copy)
         copy_bytes = 512 * 1024 * 1024
         f_scale, w_scale = copy_bytes / (cal_f * 1024), copy_bytes / (cal_w * 1024)
-        traffic = {"kernel": "k_sweep<float, 256>", "kernel_source_sha": kernel_sha(),
+        traffic = {"kernel": "k_pair_product, k_pair_reduce, k_pair_decide (sum)", "kernel_source_sha": kernel_sha(),
                    "copy_kernel_fetch_kib": cal_f, "copy_kernel_write_kib": cal_w, "copy_bytes": copy_bytes,
                    "fetch_scale": f_scale, "write_scale": w_scale,
                    "commands": [cmd("pmc", "FETCH_SIZE"), cmd("pmc", "WRITE_SIZE"), cmd("cal", "FETCH_SIZE"),
@@ -173,7 +193,7 @@ def summarize_profiles(d):
         f_scale, w_scale = copy_bytes / (cal_f * 1024), copy_bytes / (cal_w * 1024)
         fetch_kib, nf = mean_counter(os.path.join(d, "pmcb_FETCH_SIZE", "pmc_counter_collection.csv"), is_sweep)
         write_kib, nw = mean_counter(os.path.join(d, "pmcb_WRITE_SIZE", "pmc_counter_collection.csv"), is_sweep)
-        tb = {"kernel": "k_sweep, batched uneven-N launch (built-in tiles)", "kernel_source_sha": kernel_sha(),
+        tb = {"kernel": "k_pair_product, k_pair_decide, k_sweep of the batched uneven-N sweep (sum)", "kernel_source_sha": kernel_sha(),
               "fetch_kib_per_dispatch": fetch_kib, "write_kib_per_dispatch": write_kib, "dispatches": [nf, nw],
               "fetch_scale": f_scale, "write_scale": w_scale,
               "hbm_bytes_per_launch": fetch_kib * 1024 * f_scale + write_kib * 1024 * w_scale,
@@ -184,20 +204,19 @@ def summarize_profiles(d):
     sq = os.path.join(d, "sq256", "pmc_counter_collection.csv")
     if os.path.exists(sq):
         rs = rows(sq)
-        bl = ["# rocprofv3 SQ counters, headline N=256 workload: the sweep kernel and the list-stream ceiling kernel "
-              "(same grid, tile and list reads, no arithmetic), mean per dispatch",
+        bl = ["# rocprofv3 SQ counters, headline N=256 workload: the sweep's kernels and the list-stream probe, "
+              "mean per dispatch",
               "# command (from the repository root):", "#   " + cmd("sq256"), ""]
         for tag, pred in (("k_sweep", is_sweep), ("k_stream_lists", is_ceiling)):
-            acc = {}
-            for r in rs:
-                if pred(r["Kernel_Name"]):
-                    acc.setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
-            if not acc:
-                continue
-            bl.append(f"# {tag}")
-            for k in sorted(acc):
-                bl.append(f"{k:<24} {sum(acc[k]) / len(acc[k]):>16.1f}   ({len(acc[k])} dispatches)")
-            bl.append("")
+            for name in sorted({r["Kernel_Name"] for r in rs if pred(r["Kernel_Name"])}):
+                acc = {}
+                for r in rs:
+                    if r["Kernel_Name"] == name:
+                        acc.setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
+                bl.append("# " + name.replace("rlpt::(anonymous namespace)::", "").split("(")[0])
+                for k in sorted(acc):
+                    bl.append(f"{k:<24} {sum(acc[k]) / len(acc[k]):>16.1f}   ({len(acc[k])} dispatches)")
+                bl.append("")
         with open(os.path.join(ROOT, "profiles", "sweep_n256_sq_counters.txt"), "w") as f:
             f.write("\n".join(bl) + "\n")
     other = (("kta", "bench_all_kernel_stats.txt",
@@ -313,15 +332,15 @@ def batched(args, short=False):
     bytes_per_sweep = sum(reps * T * inf["deg_sum"] * 6.25 for inf in infos)
 
     if getattr(args, "batched_launches_only", False):
-        # only the mixed launch with built-in tiles, 20 eager sweeps (the counters' run)
+        # only the mixed sweep with built-in tiles, as many eager sweeps as the timed run takes (the counters' run)
         rlpt.tune_clear()
         ctx = rlpt.Context(graphs, temps, **kw)
         ctx.init(1)
-        ctx.sweep(20)
+        ctx.sweep(500)
         torch.cuda.synchronize()
         ctx.check()
         ctx.close()
-        return {"batched_launches_only": 20}
+        return {"batched_launches_only": 500}
 
     def rate(gs, ctx_kw, segments):
         """mode-updates/s of 10-sweep HIP-graph segments, then the sweep kernel's
@@ -374,8 +393,10 @@ def batched(args, short=False):
             per_N[N] = {"copies_per_block": t1_[N], "launch_ms_per_sweep": e["ms_per_sweep"]}
     # roofline of the built-in tiles' launch (the configuration whose fabric bytes are committed)
     traffic_b = traffic_for_current_kernel(bytes_per_sweep, BATCHED_TRAFFIC_FILE)
-    roof_b = {"bound": "hbm", "kernel": "k_sweep (one launch for every N, built-in tiles)", "unit": "GB/s",
-              "algorithmic_bytes_per_launch": bytes_per_sweep, "ms_per_launch": ms0,
+    roof_b = {"bound": "hbm", "unit": "GB/s",
+              "kernel": "pair-space sweep of N >= 88 beside k_sweep of the smaller N (built-in tiles)",
+              "algorithmic_bytes_per_launch": bytes_per_sweep,
+              "bytes": "of a sweep that streams every list; the pair-space sweep asks for fewer", "ms_per_launch": ms0,
               "achieved": bytes_per_sweep / ms0 / 1e6, "hbm_peak_published": HBM_PEAK_GBS,
               "frac_of_hbm_peak": bytes_per_sweep / ms0 / 1e6 / HBM_PEAK_GBS, "traffic": traffic_b,
               "ms_per_launch_tuned_tiles": ms1,
@@ -435,6 +456,8 @@ def cached_fields(args, rlpt, torch, graphs, infos, temps, common, el, n_copies,
     pair_b = sum(inf["pair_entries"] / (N * (N - 1)) * 8.0 for inf in infos) / S  # per step
     gather_b = sum(inf["gather_entries"] for inf in infos) / (S * N) * (idx_b + 4)
     bytes4 = (steps_total * pair_b + accepted * 2 * gather_b) / launches4
+    if N >= PAIR_MODES and N <= 256 and args.block == 0 and args.copies_per_block == 0:
+        bytes4 = args.sweeps / launches4 * pair_sweep_bytes(infos, N, T * reps, accepted / args.sweeps)
     tile4 = ctx.tile()
     acc_T = (o1["acc"] - o0["acc"]).sum(axis=0) / np.maximum((o1["tries"] - o0["tries"]).sum(axis=0), 1)
     ctx.close()
@@ -448,8 +471,8 @@ def cached_fields(args, rlpt, torch, graphs, infos, temps, common, el, n_copies,
         "tile": {"block_threads": int(tile4[0]), "copies_per_block": int(tile4[1][0])},
         "algorithmic_bytes_per_launch": bytes4,
         "achieved_GBs": bytes4 / (kms4 / launches4 * 1e-3) / 1e9,
-        "note": "bytes: per step the (j->k) pair list (8 B/entry), per accepted step the padded gather "
-                "blocks of j and k; the launch is bound by the hottest copies' accepted steps, not by HBM",
+        "note": "dense FP32 contexts from N = 88 on form the fields by the pair-space sweep (bytes as there); otherwise "
+                "bytes: per step the (j->k) pair list (8 B/entry), per accepted step the padded gather blocks of j and k",
     }
     log(f"cached fields: {out['cached_fields']['mode_updates_per_s']:.4g} mode-updates/s "
         f"({out['cached_fields']['speedup_vs_streaming']:.2f}x streaming), acceptance "
@@ -1040,6 +1063,8 @@ def main():
                   measure_start=args.warm_sweeps, measure_interval=1, n_bins=100, series_len=series_len,
                   block_threads=args.block, copies_per_block=args.copies_per_block, list_layout=args.layout)
 
+    accepted = {}  # per timed run: accepted updates per sweep, all copies
+
     def timed(ctx, tag):
         """warm-up, then the timed steps with sweep-kernel events; returns (s, kernel ms, launches)"""
         ctx.init(args.run_seed)
@@ -1047,6 +1072,7 @@ def main():
         ctx.sweep(args.warm_sweeps)
         ctx.check()
         torch.cuda.synchronize()
+        before = ctx.observables()["acc"].sum()
         ctx.sweep_timing(True)
         log(f"{tag}: timing {args.steps} steps ({args.sweeps} sweeps)")
         t0 = time.perf_counter()
@@ -1057,6 +1083,7 @@ def main():
         ctx.check()
         kms, launches = ctx.sweep_time()
         ctx.sweep_timing(False)
+        accepted[tag] = float(ctx.observables()["acc"].sum() - before) / args.sweeps
         return el, kms, launches
 
     def long_run(ctx, n, tag):
@@ -1093,22 +1120,25 @@ def main():
     el, kms, launches = timed(ctx, "plain")
     n_copies = ctx.n_copies
     value = N * n_copies * args.sweeps / el
-    # algorithmic bytes of one sweep launch (one sweep): every copy streams, per
-    # two-mode step, the lists of j and k; over a sweep of N/2 uniform pairs that
+    in_pairs = N >= PAIR_MODES and N <= 256 and args.block == 0 and args.copies_per_block == 0
+    # list-streaming sweep (small N or an explicit tile): every copy streams, per two-mode step, the lists of j and k; over a sweep of N/2 uniform pairs that
     # is the 4c entries of all lists on average: 8 B per entry in the packed
     # layout, 25 B per 4 entries in the chunked one (padding not counted)
     chunked = args.layout == 2 or (args.layout == 0 and N <= 256 and N >= 32)
     per_entry = 6.25 if chunked else 8.0
     sweeps_per_launch = args.sweeps / launches
     entries_per_launch = sweeps_per_launch * sum(reps * T * inf["deg_sum"] for inf in infos)
-    bytes_per_launch = entries_per_launch * per_entry
+    list_bytes = entries_per_launch * per_entry  # of a sweep that streams every list
+    bytes_per_launch = (sweeps_per_launch * pair_sweep_bytes(infos, N, reps * T, accepted["plain"]) if in_pairs
+                        else list_bytes)
     t_launch = kms / launches * 1e-3
     achieved = bytes_per_launch / t_launch / 1e9
     traffic = traffic_for_current_kernel(bytes_per_launch)
     log(f"{value:.4g} mode-updates/s; sweep kernel {kms / launches:.3f} ms/launch, {achieved:.0f} GB/s algorithmic")
-    roof = {"bound": "hbm", "achieved": achieved, "unit": "GB/s", "kernel": "k_sweep",
-            "ms_per_launch": kms / launches, "bytes_per_entry": per_entry,
-            "entries_per_launch": entries_per_launch, "algorithmic_bytes_per_launch": bytes_per_launch,
+    roof = {"bound": "hbm", "achieved": achieved, "unit": "GB/s",
+            "kernel": "k_pair_product + k_pair_reduce + k_pair_decide" if in_pairs else "k_sweep",
+            "ms_per_launch": kms / launches, "accepted_per_sweep": accepted["plain"],
+            "algorithmic_bytes_per_launch": bytes_per_launch, "list_bytes_of_a_streaming_sweep": list_bytes,
             "hbm_peak_published": HBM_PEAK_GBS, "frac_of_hbm_peak": achieved / HBM_PEAK_GBS, "traffic": traffic,
             "traffic_over_algorithmic": traffic / bytes_per_launch if traffic else None,
             "traffic_GBps": traffic / t_launch / 1e9 if traffic else None}
@@ -1134,15 +1164,16 @@ def main():
             beside.append(kr / nr)
         ms_probe = float(np.mean(probe))
         roof["list_stream_probe"] = {
-            "ms_per_launch": ms_probe, "GBps": bytes_per_launch / (ms_probe * 1e-3) / 1e9,
+            "ms_per_launch": ms_probe, "GBps": list_bytes / (ms_probe * 1e-3) / 1e9,
             "rounds_ms": [round(x, 4) for x in probe], "sweep_beside_ms": [round(x, 4) for x in beside],
             "sweep_over_probe_time": float(np.mean(beside)) / ms_probe,
-            "what": "rlpt_stream_lists: the sweep's grid, tile, LDS footprint, barriers and list reads with no "
-                    "arithmetic; the sweep takes within a few per cent of its time (box to box 0.96-1.04)"}
+            "what": "rlpt_stream_lists: the reads alone of a sweep that streams every list (grid, tile, barriers, no "
+                    "arithmetic), which the pair-space sweep does not do"}
         log(f"list-stream probe {ms_probe:.3f} ms/launch; sweep beside it {np.mean(beside):.3f} ms")
         if "peak" not in roof:
-            roof.update({"peak": bytes_per_launch / (ms_probe * 1e-3) / 1e9, "frac": ms_probe / t_launch,
-                         "peak_kind": "measured list-stream probe (no committed counters for this kernel source)"})
+            if not in_pairs:
+                roof.update({"peak": list_bytes / (ms_probe * 1e-3) / 1e9, "frac": ms_probe * 1e-3 / t_launch,
+                             "peak_kind": "measured list-stream probe (no committed counters for this kernel source)"})
     if "peak" not in roof:
         roof.update({"peak": HBM_PEAK_GBS, "frac": achieved / HBM_PEAK_GBS, "peak_kind": "published HBM peak"})
     sweeps_per_s = args.sweeps / el
@@ -1205,16 +1236,13 @@ def main():
             el2, kms2, launches2 = timed(ctx, "shared pairs")
             tau["shared_pairs"], tE2, _ = tau_block(ctx, args.sweeps / el2, t_learn, args.tau_sweeps, "shared pairs")
             tau["shared_pairs"]["mode_updates_per_s"] = N * n_copies * args.sweeps / el2
-            if chunked:
-                # the copies of a sample share their lists through L2, so the binding roof is the LDS
-                # gathers: per chunk of 4 entries one partner and 8 pair amplitudes, 9 x 8 B = 18 B per
-                # entry; LDS peak = 128 B per clock per CU x 256 CUs x 2.4 GHz
-                t2 = kms2 / launches2 * 1e-3
-                lds_gbs = entries_per_launch * 18.0 / t2 / 1e9
+            t2 = kms2 / launches2 * 1e-3
+            b2 = args.sweeps / launches2 * pair_sweep_bytes(infos, N, reps * T, accepted["shared pairs"])
+            tau["shared_pairs"]["ms_per_launch"] = kms2 / launches2
+            if in_pairs:
                 tau["shared_pairs"]["roofline"] = {
-                    "bound": "lds", "achieved": lds_gbs, "peak": LDS_PEAK_GBS, "unit": "GB/s",
-                    "frac": lds_gbs / LDS_PEAK_GBS, "bytes_per_entry": 18.0, "ms_per_launch": kms2 / launches2,
-                    "list_GBps_algorithmic": entries_per_launch * per_entry / t2 / 1e9}
+                    "bound": "hbm", "achieved": b2 / t2 / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                    "frac": b2 / t2 / 1e9 / HBM_PEAK_GBS, "algorithmic_bytes_per_launch": b2}
             tau["shared_vs_plain_eff"] = eff_ratio(tE2, tau_plain_E, args.sweeps / el2, sweeps_per_s)
             ctx.close()
         # ------------------------------------------------------------ learned global moves

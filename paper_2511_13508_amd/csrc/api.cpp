@@ -265,7 +265,7 @@ size_t pair_copies(const rlpt_config& cfg, int N) {
 // the caller names a launch tile (a tile belongs to the list-streaming
 // kernels).  Below, a sweep from the lists is as fast or faster (us per sweep,
 // lists -> pairs, 64 copies of 8 samples on an MI355X: N = 64 70 -> 67, 96 158
-// -> 115, 128 261 -> 186, 200 972 -> 502).  The tables take about 5 times the
+// -> 115, 128 261 -> 186, 200 972 -> 502).  The tables take about 4 times the
 // lists' memory (the per-pair entries), so past kPairTableBytes the context
 // keeps to the lists.
 // Contexts in cached-field mode take it when it serves every sample (us per
@@ -284,7 +284,7 @@ std::vector<int> pair_samples(const rlpt_config& cfg, const rlpt_graph* const* g
         if (g[i]->N < kPairModes || g[i]->pair_modes.empty()) continue;
         served.push_back(i);
         bytes += g[i]->band_entries * 4 + g[i]->pair_modes.size() * pair_copies(cfg, g[i]->N) * 8 +
-                 kListUnit * (size_t)g[i]->pair_first.back() * sizeof(PairEntry);
+                 kUnitBytes * (size_t)g[i]->pair_first.back();
     }
     if (bytes > kPairTableBytes) served.clear();
     if (cfg.field_mode == RLPT_FIELDS_CACHED && (int)served.size() < S) served.clear();
@@ -417,7 +417,7 @@ Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layo
             tiles += g[i]->pair_tile.size() / 2;
             band += g[i]->band_entries;
             prod += g[i]->pair_modes.size() * pair_copies(cfg, g[i]->N);
-            list += kListUnit * (size_t)g[i]->pair_first.back();
+            list += kUnitBytes * (size_t)g[i]->pair_first.back();
         }
         r.p_samples = L.take(S * sizeof(PairSample));
         r.p_rest = L.take(copies * sizeof(ItemDev));
@@ -431,7 +431,7 @@ Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layo
         r.p_order = L.take(copies * max_N * 2);
         r.p_after = L.take(copies * (max_N / 2 + 1) * 2);
         r.p_prod = L.take(prod * 8);
-        r.p_list = L.take(list * sizeof(PairEntry));
+        r.p_list = L.take(list);
         r.p_band = L.take((band + kBandSlack) * 4);
         r.p_end = L.off;
     }
@@ -499,7 +499,7 @@ void fill_pair_ptrs(PairDev& Q, unsigned char* b, const Regions& r, int max_N) {
     Q.first = reinterpret_cast<const uint32_t*>(b + r.p_first);
     Q.band = reinterpret_cast<float*>(b + r.p_band);
     Q.desc = reinterpret_cast<uint16_t*>(b + r.p_desc);
-    Q.list = reinterpret_cast<PairEntry*>(b + r.p_list);
+    Q.list = b + r.p_list;
     Q.prod = reinterpret_cast<float2*>(b + r.p_prod);
     Q.fields = reinterpret_cast<float2*>(b + r.p_fields);
     Q.draws = b + r.p_draws;
@@ -792,7 +792,7 @@ hipError_t build_pairs(rlpt_ctx* c, const rlpt_graph* const* g, const std::vecto
         at.band_base += (int64_t)q->band_entries;
         at.prod_base += (int64_t)(q->pair_modes.size() * pair_copies(c->cfg, q->N));
         at.desc_base += (int64_t)q->N * (q->N + 1);
-        at.list_base += kListUnit * (int64_t)q->pair_first.back();
+        at.list_base += kUnitBytes * (int64_t)q->pair_first.back();
         pm.insert(pm.end(), q->pair_modes.begin(), q->pair_modes.end());
         rank.insert(rank.end(), q->pair_rank.begin(), q->pair_rank.end());
         tile.insert(tile.end(), q->pair_tile.begin(), q->pair_tile.end());

@@ -2,8 +2,10 @@
 // (local fields + two-mode Metropolis update), replica exchange, FP64 energy
 // recomputation, observables, and the test hooks that reuse the sweep's field
 // code.  Method: Benedetti & Leuzzi, arXiv 2511.13508, sec. III.A.
+// Dense FP32 samples from 88 modes on are swept by pairs.hip, few copies of
+// small samples by ahead.hip, energies of dense samples summed by energy.hip.
 //
-// Sweep kernel layout
+// List-streaming sweep kernel layout
 //   * one workgroup runs an "item": n_copies copies of one disorder sample;
 //     each copy is served by waves_per_copy = (block/64)/n_copies waves;
 //   * a copy's amplitudes live in LDS for the whole launch;

@@ -106,9 +106,13 @@ __global__ __launch_bounds__(256) void k_list_fill(DevPtrs<float> P, PairDev Q) 
         d[j] = (uint16_t)(at | n0 << kStartBits);
         if (j == N - 1) d[N] = (uint16_t)(at + 2 * n0 + n1);
     }
-    PairEntry* list0 = Q.list + ps.list_base + kListUnit * (size_t)(Q.first[sd.mode_base + l] + at);
-    PairEntry* list1 = list0 + 32 * n0;
-    constexpr uint32_t kAmp = sizeof(float2);
+    unsigned char* list = Q.list + ps.list_base + (size_t)kUnitBytes * (Q.first[sd.mode_base + l] + at);
+    uint32_t next0 = 0, next1 = 32 * n0;  // the padding of both roles holds zeros already
+    const auto put = [&](uint32_t e, uint32_t p, float J) {
+        unsigned char* unit = list + (size_t)kUnitBytes * (e / kListUnit);
+        reinterpret_cast<uint16_t*>(unit)[e % kListUnit] = (uint16_t)p;
+        reinterpret_cast<float*>(unit + kUnitJ)[e % kListUnit] = J;
+    };
     for (uint32_t t0 = beg; t0 < end; t0 += kListTile) {
         __syncthreads();
         stage(t0);
@@ -119,15 +123,10 @@ __global__ __launch_bounds__(256) void k_list_fill(DevPtrs<float> P, PairDev Q) 
                 const float J = tj[i];
                 if (J == 0.0f) continue;
                 const uint32_t x = v & 255u, y = (v >> 8) & 255u, z = v >> 16;
-                PairEntry en{};
-                en.J = J;
-                if (x == (uint32_t)j) {  // l is the target's partner
-                    en.p = y * kAmp | z * kAmp << 16;
-                    *list0++ = en;
-                } else if (y == (uint32_t)j || z == (uint32_t)j) {  // the target's partner is the other of y and z
-                    en.p = (y == (uint32_t)j ? z : y) * kAmp | x * kAmp << 16;
-                    *list1++ = en;  // the padding of both holds zeros already
-                }
+                if (x == (uint32_t)j)  // l is the target's partner
+                    put(next0++, y | z << 8, J);
+                else if (y == (uint32_t)j || z == (uint32_t)j)  // the target's partner is the other of y and z
+                    put(next1++, (y == (uint32_t)j ? z : y) | x << 8, J);
             }
     }
 }
@@ -192,6 +191,13 @@ __device__ inline void draw_sweep(const PairDev& Q, const ShapeInfo& sh, int sam
 // each product, formed from the amplitudes in LDS, feeds two row tiles.
 // v_mfma_f32_16x16x4_f32: FP32 operands and accumulation.
 // Blocks past the product's draw the copies' sweeps.
+// The FP32 matrix cores bound it (busy 45 % of the time): per 4 columns a wave
+// issues 4 products of 32 cycles and forms its operands from 3 LDS reads, so
+// what else it issues is kept off the vector ALU (scalar tile, immediate
+// offsets) and the loads in flight.  Eight waves share the amplitudes of large
+// N: six waves per SIMD instead of four.  N = 256, 640 copies of 8 samples (the
+// draws included): 166 us as first written, 149 with
+// scalar addresses, 137 with eight waves (68 at the matrix cores' rate).
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <int BLOCK>
@@ -282,7 +288,9 @@ __global__ __launch_bounds__(BLOCK) void k_pair_product(DevPtrs<float> P, PairDe
 }
 
 // Large N: the fields of kCopyTile copies from their banded product, a wave
-// per mode, four pairs of the mode at a time (one row of 16 copies each)
+// per mode, four pairs of the mode at a time (one row of 16 copies each).  The
+// product is read twice (each pair belongs to two modes), 334 MB at N = 256 and
+// 640 copies in 54 us: bound by that stream, 6.2 TB/s past the L2s.
 __global__ __launch_bounds__(256) void k_pair_reduce(DevPtrs<float> P, PairDev Q, ShapeInfo sh, int first_item,
                                                      int samples, int groups, int per_wave) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -362,19 +370,35 @@ struct PairList {
     uint32_t at, n0, n1;
 };
 
+__device__ inline uint32_t units_of(uint32_t n) { return n / kListUnit * kUnitBytes; }
+
+struct PairEntry {
+    uint32_t p;  // p1 | p2 << 8
+    float J;
+};
+
 // this lane's share, entries t, t + G, ... of the n at byte offset `at`, K of
-// them, issued together (0 past the end)
-template <int K, int G>
-__device__ inline void list_load(const PairEntry* __restrict__ list, uint32_t at, uint32_t n, uint32_t t,
+// them, issued together (0 past the end).  ALL: lanes past the end read the
+// zero unit, so that no branch separates the loads (us per sweep, N = 256, 640
+// copies 894 -> 872, 160 692 -> 664; N = 128, 1920 copies 399 -> 377); otherwise
+// they are left out, which is faster where most lists end early (N = 96, 640
+// copies 114, not 117)
+template <int K, int G, bool ALL>
+__device__ inline void list_load(const unsigned char* __restrict__ list, uint32_t at, uint32_t n, uint32_t t,
                                  PairEntry* e) {
-    const char* base = reinterpret_cast<const char*>(list);
-    at += t * (uint32_t)sizeof(PairEntry);
+    static_assert(G % kListUnit == 0, "a lane keeps its place in the unit");
+    const uint32_t unit = at + units_of(t), in = t % kListUnit;
+    const uint32_t at_p = unit + 2 * in, at_J = unit + kUnitJ + 4 * in;
 #pragma unroll
     for (int u = 0; u < K; ++u) {
+        const bool in_list = t + (uint32_t)(u * G) < n;
+        constexpr uint32_t kStep = G / kListUnit * kUnitBytes;
         e[u].p = 0;
         e[u].J = 0;
-        if (t + (uint32_t)(u * G) < n)
-            e[u] = *reinterpret_cast<const PairEntry*>(base + (at + (uint32_t)(u * G * sizeof(PairEntry))));
+        if (ALL || in_list) {
+            e[u].p = *reinterpret_cast<const uint16_t*>(list + (in_list ? at_p + u * kStep : 0u));
+            e[u].J = *reinterpret_cast<const float*>(list + (in_list ? at_J + u * kStep : 0u));
+        }
     }
 }
 
@@ -382,11 +406,12 @@ __device__ inline void list_load(const PairEntry* __restrict__ list, uint32_t at
 // loaded; n: entries of the list (a wave stops where no lane has one left)
 template <int K, int G, int ROLE>
 __device__ inline void list_use(const PairEntry* e, uint32_t n, const unsigned char* a, float& sr, float& si) {
+    const float2* amp = reinterpret_cast<const float2*>(a);
 #pragma unroll
     for (int u = 0; u < K; ++u) {
         if (u >= K / 2 && !__any((uint32_t)(u * G) < n)) break;
-        const float2 x = *reinterpret_cast<const float2*>(a + (e[u].p & 0xffffu));
-        const float2 y = *reinterpret_cast<const float2*>(a + (e[u].p >> 16));
+        const float2 x = amp[e[u].p & 0xffu];
+        const float2 y = amp[e[u].p >> 8];
         const float vr = e[u].J * x.x, vi = ROLE == 0 ? e[u].J * x.y : -e[u].J * x.y;
         sr += vr * y.x - vi * y.y;
         si += vr * y.y + vi * y.x;
@@ -396,15 +421,15 @@ __device__ inline void list_use(const PairEntry* e, uint32_t n, const unsigned c
 
 // the entries past the first K0 and K1 per lane (none at the sizes they are chosen for)
 template <int K0, int K1, int G>
-__device__ inline void list_rest(const PairEntry* list, const PairList& p, uint32_t t, const unsigned char* a, float& pr,
+__device__ inline void list_rest(const unsigned char* list, const PairList& p, uint32_t t, const unsigned char* a, float& pr,
                                  float& pi, float& mr, float& mi) {
     PairEntry e[4];
     for (uint32_t i = K0 * G; i < p.n0; i += 4 * G) {
-        list_load<4, G>(list, p.at, p.n0, i + t, e);
+        list_load<4, G, false>(list, p.at, p.n0, i + t, e);
         list_use<4, G, 0>(e, p.n0 - i, a, pr, pi);
     }
     for (uint32_t i = K1 * G; i < p.n1; i += 4 * G) {
-        list_load<4, G>(list, p.at + p.n0 * (uint32_t)sizeof(PairEntry), p.n1, i + t, e);
+        list_load<4, G, false>(list, p.at + units_of(p.n0), p.n1, i + t, e);
         list_use<4, G, 1>(e, p.n1 - i, a, mr, mi);
     }
 }
@@ -432,10 +457,20 @@ __device__ inline float half_sum(float v) {
 // near.  K0, K1: entries of role 0 and 1 per lane of a target's list that are
 // loaded at once.  GATHER: the fields are summed here from the copy's banded
 // product (which the lists' descriptors then replace in LDS).
+// Bound, at large N, by reading the lists of the accepted updates (N = 256, 640
+// copies, 9 % accepted: 5.9 GB past the L2s in 748 us, 7.9 TB/s, at 8 B per
+// entry; 6 B, no branch between the loads: 674 us) and by the hottest copies' chains of them; at small N by
+// the latency of a window and of an accepted update.  The list-streaming sweep
+// read every list of every step instead: 2625 us per sweep there.
+// 32 lanes per step because a wave per step repeats the scalar work 64 times;
+// all of a target's entries are asked for before any is used, as one more
+// access at a time exposes its whole latency (957 us).  N > 136: 768 threads,
+// for the registers that hold two targets' entries (1024 spilled).
 template <int BLOCK, int LANES, int K0, int K1, bool GATHER>
 __global__ __launch_bounds__(BLOCK) void k_pair_decide(DevPtrs<float> P, PairDev Q, ShapeInfo sh, int first_item) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int kGroups = BLOCK / 16, kSlots = BLOCK / 32;
+    constexpr bool kAll = BLOCK != 1024;
     const ItemDev it = Q.items[first_item + blockIdx.x];
     const PairSample ps = Q.samples[it.sample];
     const int N = ps.N, steps = N / 2;
@@ -461,7 +496,7 @@ __global__ __launch_bounds__(BLOCK) void k_pair_decide(DevPtrs<float> P, PairDev
     const SampleDev* sd = P.samples + it.sample;
     const int64_t at = sd->amp_base + (int64_t)(c - it.sample * sh.copies_per_sample) * N;
     float2* amp_g = reinterpret_cast<float2*>(P.amp) + at;
-    const PairEntry* list = Q.list + ps.list_base;
+    const unsigned char* list = Q.list + ps.list_base;
     {
         const float2* F_g = reinterpret_cast<const float2*>(Q.fields) + at;
         const uint32_t* first_g = Q.first + sd->mode_base;
@@ -536,7 +571,7 @@ __global__ __launch_bounds__(BLOCK) void k_pair_decide(DevPtrs<float> P, PairDev
         PairList p;
         p.n0 = (v >> kStartBits) * 2 * kListUnit;
         p.n1 = ((w & ((1u << kStartBits) - 1)) - start) * kListUnit - p.n0;
-        p.at = (first[j] + start) * (uint32_t)(kListUnit * sizeof(PairEntry));
+        p.at = (first[j] + start) * (uint32_t)kUnitBytes;
         return p;
     };
     // step s belongs to half-wave s mod kSlots; its list entries come ahead,
@@ -547,8 +582,8 @@ __global__ __launch_bounds__(BLOCK) void k_pair_decide(DevPtrs<float> P, PairDev
     auto take_step = [&](int s) {
         op = PairList{0, 0, 0};
         if (s < steps) op = find(tab[s].jk & 0xffff, tab[s].jk >> 16);
-        list_load<kOwn0, 32>(list, op.at, op.n0, hl, own0);
-        list_load<kOwn1, 32>(list, op.at + op.n0 * (uint32_t)sizeof(PairEntry), op.n1, hl, own1);
+        list_load<kOwn0, 32, kAll>(list, op.at, op.n0, hl, own0);
+        list_load<kOwn1, 32, kAll>(list, op.at + units_of(op.n0), op.n1, hl, own1);
     };
     __syncthreads();
     int my = tid >> 5, base = 0, par = 0;
@@ -615,8 +650,8 @@ __global__ __launch_bounds__(BLOCK) void k_pair_decide(DevPtrs<float> P, PairDev
             };
             auto fetch = [&](int i, Fetch& f) {
                 f.p = find(src, order[i]);
-                list_load<K0, LANES>(list, f.p.at, f.p.n0, ll, f.ea);
-                list_load<K1, LANES>(list, f.p.at + f.p.n0 * (uint32_t)sizeof(PairEntry), f.p.n1, ll, f.eb);
+                list_load<K0, LANES, kAll>(list, f.p.at, f.p.n0, ll, f.ea);
+                list_load<K1, LANES, kAll>(list, f.p.at + units_of(f.p.n0), f.p.n1, ll, f.eb);
             };
             auto correct = [&](int i, const Fetch& f) {
                 float pr = 0, pi = 0, mr = 0, mi = 0, fr, fi;

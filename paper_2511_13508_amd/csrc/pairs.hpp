@@ -33,18 +33,16 @@ struct PairSample {
     int64_t band_base;     // band values
     int64_t prod_base;     // the banded product of the sample's copies
     int64_t desc_base;     // [N][N + 1] lists of source j by target l: their start in j's units | role-0 units / 2 << 13
-    int64_t list_base;     // the entries in units of 16, source by source; the first unit is zero
+    int64_t list_base;     // byte offset of the lists, source by source; the first unit is zero
 };
 
-// One term holding source j and target l: LDS byte offsets of the amplitudes
-// of its other two members, p1 | p2 << 16, and its coupling.  Role 0 (j is l's
-// partner): F_l changes by J conj(d_j) a_p1 a_p2; role 1: by J conj(a_p1) d_j
-// a_p2.  A list holds its role-0 entries, padded with J = 0 to 32, then its
-// role-1 entries, padded to 16.
-struct PairEntry {
-    uint32_t p;
-    float J;
-};
+// One term holding source j and target l: the other two members p1 | p2 << 8
+// and the coupling J.  Role 0 (j is l's partner): F_l changes by J conj(d_j)
+// a_p1 a_p2; role 1: by J conj(a_p1) d_j a_p2.  A list holds its role-0
+// entries, padded with J = 0 to 32, then its role-1 entries, padded to 16.  The
+// entries of a unit of 16 are stored as 16 p, then 16 J: 6 bytes each, as the
+// sweep of large N is bound by reading them.
+constexpr int kUnitBytes = kListUnit * 6, kUnitJ = kListUnit * 2;  // of a unit; where its J begin
 
 // one step's draws: StepDraw<float>, opaque to the host
 constexpr size_t kPairDrawBytes = 32;
@@ -58,7 +56,7 @@ struct PairDev {
     const uint32_t* first;  // first unit of each source, at the sample's list bounds
     float* band;
     uint16_t* desc;
-    PairEntry* list;
+    unsigned char* list;
     // per sweep: the banded product, the fields it gives, the draws, the
     // targets by latest need and their number per step
     float2* prod;     // [copy][pair] (N <= kGatherModes) or [copy / 16][pair][16]
