@@ -130,8 +130,12 @@ typedef struct rlpt_config {
     int32_t measure_interval; /* ... and n % measure_interval == 0 */
     int32_t n_bins;           /* overlap histogram bins on [-1, 1] */
     int32_t series_len;       /* stored measurements of E (ladder 0) and q_01 per bath */
-    int32_t block_threads;    /* threads per workgroup of the sweep kernel: 0 = tuned, else 64..1024 */
-    int32_t copies_per_block; /* copies per workgroup: 0 = tuned, else divides block_threads/64 */
+    int32_t block_threads;    /* threads per workgroup of the list-streaming sweep: 0 = tuned, else 64..1024 */
+    int32_t copies_per_block; /* copies per workgroup: 0 = tuned, else divides block_threads/64.  With
+                                 either set, every sample is swept by streaming its lists; with both
+                                 0 the library picks a sweep by size (dense FP32 samples of 88 to 256
+                                 modes in pair space, few copies of small samples several steps at a
+                                 time).  The chain is the same. */
     int32_t list_layout;      /* per-mode list layout streamed by the sweep: RLPT_LAYOUT_AUTO,
                                  RLPT_LAYOUT_PACKED (8 B/entry, any N) or RLPT_LAYOUT_CHUNKED
                                  (entries grouped by partner mode in chunks of 4 sharing one
@@ -142,8 +146,9 @@ typedef struct rlpt_config {
     int32_t mlp_components;   /* Gaussian-mixture components, 1..8 (default 4) */
     int32_t mlp_capacity;     /* training pairs stored per network (default 100000) */
     int32_t mlp_batch;        /* training minibatch (default 512) */
-    int32_t field_mode;       /* RLPT_FIELDS_STREAM (default): each two-mode update streams the
-                                 lists of j and k to form F_j, F_k (sec. III.A);
+    int32_t field_mode;       /* RLPT_FIELDS_STREAM (default): no fields are kept between sweeps; the
+                                 list-streaming sweep reads the lists of j and k for each two-mode
+                                 update to form F_j, F_k (sec. III.A);
                                  RLPT_FIELDS_CACHED: every copy keeps all N local fields
                                  (eq. local field) in device memory; an update reads only the
                                  terms holding both j and k (12 entries per term in all) and
@@ -234,7 +239,8 @@ int rlpt_run_graph(rlpt_ctx* ctx, int32_t n_sweeps, int32_t n_segments);
 int rlpt_sweep_timing(rlpt_ctx* ctx, int32_t enable);
 int rlpt_sweep_time_get(rlpt_ctx* ctx, double* total_ms, int64_t* n_launches);
 
-/* Roofline diagnostic of the streaming sweep (sec. III.A "Energy update
+/* Roofline diagnostic of the list-streaming sweep, whether or not this context
+ * uses it (sec. III.A "Energy update
  * parallel computation": each two-mode update streams the lists of j and k).
  * Runs n_launches launches of a kernel with the sweep kernel's grid, items,
  * tile and LDS footprint that reads exactly the list chunks one sweep launch
@@ -288,8 +294,9 @@ int rlpt_autotune(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32
                   const double* temps, void* d_workspace, size_t workspace_bytes, void* hip_stream,
                   int32_t sweeps_per_trial, int32_t* n_trials);
 
-/* The launch tile a context uses: workgroup size and, for sample mu, the
- * copies per workgroup (n_samples entries, may be NULL). */
+/* The list-streaming sweep's launch tile of a context: workgroup size and, for
+ * sample mu, the copies per workgroup (n_samples entries, may be NULL).
+ * Samples that another sweep serves do not use it. */
 int rlpt_tile_of(rlpt_ctx* ctx, int32_t* block_threads, int32_t* copies_per_block);
 
 /* Counters. */

@@ -131,11 +131,15 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(DevPtrs<R> P, ShapeInfo sh, int
     const SampleDev sd = P.samples[it.sample];
     const int N = sd.N, steps = sd.n_steps;
     const int wpc = kWaves / it.n_copies;  // waves per copy
-    // a scalar wave index saves FP64 instances the vector registers that keep a
-    // second workgroup off the compute unit (720 copies, us per sweep: N = 24 56
-    // -> 36, 28 65 -> 42, 80 387 -> 376); the others only lose by it (N = 64 54 -> 56)
+    // a scalar wave index saves the FP64 packed instances of up to 256 threads the
+    // vector registers that keep another workgroup off the compute unit (720
+    // copies, us per sweep: N = 24 56 -> 37, 28 65 -> 42); the others only lose by
+    // it (FP32 N = 64 54 -> 56; FP64 chunked N = 136, 150 copies 370 -> 563; packed
+    // N = 48, 32 copies in 512 threads 59 -> 63)
     const int lane = threadIdx.x & 63;
-    const int wave = sizeof(R) == 8 && !SPLIT ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
+    const int wave = sizeof(R) == 8 && LAYOUT == kLayoutPacked && BLOCK <= 256
+                         ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
+                         : threadIdx.x >> 6;
     const int g = wave / wpc;              // copy group of this wave
     const bool active = g < it.n_copies;
     const int gw = wave - g * wpc;         // wave index inside the group

@@ -457,11 +457,13 @@ __device__ inline float half_sum(float v) {
 // near.  K0, K1: entries of role 0 and 1 per lane of a target's list that are
 // loaded at once.  GATHER: the fields are summed here from the copy's banded
 // product (which the lists' descriptors then replace in LDS).
-// Bound, at large N, by reading the lists of the accepted updates (N = 256, 640
-// copies, 9 % accepted: 5.9 GB past the L2s in 748 us, 7.9 TB/s, at 8 B per
-// entry; 6 B, no branch between the loads: 674 us) and by the hottest copies' chains of them; at small N by
-// the latency of a window and of an accepted update.  The list-streaming sweep
-// read every list of every step instead: 2625 us per sweep there.
+// Bound by the chains of accepted updates of the hottest copies, which accept a
+// third of their steps: at N = 256 some 43 in a row, 13 us each, for two
+// sources' lists to half of the targets (200 KB), two passes of 12 targets in
+// flight.  The chip as a whole reads 1.8 GB past the L2s per sweep of 640
+// equilibrated copies in 663 us (2.7 TB/s), 5.9 GB before they relax (7.9 TB/s,
+// with 8 B per entry: then the bandwidth bound it, 748 us).  The list-streaming
+// sweep read every list of every step instead: 2625 us per sweep there.
 // 32 lanes per step because a wave per step repeats the scalar work 64 times;
 // all of a target's entries are asked for before any is used, as one more
 // access at a time exposes its whole latency (957 us).  N > 136: 768 threads,

@@ -40,8 +40,8 @@ struct PairSample {
 // and the coupling J.  Role 0 (j is l's partner): F_l changes by J conj(d_j)
 // a_p1 a_p2; role 1: by J conj(a_p1) d_j a_p2.  A list holds its role-0
 // entries, padded with J = 0 to 32, then its role-1 entries, padded to 16.  The
-// entries of a unit of 16 are stored as 16 p, then 16 J: 6 bytes each, as the
-// sweep of large N is bound by reading them.
+// entries of a unit of 16 are stored as 16 p, then 16 J: 6 bytes each (8: 748 us, not 674, for
+// the decisions of N = 256, 640 copies).
 constexpr int kUnitBytes = kListUnit * 6, kUnitJ = kListUnit * 2;  // of a unit; where its J begin
 
 // one step's draws: StepDraw<float>, opaque to the host
