@@ -178,7 +178,7 @@ def summarize_profiles(d):
             traffic.update({key + "fetch_kib_per_dispatch": fetch_kib, key + "write_kib_per_dispatch": write_kib,
                             key + "dispatches": [nf, nw], key + "hbm_bytes_per_launch": hbm,
                             key + "avg_duration_ns_kernel_trace": avg_ns.get(tag)})
-            lines.append(f"#   {tag}: FETCH_SIZE {fetch_kib:.0f} KiB x {f_scale:.4f} (copy-kernel scale) + WRITE_SIZE "
+            lines.append(f"#   {'the sweep' if tag == 'k_sweep' else tag}: FETCH_SIZE {fetch_kib:.0f} KiB x {f_scale:.4f} (copy-kernel scale) + WRITE_SIZE "
                          f"{write_kib:.0f} KiB x {w_scale:.4f} = {hbm / 1e9:.3f} GB per launch"
                          + (f"; over the kernel-trace average {avg_ns[tag] / 1e6:.3f} ms: {hbm / avg_ns[tag]:.0f} GB/s"
                             if tag in avg_ns else ""))
