@@ -18,8 +18,6 @@ __host__ __device__ inline size_t ahead_fixed_bytes(int max_N, int waves) {
     return (b + 15) & ~(size_t)15;
 }
 
-constexpr int kShortSlots = 4;  // entries per lane of lists no longer than 32 * kShortSlots
-
 // One workgroup per copy, one wave per step.  A step's update depends on the
 // steps before it only where one of them is accepted, and most are rejected:
 // the kWaves / 2 next steps are evaluated at once, each on the configuration
@@ -196,6 +194,8 @@ hipError_t ahead_b(const DevPtrs<R>& P, const ShapeInfo& sh, const AheadLaunch& 
 
 template <typename R>
 hipError_t ahead_t(const DevPtrs<R>& P, const ShapeInfo& sh, const AheadLaunch& L, int n_sweeps, hipStream_t st) {
+    // lists past the short ones have instances of 512 threads only
+    if (L.block != 512 && (sh.layout == kLayoutChunked || L.slots > kShortSlots)) return hipErrorInvalidValue;
     if (sh.layout != kLayoutChunked) {
         if (L.slots > 12) return ahead_b<R, 512, true, 16>(P, sh, L, n_sweeps, st);
         if (L.slots > 8) return ahead_b<R, 512, true, 12>(P, sh, L, n_sweeps, st);
@@ -211,10 +211,30 @@ hipError_t ahead_t(const DevPtrs<R>& P, const ShapeInfo& sh, const AheadLaunch& 
 
 }  // namespace
 
-size_t ahead_lds_bytes(int precision, int block, int max_N) {
-    const int w = block / 64;
-    return precision == RLPT_FP64 ? ahead_fixed_bytes<double>(max_N, w) + (size_t)w * max_N * 16
-                                  : ahead_fixed_bytes<float>(max_N, w) + (size_t)w * max_N * 8;
+size_t ahead_lds_bytes(int precision, const AheadLaunch& L) {
+    const int w = L.block / 64;
+    return precision == RLPT_FP64 ? ahead_fixed_bytes<double>(L.max_N, w) + (size_t)w * L.max_N * 16
+                                  : ahead_fixed_bytes<float>(L.max_N, w) + (size_t)w * L.max_N * 8;
+}
+
+bool ahead_plan(int precision, int layout, uint32_t longest, int max_N, AheadLaunch* L) {
+    L->max_N = max_N;
+    L->chunks = L->slots = 0;
+    L->block = 512;
+    if (layout == kLayoutChunked) {
+        L->chunks = (int)(longest + 63) / 64;
+        if (L->chunks > 6) return false;
+    } else {
+        L->slots = (int)(longest + 31) / 32;
+        if (L->slots > 16) return false;
+        const bool is_short = L->slots <= kShortSlots;
+        if (is_short) L->block = 1024;
+        // no wave without a step: the window is half the waves
+        while (L->block > 256 && L->block / 128 > max_N / 2) L->block /= 2;
+        if (!is_short && L->block < 512) return false;
+        while (is_short && L->block > 256 && ahead_lds_bytes(precision, *L) > kMaxLds) L->block /= 2;
+    }
+    return ahead_lds_bytes(precision, *L) <= kMaxLds;
 }
 
 hipError_t launch_sweep_ahead(int precision, const void* ptrs, const ShapeInfo& sh, const AheadLaunch& L, int n_sweeps,

@@ -921,24 +921,10 @@ void plan_ahead(rlpt_ctx* c, const ItemDev* items) {
     if (c->sh.cached || c->cfg.block_threads > 0 || c->cfg.copies_per_block > 0) return;
     AheadLaunch L{};
     L.items = items;
-    L.max_N = c->max_N;
-    if (c->sh.layout == kLayoutChunked) {
-        uint32_t longest = 0;
+    uint32_t longest = c->longest_list;
+    if (c->sh.layout == kLayoutChunked)
         for (uint32_t n : c->max_chunks) longest = std::max(longest, n);
-        L.chunks = (int)(longest + 63) / 64;
-        L.block = 512;
-        if (L.chunks > 6) return;
-    } else {
-        L.slots = (int)(c->longest_list + 31) / 32;
-        if (L.slots > 16) return;
-        L.block = c->sh.short_lists ? 1024 : 512;
-        // no wave without a step: the window is half the waves
-        while (L.block > 256 && L.block / 128 > c->max_N / 2) L.block /= 2;
-        if (!c->sh.short_lists && L.block < 512) return;
-    }
-    while (L.block > 256 && ahead_lds_bytes(c->cfg.precision, L.block, c->max_N) > 160 * 1024) L.block /= 2;
-    const size_t lds = ahead_lds_bytes(c->cfg.precision, L.block, c->max_N);
-    if (lds > 160 * 1024) return;
+    if (!ahead_plan(c->cfg.precision, c->sh.layout, longest, c->max_N, &L)) return;
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
@@ -1095,7 +1081,7 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
         for (int s = 0; s < n_graphs; ++s)
             for (int l = 0; l < graphs[s]->N; ++l)
                 longest = std::max(longest, graphs[s]->mode_start[l + 1] - graphs[s]->mode_start[l]);
-        c->sh.short_lists = longest <= 128 ? 1 : 0;
+        c->sh.short_lists = longest <= 32 * kShortSlots ? 1 : 0;
     }
     unsigned char* b = static_cast<unsigned char*>(d_workspace);
     fill_ptrs(c->pf, b, r);

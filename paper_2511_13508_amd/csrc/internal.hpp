@@ -157,6 +157,8 @@ struct DevPtrs {
     double* en_band;
 };
 
+constexpr size_t kMaxLds = 160 * 1024;  // bytes of a workgroup (gfx950)
+constexpr int kShortSlots = 4;   // entries per lane of a list that fits half a wave's registers
 constexpr int kAfterBaths = 8;   // baths of one sample that a workgroup measures after a sweep
 constexpr int kResyncParts = 8;  // term ranges of one energy recomputation (workgroups per copy group)
 constexpr int kBandSlack = 8 * 128;  // 32-bit words past a band that the banded products may read

@@ -400,7 +400,6 @@ __global__ __launch_bounds__(BLOCK) void k_stream_lists(DevPtrs<float> P, ShapeI
 // step's draws from the lane holding them.  Same chain, same draws as the
 // streaming sweep.  The host takes this path only when no padded list is
 // longer than 32 * kShortSlots entries.
-constexpr int kShortSlots = 4;
 
 // a step's draws plus the list bounds of its two modes
 template <typename R>

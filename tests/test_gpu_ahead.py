@@ -78,3 +78,22 @@ def test_ahead_five_to_sixteen_entries(oracle, Ns, precision):
         compare_fp64(*run_both(oracle, Ns, 0, 5, 2, 24, precision=precision, resync_interval=12))
     else:
         compare_fp32(*run_both(oracle, Ns, 0, 5, 2, 4, precision=precision))
+
+
+@pytest.mark.parametrize("Ns,z", [([995], 128), ([994], 128), ([1024], 128), ([1024, 24], 128)])
+def test_lists_past_the_short_sweep_at_the_largest_sizes_fp64(oracle, Ns, z):
+    """Lists of 129 to 512 entries have 512-thread instances only, whose LDS
+    holds 994 FP64 modes; larger samples keep the sweep of one step at a time."""
+    temps = synth.geometric_temps(0.3, 1.5, 2)
+    degree = [z if N > 100 else 0 for N in Ns]
+    graphs = [rlpt.Graph(N, SEED + i, mean_degree=d) for i, (N, d) in enumerate(zip(Ns, degree))]
+    ctx = make_ctx(graphs, temps, n_temps=2, n_reps=1, n_bins=10, precision=rlpt.FP64, resync_interval=4)
+    ctx.init(4)
+    ctx.sweep(6)
+    ctx.check()
+    ors = []
+    for mu, (N, d) in enumerate(zip(Ns, degree)):
+        pt = oracle_pt(oracle, oracle.Graph(N, SEED + mu, mean_degree=d), temps, mu, ctx.cfg, 4)
+        pt.run(6)
+        ors.append(pt)
+    compare_fp64(ctx, ors)
