@@ -87,6 +87,52 @@ static Tile default_tile_cached(int N) {
     return {std::min(512, 128 * ns), 1};
 }
 
+constexpr size_t kPairTableBytes = (size_t)64 << 30;  // most that tables in pair space may take
+
+// pairs that the widest of `parts` ranges of row tiles spans; tile: bounds of
+// each 16 rows' band values, in 64s
+int energy_columns(const std::vector<uint32_t>& tile, int parts) {
+    const int64_t n = (int64_t)tile.size() - 1;
+    int columns = 0;
+    for (int p = 0; p < parts; ++p) {
+        const int64_t t0 = n * p / parts, t1 = n * (p + 1) / parts;
+        if (t0 < t1) columns = std::max(columns, (int)(16 * (t1 - t0) + 4 * (tile[t1] - tile[t1 - 1])));
+    }
+    return columns;
+}
+
+// Ranges of the banded energy recomputation, which every context with a band
+// takes (energy.hip has the figures; it is faster at every size): 0 where the
+// terms are summed one by one, that is with a sample without a band (sparse
+// graphs, N > 256) or band tables past kPairTableBytes.
+int energy_parts(const rlpt_config& cfg, const rlpt_graph* const* g, int S) {
+    size_t bytes = 0;
+    int tiles = 1, max_N = 0;
+    for (int i = 0; i < S; ++i) {
+        if (g[i]->pair_modes.empty()) return 0;
+        bytes += (size_t)g[i]->energy_tile.back() * 512;
+        tiles = std::max(tiles, (int)g[i]->energy_tile.size() - 1);
+        max_N = std::max(max_N, g[i]->N);
+    }
+    if (bytes > kPairTableBytes) return 0;
+    // a tile per wave at least; otherwise about five blocks per compute unit,
+    // and partial energies that fit the static scratch
+    const size_t Rc = (size_t)cfg.n_temps * cfg.n_reps, blocks = (Rc + 15) / 16 * S;
+    const size_t fit = kStaticScratchBytes / (Rc * S * sizeof(double));
+    const size_t want = std::min<size_t>(kEnergyParts, std::max<size_t>(2, (1280 + blocks - 1) / blocks));
+    int parts = (int)std::min({want, std::max<size_t>(fit, 1), (size_t)(tiles + 3) / 4});
+    // a range's amplitudes and mode offsets fit a workgroup's LDS (from N = 230
+    // on in FP64, two ranges at least; the static scratch then holds up to
+    // 131072 copies' partial energies, four times what its entry point takes)
+    auto lds = [&](int n) {
+        int columns = 0;
+        for (int i = 0; i < S; ++i) columns = std::max(columns, energy_columns(g[i]->energy_tile, n));
+        return energy_lds_bytes(cfg.precision, max_N, columns);
+    };
+    while (parts < kEnergyParts && lds(parts) > kMaxLds) ++parts;
+    return lds(parts) <= kMaxLds ? parts : 0;
+}
+
 }  // namespace rlpt
 
 using namespace rlpt;
@@ -274,7 +320,6 @@ size_t pair_copies(const rlpt_config& cfg, int N) {
 // -> 522); their fields are then formed from the amplitudes in every sweep and
 // written only for a checkpoint.
 constexpr int kPairModes = 88;
-constexpr size_t kPairTableBytes = (size_t)64 << 30;
 
 std::vector<int> pair_samples(const rlpt_config& cfg, const rlpt_graph* const* g, int S) {
     std::vector<int> served;
@@ -289,27 +334,6 @@ std::vector<int> pair_samples(const rlpt_config& cfg, const rlpt_graph* const* g
     if (bytes > kPairTableBytes) served.clear();
     if (cfg.field_mode == RLPT_FIELDS_CACHED && (int)served.size() < S) served.clear();
     return served;
-}
-
-// Ranges of the banded energy recomputation, which every context with a band
-// takes (energy.hip has the figures; it is faster at every size): 0 where the
-// terms are summed one by one, that is with a sample without a band (sparse
-// graphs, N > 256) or band tables past kPairTableBytes.
-int energy_parts(const rlpt_config& cfg, const rlpt_graph* const* g, int S) {
-    size_t bytes = 0;
-    int tiles = 1;
-    for (int i = 0; i < S; ++i) {
-        if (g[i]->pair_modes.empty()) return 0;
-        bytes += (size_t)g[i]->energy_tile.back() * 512;
-        tiles = std::max(tiles, (int)g[i]->energy_tile.size() - 1);
-    }
-    if (bytes > kPairTableBytes) return 0;
-    // a tile per wave at least; otherwise about five blocks per compute unit,
-    // and partial energies that fit the static scratch
-    const size_t Rc = (size_t)cfg.n_temps * cfg.n_reps, blocks = (Rc + 15) / 16 * S;
-    const size_t fit = kStaticScratchBytes / (Rc * S * sizeof(double));
-    const size_t want = std::min<size_t>(kEnergyParts, std::max<size_t>(2, (1280 + blocks - 1) / blocks));
-    return (int)std::min({want, std::max<size_t>(fit, 1), (size_t)(tiles + 3) / 4});
 }
 
 int check_graphs(const rlpt_graph* const* g, int n) {
@@ -878,11 +902,7 @@ hipError_t build_energy(rlpt_ctx* c, const rlpt_graph* const* g, unsigned char* 
     for (int s = 0; s < c->S; ++s) {
         smp.push_back(at);
         const std::vector<uint32_t>& t = g[s]->energy_tile;
-        const int64_t n = (int64_t)t.size() - 1;
-        for (int p = 0; p < c->sh.en_parts; ++p) {
-            const int64_t t0 = n * p / c->sh.en_parts, t1 = n * (p + 1) / c->sh.en_parts;
-            if (t0 < t1) columns = std::max(columns, (int)(16 * (t1 - t0) + 4 * (t[t1] - t[t1 - 1])));
-        }
+        columns = std::max(columns, energy_columns(t, c->sh.en_parts));
         at.pair_base += (int64_t)g[s]->pair_modes.size();
         at.rank_base += (int64_t)g[s]->pair_rank.size();
         at.tile_base += (int64_t)t.size();

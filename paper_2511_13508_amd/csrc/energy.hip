@@ -15,6 +15,7 @@ namespace rlpt {
 namespace {
 
 constexpr int kRows = 16, kCols = 16;  // of a matrix-core tile: pairs, copies
+constexpr size_t kRedBytes = 4 * kCols * sizeof(double);  // the waves' sums, static LDS
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // every term's place above the diagonal: the operand of 4 columns holds, at
@@ -138,7 +139,7 @@ hipError_t fill_t(const void* ptrs, const ShapeInfo& sh, int64_t max_quads, hipS
 template <typename R>
 hipError_t band_t(const void* ptrs, const ShapeInfo& sh, hipStream_t st) {
     const int groups = (sh.copies_per_sample + kCols - 1) / kCols;
-    const size_t lds = (size_t)sh.spec_stride * kCols * 2 * sizeof(R) + (size_t)sh.en_columns * 4;
+    const size_t lds = energy_lds_bytes(sizeof(R) == 8 ? RLPT_FP64 : RLPT_FP32, sh.spec_stride, sh.en_columns) - kRedBytes;
     if (lds > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_energy_band<R>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -150,6 +151,11 @@ hipError_t band_t(const void* ptrs, const ShapeInfo& sh, hipStream_t st) {
 }
 
 }  // namespace
+
+// of a workgroup: the amplitudes of a copy tile, its pairs' offsets, the waves' sums
+size_t energy_lds_bytes(int precision, int max_N, int columns) {
+    return (size_t)max_N * kCols * 2 * (precision == RLPT_FP64 ? 8 : 4) + (size_t)columns * 4 + kRedBytes;
+}
 
 hipError_t launch_energy_fill(int precision, const void* ptrs, const ShapeInfo& sh, int64_t max_quads, hipStream_t st) {
     return precision == RLPT_FP64 ? fill_t<double>(ptrs, sh, max_quads, st) : fill_t<float>(ptrs, sh, max_quads, st);

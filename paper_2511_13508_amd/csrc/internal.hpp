@@ -223,7 +223,10 @@ constexpr size_t kStaticScratchBytes = (size_t)2 << 20;
 hipError_t static_scratch_address(void** out);
 hipError_t launch_energy_static(int precision, const void* ptrs, const ShapeInfo& sh, int n_copies, double* E,
                                 hipStream_t st);
-// banded FP64 energies (energy.hip): the table and the partial energies
+// banded FP64 energies (energy.hip): ranges of a sample, LDS of one, the table and the partial energies
+int energy_parts(const rlpt_config& cfg, const rlpt_graph* const* g, int S);
+int energy_columns(const std::vector<uint32_t>& tile, int parts);
+size_t energy_lds_bytes(int precision, int max_N, int columns);
 hipError_t launch_energy_fill(int precision, const void* ptrs, const ShapeInfo& sh, int64_t max_quads, hipStream_t st);
 hipError_t launch_energy_band(int precision, const void* ptrs, const ShapeInfo& sh, hipStream_t st);
 hipError_t launch_resync(int precision, const void* ptrs, const ShapeInfo& sh, int n_copies, int mode,

@@ -36,3 +36,19 @@ def test_banded_energies(oracle, Ns, T, reps, precision, graph):
         for c in {0, 1 % ctx.R, 15 % ctx.R, 16 % ctx.R, ctx.R - 1}:
             size = 2 * np.sum(np.abs(og.J) * np.prod(np.abs(a[c])[q], axis=1))
             assert abs(E[mu * ctx.R + c] - oracle.energy(og, a[c])) <= 1e-13 * max(size, 1.0), (N, c)
+
+
+@pytest.mark.parametrize("N,precision", [(256, rlpt.FP64), (230, rlpt.FP64), (256, rlpt.FP32)])
+def test_banded_energies_of_more_copies_than_the_scratch_has_room_for(oracle, N, precision):
+    """131074 copies: one range per copy would be all that the static scratch
+    holds, but a range's pairs have to fit a workgroup's LDS too."""
+    reps = 65537
+    ctx = make_ctx([rlpt.Graph(N, SEED)], [0.5, 1.0], n_temps=2, n_reps=reps, precision=precision, measure_interval=0)
+    ctx.init(3)
+    E = ctx.energy_fp64()
+    og = oracle.Graph(N, SEED)
+    q = np.asarray(og.quads).reshape(-1, 4)
+    for c in (0, 15, 16, 65537, ctx.R - 2, ctx.R - 1):
+        a = ctx.get_state(c, 1)
+        size = 2 * np.sum(np.abs(og.J) * np.prod(np.abs(a)[q], axis=1))
+        assert abs(E[c] - oracle.energy(og, a)) <= 1e-13 * max(size, 1.0), c

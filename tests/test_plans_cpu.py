@@ -35,3 +35,48 @@ int main() {
     assert [r for r in rows if r[0] == "bad"] == []
     assert [r[1:] for r in rows if r[0] == "edge"] == [["993", "1"], ["994", "1"], ["995", "0"], ["996", "0"]]
     assert [r[1:] for r in rows if r[0] == "short"] == [["0", "1", "1024"], ["1", "1", "256"]]
+
+
+def test_energy_ranges_fit_a_workgroup(tmp_path):
+    """The ranges of the banded energy recomputation fit a workgroup's LDS (the
+    amplitudes of 16 copies, 4 B per pair of a range, 512 B of sums) at every N
+    and number of copies, with partial energies that the entry point without
+    allocations has room for (its limit of 32768 copies)."""
+    rows = host_check.run(tmp_path, r"""
+#include <cstdio>
+#include "internal.hpp"
+using namespace rlpt;
+int main() {
+    for (int N : {4, 5, 17, 64, 128, 200, 229, 230, 243, 255, 256}) {
+        rlpt_graph_desc d{};
+        d.n_modes = N;
+        d.omega_kind = N == 4 ? RLPT_OMEGA_COMB : RLPT_OMEGA_RANDOM;
+        d.seed = 2511135081;
+        d.split_mask = RLPT_SPLIT_ALL;
+        rlpt_graph* g = nullptr;
+        if (rlpt_graph_build(&d, &g)) return 1;
+        for (int prec : {RLPT_FP32, RLPT_FP64})
+            for (int reps : {1, 50, 1000, 32768, 65536, 131072, 131073, 262144, 262145, 1 << 22}) {
+                rlpt_config c;
+                rlpt_config_default(&c);
+                c.n_reps = reps;
+                c.precision = prec;
+                const int parts = energy_parts(c, &g, 1);
+                const int tiles = (N * (N - 1) / 2 + 15) / 16;
+                size_t lds = 0;  // as the kernel lays it out
+                for (int p = 0; p < parts; ++p) {
+                    const int t0 = (int)((long)tiles * p / parts), t1 = (int)((long)tiles * (p + 1) / parts);
+                    if (t0 == t1) continue;
+                    const size_t n = 16 * (t1 - t0) + 4 * (g->energy_tile[t1] - g->energy_tile[t1 - 1]);
+                    const size_t b = (size_t)N * 16 * (prec == RLPT_FP64 ? 16 : 8) + 4 * n + 512;
+                    if (b > lds) lds = b;
+                }
+                const bool scratch = reps > 32768 || (size_t)reps * parts * 8 <= kStaticScratchBytes;
+                printf("%d %d %d %d %d %d\n", N, prec, reps, parts, (int)(lds <= 160 * 1024), (int)scratch);
+            }
+        rlpt_graph_free(g);
+    }
+}
+""")
+    assert len(rows) == 11 * 2 * 10
+    assert [r for r in rows if int(r[3]) < 1 or int(r[3]) > 64 or r[4] == "0" or r[5] == "0"] == []
