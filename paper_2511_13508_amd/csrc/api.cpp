@@ -545,10 +545,12 @@ bool measuring_at(const rlpt_ctx* c, int64_t n) {
     return n > c->cfg.measure_start && c->cfg.measure_interval > 0 && n % c->cfg.measure_interval == 0;
 }
 
-// cached-field mode: recompute every copy's fields from its amplitudes
-// (the pair-space sweep forms its own)
-int refresh_fields(rlpt_ctx* c, bool saving = false) {
-    if (!c->sh.cached || (!c->pair_launch.empty() && !saving)) return RLPT_OK;
+// cached-field mode: recompute every copy's fields from its amplitudes.  The
+// cached-field sweep carries its fields from sweep to sweep; the pair-space sweep
+// forms its own, so a context that it serves has fields only when a checkpoint
+// is written (pairs = true)
+int refresh_fields(rlpt_ctx* c, bool pairs = false) {
+    if (!c->sh.cached || pairs == c->pair_launch.empty()) return RLPT_OK;
     HIP_TRY(launch_fields_all(c->cfg.precision, c->ptrs(), c->sh, c->n_copies, c->stream), "fields launch");
     return RLPT_OK;
 }

@@ -63,3 +63,26 @@ def test_checkpoint_of_another_context_is_rejected(tmp_path):
         f.write(head)
     with pytest.raises(rlpt.RlptError):
         a.checkpoint_load(bad)
+
+
+@pytest.mark.parametrize("Ns,field_mode", [([48, 32], rlpt.FIELDS_CACHED), ([90], rlpt.FIELDS_CACHED),
+                                           ([48, 32], rlpt.FIELDS_STREAM), ([90], rlpt.FIELDS_STREAM)])
+def test_saving_leaves_the_run_alone(tmp_path, Ns, field_mode):
+    """A run that writes checkpoints has the bits of one that does not: the
+    cached fields that a sweep carries on are not formed anew by the save."""
+    graphs = [rlpt.Graph(N, SEED0 + 710 + i) for i, N in enumerate(Ns)]
+    temps = temps_geo(0.3, 1.5, 6)
+    kw = dict(n_temps=6, n_reps=2, field_mode=field_mode, resync_interval=0, n_bins=20)
+    a, b = (make_ctx(graphs, temps, **kw) for _ in range(2))
+    for c in (a, b):
+        c.init(9)
+    for _ in range(4):
+        a.sweep(7)
+        b.sweep(7)
+        a.checkpoint_save(str(tmp_path / "run.ckpt"))
+    got, ref = snapshot(a), snapshot(b)
+    assert np.array_equal(got[0], ref[0])
+    assert np.array_equal(got[1], ref[1])
+    assert np.array_equal(got[2], ref[2])
+    for k in ref[3]:
+        assert np.array_equal(got[3][k], ref[3][k]), k
