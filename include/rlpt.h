@@ -133,9 +133,10 @@ typedef struct rlpt_config {
     int32_t block_threads;    /* threads per workgroup of the list-streaming sweep: 0 = tuned, else 64..1024 */
     int32_t copies_per_block; /* copies per workgroup: 0 = tuned, else divides block_threads/64.  With
                                  either set, every sample is swept by streaming its lists; with both
-                                 0 the library picks a sweep by size (dense FP32 samples of 88 to 256
-                                 modes in pair space, few copies of small samples several steps at a
-                                 time).  The chain is the same. */
+                                 0 the library picks a sweep by size and by the acceptance to be
+                                 expected on the ladder (dense FP32 samples of 88 to 256 modes in
+                                 pair space unless most updates are accepted, few copies of small
+                                 samples several steps at a time).  The chain is the same. */
     int32_t list_layout;      /* per-mode list layout streamed by the sweep: RLPT_LAYOUT_AUTO,
                                  RLPT_LAYOUT_PACKED (8 B/entry, any N) or RLPT_LAYOUT_CHUNKED
                                  (entries grouped by partner mode in chunks of 4 sharing one

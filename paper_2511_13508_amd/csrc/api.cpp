@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "context.hpp"
+#include "route.hpp"
 
 namespace rlpt {
 
@@ -50,16 +51,21 @@ static Tile default_tile(int N) {
     return {256, 4};
 }
 
+static int compute_units() {
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
+        cus = 256;
+    return cus;
+}
+
 // Few copies for the chip: a copy's sweep is a chain of dependent two-mode
 // steps, so with fewer than two workgroups per compute unit the launch is
 // bound by a step's latency. Spread the copies first (fewer per workgroup),
 // then give each copy more waves (a step's list is cut into shorter pieces).
 static void spread_tile(const std::map<int, int>& counts, int copies_per_sample, int block_max, int* block,
                         std::map<int, int>* copies) {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        cus = 256;
+    const int cus = compute_units();
     auto n_blocks = [&]() {
         int64_t n = 0;
         for (const auto& nc : counts) {
@@ -309,29 +315,52 @@ size_t pair_copies(const rlpt_config& cfg, int N) {
 // Samples of a context that the pair-space sweep serves: those with a narrow
 // band (complete graphs, N <= 256) from kPairModes modes on, in FP32, unless
 // the caller names a launch tile (a tile belongs to the list-streaming
-// kernels).  Below, a sweep from the lists is as fast or faster (us per sweep,
-// lists -> pairs, 64 copies of 8 samples on an MI355X: N = 64 70 -> 67, 96 158
-// -> 115, 128 261 -> 186, 200 972 -> 502).  The tables take about 4 times the
-// lists' memory (the per-pair entries), so past kPairTableBytes the context
+// kernels).  Us per sweep, lists -> pairs, T = 0.25-1.5 on an MI355X, at 80, 320,
+// 640, 1024 and 5120 copies: N = 48 44 -> 51, 47 -> 55, 49 -> 61, 61 -> 74, 229 ->
+// 241; N = 64 60 -> 61, 66 -> 70, 73 -> 78, 99 -> 96, 288 -> 319; N = 72 68 -> 63,
+// 142 -> 78, 164 -> 90, 122 -> 111, 378 -> 380; N = 80 87 -> 76, 160 -> 89, 190 ->
+// 100, 144 -> 132, 491 -> 427; N = 96 107 -> 89, 200 -> 105, 248 -> 122, 196 ->
+// 164, 669 -> 556 (so N = 72 to 87, up to some 1000 copies, would gain as well).  The tables take about 4 times the
+// lists' memory (the per-pair entries) and the banded product N (N - 1) / 2 * 8
+// bytes per copy (261 KB at N = 256), so past kPairTableBytes the context
 // keeps to the lists.
-// Contexts in cached-field mode take it when it serves every sample (us per
+// A class of one N is served as a whole or not at all, and in streaming mode only
+// where it pays at the ladder's acceptance (temps; without it, for the size of a
+// workspace, all that a cold ladder would have it serve).
+// Contexts in cached-field mode take it when it serves every sample, at any
+// ladder: the cached-field sweep's cost follows the acceptance too (us per
 // sweep, cached fields -> pairs, 640 copies of 8 samples: N = 96 410 -> 121,
-// 128 600 -> 198, 256 1638 -> 979; 8 copies of one: 249 -> 74, 339 -> 101, 1103
-// -> 522); their fields are then formed from the amplitudes in every sweep and
-// written only for a checkpoint.
+// 128 600 -> 198, 256 1638 -> 979, and at T = 50-100, 0.98 accepted, N = 96
+// 1830 -> 569, 256 13980 -> 6000; 8 copies of one, cold: 249 -> 74, 339 -> 101,
+// 1103 -> 522); their fields are then formed from the amplitudes in every sweep
+// and written only for a checkpoint.
 constexpr int kPairModes = 88;
 
-std::vector<int> pair_samples(const rlpt_config& cfg, const rlpt_graph* const* g, int S) {
+std::vector<int> pair_samples(const rlpt_config& cfg, const rlpt_graph* const* g, int S, const double* temps) {
     std::vector<int> served;
     if (cfg.precision != RLPT_FP32 || cfg.block_threads > 0 || cfg.copies_per_block > 0) return served;
-    size_t bytes = 0;
+    std::map<int, bool> take;  // by N
     for (int i = 0; i < S; ++i) {
-        if (g[i]->N < kPairModes || g[i]->pair_modes.empty()) continue;
-        served.push_back(i);
-        bytes += g[i]->band_entries * 4 + g[i]->pair_modes.size() * pair_copies(cfg, g[i]->N) * 8 +
-                 kUnitBytes * (size_t)g[i]->pair_first.back();
+        const bool ok = g[i]->N >= kPairModes && !g[i]->pair_modes.empty();
+        take[g[i]->N] = (take.count(g[i]->N) ? take[g[i]->N] : true) && ok;
     }
-    if (bytes > kPairTableBytes) served.clear();
+    size_t bytes = 0;
+    for (int i = 0; i < S; ++i)
+        if (take[g[i]->N])
+            bytes += g[i]->band_entries * 4 + g[i]->pair_modes.size() * pair_copies(cfg, g[i]->N) * 8 +
+                     kUnitBytes * (size_t)g[i]->pair_first.back();
+    if (bytes > kPairTableBytes) return served;
+    if (temps && cfg.field_mode != RLPT_FIELDS_CACHED) {
+        const Ladder at = ladder_acceptance(std::vector<double>(temps, temps + cfg.n_temps), cfg.rho);
+        int64_t copies[2] = {0, 0};  // of the two launches, see build_pairs
+        for (int i = 0; i < S; ++i)
+            if (take[g[i]->N]) copies[g[i]->N > kGatherModes] += (int64_t)cfg.n_temps * cfg.n_reps;
+        for (auto& t : take)
+            t.second = t.second && pair_space_pays(t.first, copies[t.first > kGatherModes], cfg.shared_pairs != 0,
+                                                   compute_units(), at.mean, at.hottest);
+    }
+    for (int i = 0; i < S; ++i)
+        if (take[g[i]->N]) served.push_back(i);
     if (cfg.field_mode == RLPT_FIELDS_CACHED && (int)served.size() < S) served.clear();
     return served;
 }
@@ -343,10 +372,9 @@ int check_graphs(const rlpt_graph* const* g, int n) {
     return RLPT_OK;
 }
 
-Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layout) {
+Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layout, const std::vector<int>& served) {
     const size_t rb = cfg.precision == RLPT_FP64 ? 8 : 4;
     const size_t T = cfg.n_temps, reps = cfg.n_reps, Rc = T * reps, copies = Rc * S;
-    const std::vector<int> served = pair_samples(cfg, g, S);
     // tables of the cached-field sweep: only where it runs
     const bool cached = cfg.field_mode == RLPT_FIELDS_CACHED && served.empty();
     size_t modes = 0, entries = 0, chunks = 0, quads = 0, amp = 0, pairs = 0, pair_entries = 0;
@@ -827,17 +855,11 @@ hipError_t build_pairs(rlpt_ctx* c, const rlpt_graph* const* g, const std::vecto
     }
     // one launch for each kind of decision kernel, over samples of any N it
     // takes (largest N first): alone, a class of few copies leaves compute units
-    // idle.  A class is served as a whole or not at all.
+    // idle
     std::vector<std::vector<int>> groups(2);
-    for (const auto& kv : samples_by_N(c)) {
-        bool whole = true;
-        for (int s : kv.second) whole = whole && smp[s].N > 0;
-        std::vector<int>& group = groups[kv.first > kGatherModes ? 0 : 1];
-        for (int s : kv.second) {
-            if (whole) group.push_back(s);
-            else smp[s].N = 0;
-        }
-    }
+    for (const auto& kv : samples_by_N(c))
+        for (int s : kv.second)
+            if (smp[s].N > 0) groups[kv.first > kGatherModes ? 0 : 1].push_back(s);
     int first_item = 0;
     for (const auto& group : groups) {
         if (group.empty()) continue;
@@ -947,10 +969,7 @@ void plan_ahead(rlpt_ctx* c, const ItemDev* items) {
     if (c->sh.layout == kLayoutChunked)
         for (uint32_t n : c->max_chunks) longest = std::max(longest, n);
     if (!ahead_plan(c->cfg.precision, c->sh.layout, longest, c->max_N, &L)) return;
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        cus = 256;
+    const int cus = compute_units();
     // a long sweep gains more than a short one's fixed part costs
     const bool light = L.chunks <= 3 || c->cfg.precision == RLPT_FP64;
     const int per_cu2 = L.chunks > 0 ? (light ? 3 : 1) : L.max_N > 128 ? 6 : 3;  // copies per two compute units
@@ -1028,7 +1047,7 @@ int rlpt_workspace_size(const rlpt_config* cfg, const rlpt_graph* const* graphs,
     if ((rc = mlp_check_config(*cfg, graphs, n_graphs))) return rc;
     int layout = 0;
     if ((rc = choose_layout(*cfg, graphs, n_graphs, &layout))) return rc;
-    *bytes = plan(*cfg, graphs, n_graphs, layout).total;
+    *bytes = plan(*cfg, graphs, n_graphs, layout, pair_samples(*cfg, graphs, n_graphs, nullptr)).total;
     return RLPT_OK;
 }
 
@@ -1051,8 +1070,8 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
     }
     int layout = 0;
     if ((rc = choose_layout(*cfg, graphs, n_graphs, &layout))) return rc;
-    const Regions r = plan(*cfg, graphs, n_graphs, layout);
-    const std::vector<int> served = pair_samples(*cfg, graphs, n_graphs);
+    const std::vector<int> served = pair_samples(*cfg, graphs, n_graphs, temps);
+    const Regions r = plan(*cfg, graphs, n_graphs, layout, served);
     if (workspace_bytes < r.total) return fail(RLPT_E_NOMEM, "workspace smaller than rlpt_workspace_size()");
     rlpt_ctx* c = new (std::nothrow) rlpt_ctx;
     if (!c) return fail(RLPT_E_NOMEM, "out of host memory");

@@ -153,3 +153,28 @@ def test_mixed_sizes_replay_bitwise_in_graphs():
         assert np.array_equal(a.energies()[0], b.energies()[0])
         assert np.array_equal(a.energies()[1], b.energies()[1])
         assert a.counters() == b.counters()
+
+
+@pytest.mark.parametrize("Ns,cfg", [([96], {}), ([160, 40], {}), ([128], dict(shared_pairs=1))])
+def test_hot_ladders_are_swept_from_their_lists(oracle, Ns, cfg):
+    """Where most updates are accepted the lists are streamed: the bits of a
+    context that names the same launch tile, and the oracle's chain."""
+    temps = synth.geometric_temps(5.0, 20.0, 4)
+    graphs = [rlpt.Graph(N, SEED + i) for i, N in enumerate(Ns)]
+    kw = dict(n_temps=4, n_reps=2, n_bins=20, **cfg)
+    a = make_ctx(graphs, temps, **kw)
+    block, copies = a.tile()
+    b = make_ctx(graphs, temps, block_threads=int(block), copies_per_block=int(copies[0]), **kw)
+    assert len(set(copies)) == 1
+    for c in (a, b):
+        c.init(6)
+        c.sweep(3)
+    for mu in range(len(Ns)):
+        assert np.array_equal(a.get_state(mu * a.R, a.R), b.get_state(mu * b.R, b.R))
+    assert np.array_equal(a.energies()[0], b.energies()[0])
+    ors = []
+    for mu, N in enumerate(Ns):
+        pt = oracle_pt(oracle, oracle.Graph(N, SEED + mu), temps, mu, a.cfg, 6)
+        pt.run(3)
+        ors.append(pt)
+    compare_fp32(a, ors)

@@ -80,3 +80,50 @@ int main() {
 """)
     assert len(rows) == 11 * 2 * 10
     assert [r for r in rows if int(r[3]) < 1 or int(r[3]) > 64 or r[4] == "0" or r[5] == "0"] == []
+
+
+def test_pair_space_is_left_to_cold_ladders(tmp_path):
+    """The acceptance estimate rises with the temperature to 1, and the rule for
+    pair space takes every size on a ladder of 0.25 to 1.5 and none on one of 5
+    to 20, whatever the number of copies; once refused, a hotter ladder is
+    refused too."""
+    rows = host_check.run(tmp_path, r"""
+#include <cstdio>
+#include "route.hpp"
+using namespace rlpt;
+int main() {
+    for (int rho : {4, 2}) {
+        double last = 0;
+        for (double T = 0.05; T < 300; T *= 1.01) {
+            const double a = update_acceptance(T, rho);
+            if (!(a >= last && a > 0 && a < 1)) printf("bad acceptance %g %g\n", T, a);
+            last = a;
+        }
+    }
+    std::vector<double> t(40);
+    auto ladder = [&](double lo, double hi) {
+        for (int i = 0; i < 40; ++i) t[i] = lo * pow(hi / lo, i / 39.0);
+        return ladder_acceptance(t, 4);
+    };
+    const Ladder cold = ladder(0.25, 1.5), warm = ladder(1, 3), hot = ladder(5, 20);
+    printf("ladders %.3f %.3f %.3f %.3f\n", cold.mean, cold.hottest, warm.mean, warm.hottest);
+    for (int N = 88; N <= 256; ++N)
+        for (long copies = 1; copies < 100000; copies += 1 + copies / 7)
+            for (bool shared : {false, true}) {
+                bool last = true;
+                for (double f = 1; f < 8; f *= 1.1) {
+                    const Ladder l = ladder(0.25 * f, 1.5 * f);
+                    const bool now = pair_space_pays(N, copies, shared, 256, l.mean, l.hottest);
+                    if (now && !last) printf("bad order %d %ld\n", N, copies);
+                    last = now;
+                }
+                if (!pair_space_pays(N, copies, shared, 256, cold.mean, cold.hottest) ||
+                    pair_space_pays(N, copies, shared, 256, hot.mean, hot.hottest))
+                    printf("bad rule %d %ld %d\n", N, copies, (int)shared);
+            }
+}
+""")
+    assert [r for r in rows if r[0] == "bad"] == []
+    # measured on those ladders over N and copies: 0.076-0.085, 0.25-0.28; 0.335-0.345, 0.57-0.59
+    cold, hot_c, warm, hot_w = (float(x) for x in rows[0][1:])
+    assert abs(cold - 0.08) < 0.02 and abs(hot_c - 0.27) < 0.03 and abs(warm - 0.34) < 0.03 and abs(hot_w - 0.58) < 0.03
