@@ -947,7 +947,8 @@ hipError_t build_energy(rlpt_ctx* c, const rlpt_graph* const* g, unsigned char* 
     return e;
 }
 
-// few copies: several steps of a copy at a time (ahead.hip).  A copy takes 4 to
+// few copies: several steps of a copy at a time (ahead.hip) where the ladder's
+// acceptance lets it pay (ahead_pays).  A copy takes 4 to
 // 16 waves, so it pays while the chip has room for every copy's at once; past
 // that the waves of one copy only delay the others.  Us per sweep, one step at
 // a time -> several, on an MI355X:
@@ -974,6 +975,11 @@ void plan_ahead(rlpt_ctx* c, const ItemDev* items) {
     const bool light = L.chunks <= 3 || c->cfg.precision == RLPT_FP64;
     const int per_cu2 = L.chunks > 0 ? (light ? 3 : 1) : L.max_N > 128 ? 6 : 3;  // copies per two compute units
     if (c->n_copies > per_cu2 * cus / 2) return;
+    const bool crowded = c->cfg.precision == RLPT_FP64 && !c->sh.short_lists && c->launch.block_threads == 512 &&
+                         c->launch.n_items > cus;
+    if (!ahead_pays(c->cfg.precision, L, ahead_lds_bytes(c->cfg.precision, L), c->n_copies, cus, crowded, c->temps,
+                    c->sh.rho))
+        return;
     L.n_items = c->n_copies;
     c->ahead = L;
 }

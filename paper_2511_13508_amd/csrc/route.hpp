@@ -86,4 +86,46 @@ inline Ladder ladder_acceptance(const std::vector<double>& temps, int rho) {
     return l;
 }
 
+// Whether the sweep of several steps at a time (ahead.hip) pays on a ladder,
+// against one step at a time.  A round decides W steps unless one is accepted,
+// so a step costs p / (1 - (1 - p)^W) rounds at acceptance p (beside a part that
+// does not follow it, most of it a sweep's draws).  A round's time over a step's
+// of the other sweep was measured where nearly everything is accepted (T =
+// 50-100, 0.98; up to a copy per compute unit): packed lists of up to 128 entries 0.7-0.8 at N = 8,
+// 0.9-1.0 at 16, 1.4 from 128 on (1.06 in FP64 with 256 threads, N = 1024); of
+// up to 256, 384 and 512 entries 0.7, 0.8 and 0.9; chunked lists 1.25 at N = 32,
+// 1.45 at 36, 1.6 at 40, 1.8-1.9 from 48 on.  The hottest copies bound the sweep
+// while every workgroup is resident at once; beyond that the sum over the copies
+// does, or those that share a place.  In FP64 with 512 threads the other sweep is
+// half as fast past a copy per compute unit, too.  On the measured grid (268 sizes, numbers of copies
+// and types, three ladders) the choice is the faster sweep within 5 %, but for 14
+// points in 804 (6 to 35 %).  Us per sweep, one step at a time -> several, at T =
+// 0.25-1.5, 1-3 and 50-100: N = 1024 of mean degree 40, FP32, 256 copies 403 -> 177, 340,
+// 557; 768 copies 404 -> 323, 656, 1662; FP64 545 -> 307, 391, 546 and 549 ->
+// 810, 990, 1628; N = 48 FP32, 8 copies 30 -> 21, 32, 53; N = 24 23 -> 9, 12, 18.
+inline bool ahead_pays(int precision, const AheadLaunch& L, size_t lds_bytes, int64_t copies, int cus,
+                       bool others_crowd, const std::vector<double>& temps, int rho) {
+    double round;
+    if (L.chunks > 0) round = std::min(1.95, 1.3 + 0.04 * std::max(0, L.max_N - 32));
+    else if (L.slots > kShortSlots) round = L.slots > 12 ? 0.95 : L.slots > 8 ? 0.85 : 0.8;
+    else round = std::min(L.block == 256 ? 1.1 : 1.45, 0.45 + 0.028 * L.max_N);
+    const double W = L.block / 128;
+    const double fixed = 0.06 + 2.0 / L.max_N;
+    const int n = (int)temps.size();
+    std::vector<double> cost(n);  // of a copy at each bath, the hottest first, over the other sweep's
+    double mean = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const double p = update_acceptance(temps[n - 1 - i], rho);
+        cost[i] = round * (fixed + (1.0 - fixed) * p / (1.0 - pow(1.0 - p, W)));
+        mean += cost[i] / n;
+    }
+    // resident workgroups of a compute unit: by registers, and by LDS
+    const int by_regs = L.block == 1024 || (L.block == 512 && precision == RLPT_FP64) ? 1 : 2;
+    const int64_t room = (int64_t)cus * std::min(by_regs, (int)(kMaxLds / lds_bytes));
+    double t = std::max(cost[0], mean * (double)copies / (double)room);
+    for (int64_t k = 1; k * room < copies; ++k)  // of the k room + 1 hottest copies, k + 1 go one after another
+        t = std::max(t, (double)(k + 1) * cost[k * room * n / copies]);
+    return t < (!others_crowd ? 1.0 : L.chunks > 0 ? 1.65 : 1.7);
+}
+
 }  // namespace rlpt

@@ -97,3 +97,22 @@ def test_lists_past_the_short_sweep_at_the_largest_sizes_fp64(oracle, Ns, z):
         pt.run(6)
         ors.append(pt)
     compare_fp64(ctx, ors)
+
+
+@pytest.mark.parametrize("N,z,precision", [(256, 24, rlpt.FP64), (48, 0, rlpt.FP64), (256, 24, rlpt.FP32)])
+def test_hot_ladders_take_one_step_at_a_time(oracle, N, z, precision):
+    """Where most updates are accepted a step at a time is swept: the bits of a
+    context that names the same launch tile, and the oracle's chain."""
+    temps = synth.geometric_temps(20.0, 100.0, 3)
+    kw = dict(n_temps=3, n_reps=2, n_bins=10, precision=precision)
+    g = [rlpt.Graph(N, SEED, mean_degree=z)]
+    a = make_ctx(g, temps, **kw)
+    block, copies = a.tile()
+    b = make_ctx(g, temps, block_threads=int(block), copies_per_block=int(copies[0]), **kw)
+    for c in (a, b):
+        c.init(4)
+        c.sweep(6)
+    assert np.array_equal(a.get_state(), b.get_state()) and np.array_equal(a.energies()[0], b.energies()[0])
+    pt = oracle_pt(oracle, oracle.Graph(N, SEED, mean_degree=z), temps, 0, a.cfg, 4)
+    pt.run(6)
+    (compare_fp64 if precision == rlpt.FP64 else compare_fp32)(a, [pt])

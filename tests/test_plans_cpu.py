@@ -127,3 +127,33 @@ int main() {
     # measured on those ladders over N and copies: 0.076-0.085, 0.25-0.28; 0.335-0.345, 0.57-0.59
     cold, hot_c, warm, hot_w = (float(x) for x in rows[0][1:])
     assert abs(cold - 0.08) < 0.02 and abs(hot_c - 0.27) < 0.03 and abs(warm - 0.34) < 0.03 and abs(hot_w - 0.58) < 0.03
+
+
+def test_several_steps_are_left_to_cold_ladders(tmp_path):
+    """Short lists on ladders of T = 0.25 to 1.5 take several steps at a time
+    with a copy per compute unit, at any size; samples of 128 modes and more
+    with short lists on ladders of 50 to 100 do not (but lists past 128 entries
+    do, where a round costs less than the other sweep's step)."""
+    rows = host_check.run(tmp_path, r"""
+#include <cstdio>
+#include "route.hpp"
+using namespace rlpt;
+int main() {
+    std::vector<double> t(8);
+    for (int prec : {RLPT_FP32, RLPT_FP64})
+        for (int N = 8; N <= 1024; N += 8)
+            for (unsigned longest : {100u, 250u})
+                for (double f : {1.0, 100.0}) {
+                    for (int i = 0; i < 8; ++i) t[i] = 0.25 * f * pow(6.0, i / 7.0);
+                    AheadLaunch L{};
+                    if (!ahead_plan(prec, kLayoutPacked, longest, N, &L)) continue;
+                    const size_t lds = ahead_lds_bytes(prec, L);
+                    for (int copies : {8, 256})
+                        printf("%d %d %u %g %d %d\n", prec, N, longest, f, copies,
+                               (int)ahead_pays(prec, L, lds, copies, 256, false, t, 4));
+                }
+}
+""")
+    assert all(r[5] == "1" for r in rows if r[3] == "1")
+    hot = [r for r in rows if r[3] == "100" and int(r[1]) >= 128]
+    assert all(r[5] == ("1" if r[2] == "250" else "0") for r in hot) and len(hot) > 800
