@@ -181,13 +181,20 @@ typedef struct rlpt_config {
  * recomputation every 100 sweeps, renorm_tol 1e-6, drift_tol 1e-3, 100 bins. */
 int rlpt_config_default(rlpt_config* cfg);
 
-/* Device bytes needed for a context over graphs[0..n_graphs) (one per sample). */
+/* Device bytes for a context over graphs[0..n_graphs) (one per sample).  Beside
+ * lists, state and accumulators they hold the tables of the pair-space sweep of
+ * dense FP32 samples of 88 to 256 modes (about 4 times the lists, and 4 N (N - 1)
+ * bytes per copy: 261 KB at N = 256) and those of the energies of dense
+ * samples (about 8 bytes per term).  rlpt_create takes less: without room for
+ * them it sweeps from the lists (the size with block_threads set) and, with
+ * less still, sums the energies term by term.  Same chain up to rounding. */
 int rlpt_workspace_size(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t n_graphs,
                         size_t* bytes);
 
 /* Create a context.  temps[n_temps] (strictly ascending, > 0) is the ladder of
- * every sample.  d_workspace: caller-owned device memory of at least
- * rlpt_workspace_size() bytes, 256-byte aligned, alive until rlpt_destroy.
+ * every sample.  d_workspace: caller-owned device memory of
+ * rlpt_workspace_size() bytes (or less, see there), 256-byte aligned, alive until
+ * rlpt_destroy.
  * hip_stream: a hipStream_t (NULL = default stream).  Uploads lists,
  * couplings and ladders (host -> device copies on the stream).  The graphs
  * may be freed after this call.  Errors: RLPT_E_ARG, RLPT_E_NOMEM, RLPT_E_HIP. */

@@ -372,7 +372,8 @@ int check_graphs(const rlpt_graph* const* g, int n) {
     return RLPT_OK;
 }
 
-Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layout, const std::vector<int>& served) {
+Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layout, const std::vector<int>& served,
+             int en_parts) {
     const size_t rb = cfg.precision == RLPT_FP64 ? 8 : 4;
     const size_t T = cfg.n_temps, reps = cfg.n_reps, Rc = T * reps, copies = Rc * S;
     // tables of the cached-field sweep: only where it runs
@@ -441,7 +442,6 @@ Regions plan(const rlpt_config& cfg, const rlpt_graph* const* g, int S, int layo
     r.acc_end = L.off;
     r.scratch_doubles = std::max<size_t>(2 * amp, 8192);
     r.scratch = L.take(r.scratch_doubles * 8);
-    const int en_parts = energy_parts(cfg, g, S);
     r.rs_part = L.take(copies * std::max(en_parts, kResyncParts) * 8);
     if (en_parts > 0) {
         size_t np = 0, rank = 0, tiles = 0, band = 0;
@@ -1053,7 +1053,8 @@ int rlpt_workspace_size(const rlpt_config* cfg, const rlpt_graph* const* graphs,
     if ((rc = mlp_check_config(*cfg, graphs, n_graphs))) return rc;
     int layout = 0;
     if ((rc = choose_layout(*cfg, graphs, n_graphs, &layout))) return rc;
-    *bytes = plan(*cfg, graphs, n_graphs, layout, pair_samples(*cfg, graphs, n_graphs, nullptr)).total;
+    *bytes = plan(*cfg, graphs, n_graphs, layout, pair_samples(*cfg, graphs, n_graphs, nullptr),
+                  energy_parts(*cfg, graphs, n_graphs)).total;
     return RLPT_OK;
 }
 
@@ -1076,8 +1077,22 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
     }
     int layout = 0;
     if ((rc = choose_layout(*cfg, graphs, n_graphs, &layout))) return rc;
-    const std::vector<int> served = pair_samples(*cfg, graphs, n_graphs, temps);
-    const Regions r = plan(*cfg, graphs, n_graphs, layout, served);
+    // the tables in pair space (of the sweep, then of the energies) only where the
+    // workspace has room for them: they cost memory, and the lists serve as well
+    std::vector<int> served = pair_samples(*cfg, graphs, n_graphs, temps);
+    int parts = energy_parts(*cfg, graphs, n_graphs);
+    Regions r = plan(*cfg, graphs, n_graphs, layout, served, parts);
+    if (workspace_bytes < r.total && !served.empty()) {
+        const Regions less = plan(*cfg, graphs, n_graphs, layout, {}, parts);
+        if (less.total < r.total) {
+            served.clear();
+            r = less;
+        }
+    }
+    if (workspace_bytes < r.total && parts > 0) {
+        parts = 0;
+        r = plan(*cfg, graphs, n_graphs, layout, served, parts);
+    }
     if (workspace_bytes < r.total) return fail(RLPT_E_NOMEM, "workspace smaller than rlpt_workspace_size()");
     rlpt_ctx* c = new (std::nothrow) rlpt_ctx;
     if (!c) return fail(RLPT_E_NOMEM, "out of host memory");
@@ -1283,7 +1298,7 @@ int rlpt_create(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t
     else up(r.beta, b32);
     up(r.beta64, b64);
     std::vector<ItemDev> by_slot;
-    c->sh.en_parts = energy_parts(*cfg, graphs, n_graphs);
+    c->sh.en_parts = parts;
     if (c->sh.en_parts > 0 && e == hipSuccess) e = build_energy(c, graphs, b, r);
     if (!served.empty()) {
         if (e == hipSuccess) e = build_pairs(c, graphs, served, b, r);

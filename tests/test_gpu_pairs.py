@@ -178,3 +178,38 @@ def test_hot_ladders_are_swept_from_their_lists(oracle, Ns, cfg):
         pt.run(3)
         ors.append(pt)
     compare_fp32(a, ors)
+
+
+@pytest.mark.parametrize("Ns", [[96], [140, 40]])
+def test_smaller_workspaces_take_the_lists(oracle, monkeypatch, Ns):
+    """A workspace without room for the tables in pair space (the size of a
+    context that names a launch tile), or for those of the energies either, is
+    taken, and gives the same chain; one without room for the lists is not."""
+    size_of, want = rlpt.lib().rlpt_workspace_size, {}
+
+    def workspace_size(cfg, graphs, n, out):
+        rc = size_of(cfg, graphs, n, out)
+        want["size"] = out._obj.value
+        out._obj.value = want.get("give", out._obj.value)
+        return rc
+
+    monkeypatch.setattr(rlpt.lib(), "rlpt_workspace_size", workspace_size)
+    kw = dict(resync_interval=2)
+    full, ors = run_both(oracle, Ns, 4, 2, 3, **kw)
+    most = want["size"]
+    tile, _ = run_both(oracle, Ns, 4, 2, 1, block_threads=256, copies_per_block=1, **kw)
+    least = want["size"]
+    assert least < most
+    for give in (most, most - 256, least, least - 256):
+        want["give"] = give
+        ctx, _ = run_both(oracle, Ns, 4, 2, 3, **kw)
+        compare_fp32(ctx, ors)
+        if give < most:  # the lists' bits, whatever the size
+            ref = ref if give < most - 256 else ctx.get_state(0, ctx.R)
+            assert np.array_equal(ctx.get_state(0, ctx.R), ref)
+        E, E64 = ctx.energies()[0], ctx.energy_fp64()
+        assert np.all(np.abs(E - E64) <= 1e-4 * np.maximum(1.0, np.abs(E64)))
+    want["give"] = least // 4
+    with pytest.raises(rlpt.RlptError) as e:
+        run_both(oracle, Ns, 4, 2, 1, **kw)
+    assert e.value.code == rlpt.RLPT_E_NOMEM
