@@ -292,11 +292,15 @@ int rlpt_tune_load(const char* path);
 
 /* Measure tiles on one temporary context holding all graphs (cfg's ladder and
  * precision) in the caller's workspace (>= rlpt_workspace_size for all
- * graphs).  For each workgroup size the N classes are tuned in turn: every
- * copies-per-workgroup value of one N is timed on the whole launch (all N
- * together) with the other N at their current choice (built-in at first), and
- * the best is kept; sweeps_per_trial timed sweeps per tile after one warm-up
- * sweep; each trial is recorded in the registry under its N.
+ * graphs).  Trials time the launch over the samples that a context without an
+ * explicit tile sweeps from their lists, all N together; the samples that it
+ * sweeps in pair space have trials of their own, for contexts that stream them
+ * (hot ladders, small workspaces).  For each workgroup size the N classes are
+ * tuned in turn: every copies-per-workgroup value of one N is timed with the
+ * other N of the launch at their current choice (built-in at first), and the
+ * best is kept; sweeps_per_trial timed sweeps per tile after one warm-up
+ * sweep; each trial is recorded in the registry under its N.  (Contexts of few
+ * copies of short lists that take several steps at a time do not use a tile.)
  * *n_trials (may be NULL) receives the number of tiles timed.  Synchronous. */
 int rlpt_autotune(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32_t n_graphs,
                   const double* temps, void* d_workspace, size_t workspace_bytes, void* hip_stream,

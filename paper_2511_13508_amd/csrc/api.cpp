@@ -1795,57 +1795,69 @@ int rlpt_autotune(const rlpt_config* cfg, const rlpt_graph* const* graphs, int32
         return fail(RLPT_E_UNSUPPORTED, "the autotuner times the streaming sweep; use field_mode = RLPT_FIELDS_STREAM");
     if ((rc = check_graphs(graphs, n_graphs))) return rc;
     if (sweeps_per_trial < 1) return fail(RLPT_E_ARG, "sweeps_per_trial must be >= 1");
-    std::map<int, int> counts;
-    for (int i = 0; i < n_graphs; ++i) counts[graphs[i]->N] += 1;
     rlpt_config c2 = *cfg;
     c2.swap_interval = 1 << 30;  // timing covers sweeps only: one launch per trial
     c2.resync_interval = 0;
     c2.measure_interval = 0;
     c2.block_threads = 256;
     c2.copies_per_block = 1;
-    // every trial times the whole context's launch (all N together, as the
-    // context will run): per workgroup size, the N classes are tuned one after
-    // another, each over its copies per workgroup with the others at their
-    // current choice (built-in first), and each trial is recorded for its N
+    // a trial times the launch that a context without an explicit tile runs: the
+    // samples it sweeps from their lists, all N together.  Those that it sweeps in
+    // pair space come after, in launches of their own (for contexts that stream
+    // them: hot ladders, small workspaces).  Per workgroup size, the N classes
+    // are tuned one after another, each over its copies per workgroup with the
+    // others at their current choice (built-in first), and each trial is recorded
+    // for its N
+    std::vector<std::vector<int>> parts(2);
+    {
+        rlpt_config any_tile = *cfg;
+        any_tile.block_threads = any_tile.copies_per_block = 0;
+        const std::vector<int> served = temps ? pair_samples(any_tile, graphs, n_graphs, temps) : std::vector<int>();
+        for (int i = 0; i < n_graphs; ++i) parts[std::binary_search(served.begin(), served.end(), i)].push_back(i);
+    }
     rlpt_ctx* c = nullptr;
     rc = rlpt_create(&c2, graphs, n_graphs, temps, d_workspace, workspace_bytes, hip_stream, &c);
     if (rc) return rc;
     rc = rlpt_init(c, 1);
     int trials = 0;
-    for (int b = 64; b <= 1024 && rc == RLPT_OK; b *= 2) {
-        std::map<int, int> cur;
-        for (const auto& nc : counts) cur[nc.first] = std::max(1, std::min(default_tile(nc.first).copies, b / 64));
-        for (const auto& nc : counts) {
-            double best = -1.0;
-            int best_cp = cur[nc.first];
-            for (int cp = 1; cp <= b / 64 && rc == RLPT_OK; cp *= 2) {
-                std::map<int, int> copies = cur;
-                copies[nc.first] = cp;
-                if (build_items(c, b, copies) != RLPT_OK) continue;  // LDS limit
-                if ((rc = upload_items(c))) break;
-                if ((rc = rlpt_sweep(c, 1))) break;
-                c->timing = true;
-                if ((rc = rlpt_sweep(c, sweeps_per_trial))) break;
-                double ms = 0;
-                int64_t n = 0;
-                rc = rlpt_sweep_time_get(c, &ms, &n);
-                c->timing = false;
-                if (rc) break;
-                rlpt_tile t{};
-                t.n_modes = nc.first;
-                t.precision = cfg->precision;
-                t.shared_pairs = cfg->shared_pairs;
-                t.block_threads = b;
-                t.copies_per_block = cp;
-                t.ms_per_sweep = ms / sweeps_per_trial;
-                tune_record(t);
-                ++trials;
-                if (best < 0 || t.ms_per_sweep < best) {
-                    best = t.ms_per_sweep;
-                    best_cp = cp;
+    for (const std::vector<int>& part : parts) {
+        std::map<int, int> counts;
+        for (int i : part) counts[graphs[i]->N] += 1;
+        for (int b = 64; b <= 1024 && rc == RLPT_OK && !part.empty(); b *= 2) {
+            std::map<int, int> cur;
+            for (const auto& nc : counts) cur[nc.first] = std::max(1, std::min(default_tile(nc.first).copies, b / 64));
+            for (const auto& nc : counts) {
+                double best = -1.0;
+                int best_cp = cur[nc.first];
+                for (int cp = 1; cp <= b / 64 && rc == RLPT_OK; cp *= 2) {
+                    std::map<int, int> copies = cur;
+                    copies[nc.first] = cp;
+                    if (lay_items(c, b, copies, part, &c->items, &c->launch) != RLPT_OK) continue;  // LDS limit
+                    if ((rc = upload_items(c))) break;
+                    if ((rc = rlpt_sweep(c, 1))) break;
+                    c->timing = true;
+                    if ((rc = rlpt_sweep(c, sweeps_per_trial))) break;
+                    double ms = 0;
+                    int64_t n = 0;
+                    rc = rlpt_sweep_time_get(c, &ms, &n);
+                    c->timing = false;
+                    if (rc) break;
+                    rlpt_tile t{};
+                    t.n_modes = nc.first;
+                    t.precision = cfg->precision;
+                    t.shared_pairs = cfg->shared_pairs;
+                    t.block_threads = b;
+                    t.copies_per_block = cp;
+                    t.ms_per_sweep = ms / sweeps_per_trial;
+                    tune_record(t);
+                    ++trials;
+                    if (best < 0 || t.ms_per_sweep < best) {
+                        best = t.ms_per_sweep;
+                        best_cp = cp;
+                    }
                 }
+                cur[nc.first] = best_cp;
             }
-            cur[nc.first] = best_cp;
         }
     }
     int rc2 = rlpt_destroy(c);

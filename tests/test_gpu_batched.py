@@ -82,3 +82,25 @@ def test_batched_uneven_full_size_sampled(oracle):
         assert bad <= 1, (N, bad)
     obs = ctx.observables()
     assert np.all(obs["e_n"] == 2 * 2)  # two measurements x two replicas per (sample, T)
+
+
+def test_autotune_times_the_launches_that_run():
+    """Samples swept in pair space are no part of the trials of the others: a
+    tile of N = 32 (4 samples of 12 copies) is timed in a small part of the
+    milliseconds that streaming the lists of N = 256 takes; every N has its
+    entries, and an explicit ladder's context still takes the tuned tiles."""
+    graphs = [rlpt.Graph(N, SEED2 + 950 + i) for i, N in enumerate([256, 256, 32, 32, 32, 32])]
+    temps = synth.geometric_temps(0.4, 1.5, 6)
+    rlpt.tune_clear()
+    try:
+        rlpt.autotune(graphs, temps, n_temps=6, n_reps=2, sweeps_per_trial=4)
+        ms = {N: [e["ms_per_sweep"] for e in rlpt.tune_entries() if e["n_modes"] == N] for N in (32, 256)}
+        assert len(ms[32]) >= 13 and len(ms[256]) >= 13
+        assert max(ms[32]) < 0.5 * min(ms[256])
+        hot = make_ctx(graphs, synth.geometric_temps(5.0, 20.0, 6), n_temps=6, n_reps=2)
+        block, copies = hot.tile()
+        best = {N: min((e for e in rlpt.tune_entries() if e["n_modes"] == N and e["block_threads"] == block),
+                       key=lambda e: e["ms_per_sweep"])["copies_per_block"] for N in (32, 256)}
+        assert [int(c) for c in copies] == [best[g.N] for g in graphs]
+    finally:
+        rlpt.tune_clear()
