@@ -10,7 +10,10 @@ each followed by its swap round and measurement, then the FP64
 recomputation -- every part of the path.  Inputs are synthetic and already
 resident in HBM when timing starts.
 
-Prints one JSON line.  ``value`` = mode-updates/s (N mode-updates per copy
+Prints one JSON line of at most LINE_CHARS characters on stdout (contract_line:
+the headline, its roofline and the other blocks' main figures); the full
+report with every block's details goes to stderr as one JSON line, and to a
+file with --report.  ``value`` = mode-updates/s (N mode-updates per copy
 per sweep) over the timed steps.  ``roofline`` describes the sweep: for the
 pair-space sweep (the default tile) ``achieved`` = the bytes its method asks
 of memory per sweep (the banded couplings once per 16 copies, and for every
@@ -50,7 +53,7 @@ BATCHED_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "batched_traffic.json")
 # the sweep kernels and the host code that lays out their launches (tables, tiles, item order)
 KERNEL_SRC = [os.path.join(ROOT, "paper_2511_13508_amd", "csrc", f)
               for f in ("kernels.hip", "pairs.hip", "pairs.hpp", "ahead.hip", "device.hpp", "lists.hpp", "api.cpp")]
-PAIR_MODES = 88  # dense FP32 samples from here on take the pair-space sweep
+PAIR_MODES = 88  # dense FP32 samples from here on take the pair-space sweep (on ladders as cold as these)
 
 
 def log(msg):
@@ -393,7 +396,7 @@ def batched(args, short=False):
             per_N[N] = {"copies_per_block": t1_[N], "launch_ms_per_sweep": e["ms_per_sweep"]}
     # roofline of the built-in tiles' launch (the configuration whose fabric bytes are committed)
     traffic_b = traffic_for_current_kernel(bytes_per_sweep, BATCHED_TRAFFIC_FILE)
-    roof_b = {"bound": "hbm", "unit": "GB/s",
+    roof_b = {"bound": "latency", "unit": "GB/s",
               "kernel": "pair-space sweep of N >= 88 beside k_sweep of the smaller N (built-in tiles)",
               "list_bytes_of_a_streaming_sweep": bytes_per_sweep, "ms_per_launch": ms0,
               "hbm_peak_published": HBM_PEAK_GBS, "peak": HBM_PEAK_GBS, "traffic": traffic_b,
@@ -954,6 +957,51 @@ def equilibrated_state(src, dst, N, S, T, reps):
     dst.set_state(b.reshape(-1))
 
 
+LINE_CHARS = 1900  # of the stdout line: what reads it may keep only the end of a run's output
+
+
+def rounded(x, digits=6):
+    """x with every float at `digits` significant digits"""
+    if isinstance(x, float):
+        return float(f"{x:.{digits}g}")
+    if isinstance(x, dict):
+        return {k: rounded(v, digits) for k, v in x.items()}
+    if isinstance(x, (list, tuple)):
+        return [rounded(v, digits) for v in x]
+    return x
+
+
+def contract_line(out):
+    """The stdout line of a full report: its contract fields, the roofline's
+    figures, the tau_int-corrected ratios, and one figure of each other block.
+    Dropped from the end if longer than LINE_CHARS."""
+    keep = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+            "vs_baseline", "dtype", "data", "config")
+    line = {k: out[k] for k in keep if k in out}
+    if "roofline" in out:
+        line["roofline"] = {k: out["roofline"][k] for k in ("bound", "kernel", "achieved", "peak", "unit", "frac",
+                                                            "ms_per_launch", "traffic") if k in out["roofline"]}
+    if "cpu_baseline" in out:
+        line["cpu_baseline"] = {k: out["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind")
+                                if k in out["cpu_baseline"]}
+    more = {"sweeps_per_s": out.get("sweeps_per_s")}
+    tau = out.get("tau_int_corrected", {})
+    for name in ("learned_vs_plain_eff", "learned_subset_vs_plain_eff", "shared_vs_plain_eff"):
+        if name in tau:
+            more[name] = {k: tau[name][k] for k in ("ratio", "lo", "hi") if k in tau[name]}
+    if "learned_vs_plain_eff_E" in out.get("learned_n64", {}):
+        more["learned_n64_vs_plain_eff"] = {k: out["learned_n64"]["learned_vs_plain_eff_E"].get(k) for k in ("ratio", "lo", "hi")}
+    for name, field in (("cached_fields", "mode_updates_per_s"),
+                        ("n64_configuration", "mode_updates_per_s"), ("batched", "value"),
+                        ("sparse_graph", "mode_updates_per_s")):
+        if field in out.get(name, {}):
+            more[name] = out[name][field]
+    for k, v in more.items():
+        if v is not None and len(json.dumps(rounded({**line, k: v}))) <= LINE_CHARS:
+            line[k] = v
+    return json.dumps(rounded(line))
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -988,6 +1036,7 @@ def main():
     ap.add_argument("--harvest-rounds", type=int, default=400)
     ap.add_argument("--train-steps", type=int, default=600)
     ap.add_argument("--reeq", type=int, default=500, help="sweeps with swaps between harvest and the learned window")
+    ap.add_argument("--report", metavar="FILE", default=None, help="write the full report to FILE as well")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-cached", action="store_true", help="skip the cached-field, sparse, IPR and N=64 runs")
     ap.add_argument("--no-n64", action="store_true", help="skip the N=64 physics run and learned comparison")
@@ -1129,7 +1178,9 @@ def main():
     achieved = bytes_per_launch / t_launch / 1e9
     traffic = traffic_for_current_kernel(bytes_per_launch)
     log(f"{value:.4g} mode-updates/s; sweep kernel {kms / launches:.3f} ms/launch, {achieved:.0f} GB/s algorithmic")
-    roof = {"bound": "hbm", "achieved": achieved, "unit": "GB/s",
+    # the pair-space sweep's time is the chains of accepted updates of the hottest copies; the bytes' share of the
+    # HBM peak says how far it is from the next bound
+    roof = {"bound": "latency" if in_pairs else "hbm", "achieved": achieved, "unit": "GB/s",
             "kernel": "k_pair_product + k_pair_reduce + k_pair_decide" if in_pairs else "k_sweep",
             "ms_per_launch": kms / launches, "accepted_per_sweep": accepted["plain"],
             "algorithmic_bytes_per_launch": bytes_per_launch, "list_bytes_of_a_streaming_sweep": list_bytes,
@@ -1235,7 +1286,7 @@ def main():
             tau["shared_pairs"]["ms_per_launch"] = kms2 / launches2
             if in_pairs:
                 tau["shared_pairs"]["roofline"] = {
-                    "bound": "hbm", "achieved": b2 / t2 / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                    "bound": "latency", "achieved": b2 / t2 / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": b2 / t2 / 1e9 / HBM_PEAK_GBS, "algorithmic_bytes_per_launch": b2}
             tau["shared_vs_plain_eff"] = eff_ratio(tE2, tau_plain_E, args.sweeps / el2, sweeps_per_s)
             ctx.close()
@@ -1332,7 +1383,12 @@ def main():
             nthr = os.cpu_count() or 1
         log(f"cpu baseline: oracle on {nthr} threads for ~{args.cpu_seconds:.0f} s")
         out["cpu_baseline"] = cpu_baseline(N, temps, reps, args.cpu_seconds, nthr)
-    print(json.dumps(out), flush=True)
+    report = json.dumps(out)
+    print(report, file=sys.stderr, flush=True)
+    if args.report:
+        with open(args.report, "w") as f:
+            f.write(report + "\n")
+    print(contract_line(out), flush=True)
 
 
 if __name__ == "__main__":

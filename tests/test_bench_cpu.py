@@ -138,3 +138,32 @@ def test_fabric_traffic_is_the_counters_scaled_by_the_copy_calibration(tmp_path,
     t["kernel_source_sha"] = "0" * 16
     json.dump(t, open(bench.TRAFFIC_FILE, "w"))
     assert bench.traffic_for_current_kernel(1.0, bench.TRAFFIC_FILE) is None
+
+
+@pytest.mark.parametrize("blow_up", [1, 400])
+def test_stdout_line_is_short_and_holds_the_contract(blow_up):
+    """The line stays within LINE_CHARS whatever the report holds beside the
+    contract, and keeps the contract's fields and the ratios."""
+    import json
+    ratio = {"ratio": [1.23456789] * 4, "lo": [0.9] * 4, "hi": [1.4] * 4, "status": ["faster"] * 4, "method": "m" * 120}
+    out = {"metric": bench.METRIC, "value": 188877012.345, "unit": "mode-updates/s", "n_gpus": 1, "steps": 20, "warmup": 5,
+           "ms_per_step": 86.744123456, "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32",
+           "data": "synthetic", "config": {"workload": "w" * 150, "n_modes": 256, "terms_per_sample": [1388839] * 8},
+           "roofline": {"bound": "latency", "kernel": "k", "achieved": 2714.2, "peak": 7935.0, "unit": "GB/s", "frac": 0.342,
+                        "ms_per_launch": 0.8447, "peak_kind": "p" * 300, "list_stream_probe": {"rounds": [1.0] * 50}},
+           "sweeps_per_s": 1152.8, "tau_int_corrected": {"learned_vs_plain_eff": ratio, "shared_vs_plain_eff": ratio,
+                                                          "plain": {"tau": [[1.0] * 8] * blow_up}},
+           "learned_n64": {"learned_vs_plain_eff_E": ratio, "plain": list(range(blow_up))},
+           "batched": {"value": 8.9e8, "per_N": {str(i): 1.0 for i in range(blow_up)}},
+           "sparse_graph": {"mode_updates_per_s": [1.0] * blow_up},
+           "cpu_baseline": {"value": 155347.8, "unit": "mode-updates/s", "cores": 16, "kind": "oracle", "sample": "s" * 200}}
+    text = bench.contract_line(out)
+    assert len(text) <= bench.LINE_CHARS and "\n" not in text
+    line = json.loads(text)
+    for k in ("metric", "unit", "n_gpus", "steps", "warmup", "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config"):
+        assert line[k] == out[k], k
+    assert line["value"] == pytest.approx(out["value"], rel=1e-5)
+    assert line["ms_per_step"] == pytest.approx(out["ms_per_step"], rel=1e-5)
+    assert line["roofline"]["frac"] == pytest.approx(0.342) and line["cpu_baseline"]["value"] == pytest.approx(155347.8, rel=1e-5)
+    assert line["learned_vs_plain_eff"]["ratio"] == pytest.approx([1.23457] * 4, rel=1e-5)
+    assert ("sparse_graph" in line) == (blow_up == 1)
