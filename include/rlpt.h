@@ -11,7 +11,10 @@
  *  - Host pointers are plain caller-owned arrays.  Device memory for a context
  *    is ONE caller-owned workspace (e.g. a torch uint8 tensor), sized by
  *    rlpt_workspace_size(); the library never allocates device memory for a
- *    context and never frees the workspace.  The stream is caller-owned too.
+ *    context and never frees the workspace.  The stream is caller-owned too;
+ *    a context of mixed sizes has a second one for part of a sweep's kernels,
+ *    forked from the caller's and joined to it within the same call, so work
+ *    ordered after the call on the caller's stream is ordered after all of it.
  *  - Work submitted by rlpt_init / rlpt_sweep / rlpt_swap is asynchronous on
  *    the context's stream.  Calls that return host data synchronise the stream.
  *  - Complex amplitudes cross the boundary as interleaved (re, im) doubles.

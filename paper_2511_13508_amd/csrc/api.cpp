@@ -820,8 +820,9 @@ std::vector<ItemDev> slot_items(const rlpt_ctx* c, const std::vector<std::vector
 }
 
 // pair-space sweep: uploads the samples' band structure, fills the tables on
-// the device from the lists already there, and lays out the launches: one per
-// N it serves, and the list-streaming kernel's over the items of the others
+// the device from the lists already there, and lays out the launches: one for N
+// up to kGatherModes, one above, and the list-streaming kernel's over the items
+// of the others
 hipError_t build_pairs(rlpt_ctx* c, const rlpt_graph* const* g, const std::vector<int>& served,
                        unsigned char* b, const Regions& r) {
     fill_pair_ptrs(c->pairs, b, r, c->max_N);
@@ -868,6 +869,7 @@ hipError_t build_pairs(rlpt_ctx* c, const rlpt_graph* const* g, const std::vecto
         L.first = first_item;
         L.samples = (int)group.size();
         L.n = L.samples * c->Rc;
+        L.threads = pairs_decide_threads(L.N, L.n, compute_units());
         const int per_block = pairs_product_waves(L.N) * pairs_tiles_per_wave(L.N);
         for (int s : group) {
             const std::vector<uint32_t>& t = g[s]->pair_tile;

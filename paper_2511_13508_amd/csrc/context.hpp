@@ -31,8 +31,8 @@ struct rlpt_ctx {
     SweepLaunch launch{};
     DevPtrs<float> pf{};
     DevPtrs<double> pd{};
-    // pair-space sweep: its tables and one launch per N it serves; the samples
-    // it does not serve are swept from their lists (rest)
+    // pair-space sweep: its tables, and a launch for N up to kGatherModes and one
+    // above; the samples it does not serve are swept from their lists (rest)
     rlpt::PairDev pairs{};
     std::vector<rlpt::PairLaunch> pair_launch;
     DevPtrs<float> pf_rest{};

@@ -191,10 +191,10 @@ __device__ inline void draw_sweep(const PairDev& Q, const ShapeInfo& sh, int sam
 // each product, formed from the amplitudes in LDS, feeds two row tiles.
 // v_mfma_f32_16x16x4_f32: FP32 operands and accumulation.
 // Blocks past the product's draw the copies' sweeps.
-// The FP32 matrix cores bound it (busy 45 % of the time): per 4 columns a wave
-// issues 4 products of 32 cycles and forms its operands from 3 LDS reads, so
-// what else it issues is kept off the vector ALU (scalar tile, immediate
-// offsets) and the loads in flight.  Eight waves share the amplitudes of large
+// It takes twice the time of its matrix-core products (4 of 32 cycles per 4
+// columns of a wave's 32 rows); what a wave issues between them, 3 LDS reads and the
+// operands they form, is the rest, so that is kept off the vector ALU where it can be
+// (scalar tile, immediate offsets) and the loads in flight.  Eight waves share the amplitudes of large
 // N: six waves per SIMD instead of four.  N = 256, 640 copies of 8 samples (the
 // draws included): 166 us as first written, 149 with
 // scalar addresses, 137 with eight waves (68 at the matrix cores' rate).
@@ -769,14 +769,22 @@ hipError_t launch_pair_fields(const DevPtrs<float>& P, const PairDev& Q, const S
 
 hipError_t launch_pair_decide(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& sh, const PairLaunch& L,
                               hipStream_t st) {
-    if (L.N > kGatherModes) return decide_b<768, 32, 4, 9, false>(P, Q, sh, L, st);
+    switch (L.threads) {
+        case 512: return decide_b<512, 16, 6, 10, true>(P, Q, sh, L, st);
+        case 768: return decide_b<768, 32, 4, 9, false>(P, Q, sh, L, st);
+        case 1024: return decide_b<1024, 16, 6, 10, true>(P, Q, sh, L, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+int pairs_decide_threads(int N, int copies, int cus) {
+    if (N > kGatherModes) return 768;
     // A copy's chain of accepted updates is latency; 1024 threads shorten it,
-    // 512 let a compute unit (256 of them) interleave two copies' chains.  Us
-    // per sweep, 1024 -> 512: N = 96, 640 copies 121 -> 143, 960 146 -> 156, 1280
+    // 512 let a compute unit interleave two copies' chains.  Us per sweep on 256
+    // units, 1024 -> 512: N = 96, 640 copies 121 -> 143, 960 146 -> 156, 1280
     // 180 -> 167, 3200 461 -> 366; N = 128 198 -> 237, 255 -> 280, 331 -> 314,
     // 809 -> 675; 1024 copies beside a list sweep 381 -> 354.
-    return L.n >= 4 * 256 ? decide_b<512, 16, 6, 10, true>(P, Q, sh, L, st)
-                          : decide_b<1024, 16, 6, 10, true>(P, Q, sh, L, st);
+    return copies >= 4 * cus ? 512 : 1024;
 }
 
 hipError_t launch_pairs_tables(const DevPtrs<float>& P, const PairDev& Q, const ShapeInfo& sh, int n_samples, int max_N,

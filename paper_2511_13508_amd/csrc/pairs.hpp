@@ -68,15 +68,19 @@ struct PairDev {
     int32_t max_steps;
 };
 
-// what one launch covers: items [first, first + n), copies of samples of one N
+// what one launch covers: items [first, first + n), copies of samples of any N
+// up to the launch's N on the same side of kGatherModes; N sizes the grid and
+// the LDS, each block reads its own sample's
 struct PairLaunch {
     int N, first, n;
+    int threads;  // per workgroup of the decisions
     int samples;  // the launch's samples: every `samples`-th item is of one of them
     int columns;  // most columns (and 4) that the row tiles of one product workgroup span
 };
 
 int pairs_product_waves(int N);   // waves per workgroup of the banded product
 int pairs_tiles_per_wave(int N);  // row tiles per wave of the banded product
+int pairs_decide_threads(int N, int copies, int cus);
 
 // fills band, desc and list of every sample (on the stream) from the context's
 // lists and by-term arrays; band and list must hold zeros
