@@ -583,6 +583,33 @@ int refresh_fields(rlpt_ctx* c, bool pairs = false) {
     return RLPT_OK;
 }
 
+// n sweeps of a context that the pair-space sweep serves.  The samples swept from
+// their lists run beside the others' decisions, on the context's own stream; it
+// is joined whatever fails after the fork, so that nothing of the call is left
+// unordered on the caller's stream (or open in its capture)
+hipError_t sweep_in_pairs(rlpt_ctx* c, int n) {
+    hipError_t e = hipSuccess;
+    bool forked = false;
+    for (int w = 0; w < n && e == hipSuccess; ++w) {
+        for (const PairLaunch& L : c->pair_launch)
+            if (e == hipSuccess) e = launch_pair_fields(c->pf, c->pairs, c->sh, L, w, c->stream);
+        if (c->side && w == 0 && e == hipSuccess) {
+            e = hipEventRecord(c->fork, c->stream);
+            if (e == hipSuccess) e = hipStreamWaitEvent(c->side, c->fork, 0);
+            forked = e == hipSuccess;
+            if (e == hipSuccess) e = launch_sweep(RLPT_FP32, &c->pf_rest, c->sh, c->rest, n, c->side);
+        }
+        for (const PairLaunch& L : c->pair_launch)
+            if (e == hipSuccess) e = launch_pair_decide(c->pf, c->pairs, c->sh, L, c->stream);
+    }
+    if (forked) {
+        hipError_t j = hipEventRecord(c->join, c->side);
+        if (j == hipSuccess) j = hipStreamWaitEvent(c->stream, c->join, 0);
+        if (e == hipSuccess) e = j;
+    }
+    return e;
+}
+
 // enqueue n sweeps starting after `done` completed sweeps (no host mirror update)
 int enqueue_sweeps(rlpt_ctx* c, int64_t done, int64_t n, int64_t* swaps_added) {
     const rlpt_config& cfg = c->cfg;
@@ -612,19 +639,7 @@ int enqueue_sweeps(rlpt_ctx* c, int64_t done, int64_t n, int64_t* swaps_added) {
         } else if (c->pair_launch.empty()) {
             HIP_TRY(launch_sweep(cfg.precision, c->ptrs(), c->sh, c->launch, (int)step, c->stream), "sweep launch");
         } else {
-            for (int w = 0; w < (int)step; ++w) {
-                for (const PairLaunch& L : c->pair_launch)
-                    HIP_TRY(launch_pair_fields(c->pf, c->pairs, c->sh, L, w, c->stream), "sweep launch");
-                if (c->side && w == 0) {  // the samples swept from their lists run beside the others' decisions
-                    HIP_TRY(hipEventRecord(c->fork, c->stream), "fork");
-                    HIP_TRY(hipStreamWaitEvent(c->side, c->fork, 0), "fork");
-                    HIP_TRY(launch_sweep(RLPT_FP32, &c->pf_rest, c->sh, c->rest, (int)step, c->side), "sweep launch");
-                    HIP_TRY(hipEventRecord(c->join, c->side), "join");
-                }
-                for (const PairLaunch& L : c->pair_launch)
-                    HIP_TRY(launch_pair_decide(c->pf, c->pairs, c->sh, L, c->stream), "sweep launch");
-            }
-            if (c->side) HIP_TRY(hipStreamWaitEvent(c->stream, c->join, 0), "join");
+            HIP_TRY(sweep_in_pairs(c, (int)step), "sweep launch");
         }
         if (ev.first) {
             HIP_TRY(hipEventRecord(ev.second, c->stream), "event record");
