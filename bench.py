@@ -52,7 +52,8 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_n256_traffic.json")
 BATCHED_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "batched_traffic.json")
 # the sweep kernels and the host code that lays out their launches (tables, tiles, item order)
 KERNEL_SRC = [os.path.join(ROOT, "paper_2511_13508_amd", "csrc", f)
-              for f in ("kernels.hip", "pairs.hip", "pairs.hpp", "ahead.hip", "device.hpp", "lists.hpp", "api.cpp")]
+              for f in ("kernels.hip", "pairs.hip", "pairs.hpp", "ahead.hip", "device.hpp", "lists.hpp", "route.hpp",
+                        "api.cpp")]
 PAIR_MODES = 88  # dense FP32 samples from here on take the pair-space sweep (on ladders as cold as these)
 
 

@@ -320,10 +320,11 @@ size_t pair_copies(const rlpt_config& cfg, int N) {
 // 241; N = 64 60 -> 61, 66 -> 70, 73 -> 78, 99 -> 96, 288 -> 319; N = 72 68 -> 63,
 // 142 -> 78, 164 -> 90, 122 -> 111, 378 -> 380; N = 80 87 -> 76, 160 -> 89, 190 ->
 // 100, 144 -> 132, 491 -> 427; N = 96 107 -> 89, 200 -> 105, 248 -> 122, 196 ->
-// 164, 669 -> 556 (so N = 72 to 87, up to some 1000 copies, would gain as well).  The tables take about 4 times the
-// lists' memory (the per-pair entries) and the banded product N (N - 1) / 2 * 8
-// bytes per copy (261 KB at N = 256), so past kPairTableBytes the context
-// keeps to the lists.
+// 164, 669 -> 556 (so N = 72 to 87, up to some 1000 copies, would gain as well).
+// The tables take about 4 times the lists' memory (the per-pair entries) and the
+// banded product N (N - 1) / 2 * 8 bytes per copy (261 KB at N = 256), so past
+// kPairTableBytes the context keeps to the lists, as it does without room for
+// them in the workspace.
 // A class of one N is served as a whole or not at all, and in streaming mode only
 // where it pays at the ladder's acceptance (temps; without it, for the size of a
 // workspace, all that a cold ladder would have it serve).
@@ -965,10 +966,10 @@ hipError_t build_energy(rlpt_ctx* c, const rlpt_graph* const* g, unsigned char* 
 }
 
 // few copies: several steps of a copy at a time (ahead.hip) where the ladder's
-// acceptance lets it pay (ahead_pays).  A copy takes 4 to
-// 16 waves, so it pays while the chip has room for every copy's at once; past
-// that the waves of one copy only delay the others.  Us per sweep, one step at
-// a time -> several, on an MI355X:
+// acceptance lets it pay (ahead_pays).  A copy takes 4 to 16 waves, so it pays
+// while the chip has room for every copy's at once; past that the waves of one
+// copy only delay the others.  Us per sweep, one step at a time -> several, T =
+// 0.25-1.5 on an MI355X:
 // packed lists of up to 16 entries per lane: N = 1024 of mean degree 32, 320
 // copies 412 -> 191, 640 416 -> 285, 1280 527 -> 525; N = 16, 16 copies 18 -> 14,
 // 384 18 -> 16, 640 18 -> 21; N = 24, 8 copies 29 -> 13, 384 31 -> 18 (FP64 57 ->

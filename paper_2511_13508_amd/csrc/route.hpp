@@ -36,12 +36,17 @@ inline double update_acceptance(double T, int rho) {
 // acceptance that was measured over N and the number of copies (us per sweep at
 // two ladders, T = 0.25-1.5 and 1-3, both sweeps on an MI355X; where the lines
 // cross, by linear interpolation).  With at most a copy per compute unit the
-// chain of the hottest bath is the sweep's time, with more the mean of all.  The lists' side
-// is uneven (its tiles change with the number of copies), hence a table.  Lists
-// against pairs, cold and warm ladder: N = 96, 8 copies 103 against 65 and 121, 640 copies 248
-// against 122 and 248, 2048 copies 281 against 244 and 511; N = 128, 640 copies
-// 289 against 197 and 415; N = 256, 8 copies 954 against 430 and 994, 640
-// copies 2618 against 869 and 2133 (3892 at T = 2-6).
+// chain of the hottest bath is the sweep's time, with more the mean of all.  The
+// lists' side is uneven (its tiles change with the number of copies), hence a
+// table.  Lists against pairs, cold and warm ladder: N = 96, 8 copies 103 against
+// 65 and 121, 640 copies 248 against 122 and 248, 2048 copies 281 against 244 and
+// 511; N = 128, 640 copies 289 against 197 and 415; N = 256, 8 copies 954 against
+// 430 and 994, 640 copies 2618 against 869 and 2133 (3892 at T = 2-6).
+// In equilibrium, that is: the first sweeps from a random state accept more, on
+// any ladder, and take longer (N = 128, 640 copies, T = 0.25-1.5: 594, 433, 374, 337
+// against 328 from the lists, level after the fourth sweep and ahead in all after some
+// ten; N = 256 the first only, 3246 against 2626).  The sweep does not change in a
+// run: replayed graphs and resumed runs have the same bits.
 inline bool pair_space_pays(int N, int64_t copies, bool shared_pairs, int cus, double mean, double hottest) {
     struct Row {
         int N;
