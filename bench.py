@@ -415,7 +415,8 @@ def batched(args, short=False):
            "per_N_alone": alone,
            "tile_builtin": {"block": b0, "copies_per_block": t0_}, "tile_tuned": {"block": b1, "copies_per_block": t1_},
            "autotune": {"trials": n_trials, "seconds": t_tune,
-                        "method": "per workgroup size, each N's copies per workgroup timed on the whole launch "
+                        "method": "per workgroup size, each N's copies per workgroup timed on the launch over the "
+                                  "samples swept from their lists (those in pair space in one of their own) "
                                   "with the other N at their current choice", "chosen_trials": per_N}}
     log(f"batched: {v1:.4g} mode-updates/s tuned, {v0:.4g} built-in")
     return out
